@@ -56,6 +56,7 @@
 namespace cpm {
 namespace {
 
+typedef double d2 __attribute__((ext_vector_type(2)));
 typedef double d4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 
@@ -288,6 +289,12 @@ __global__ __launch_bounds__(64 * MR_WAVES) void block_matvec_rows_kernel(
   }
 }
 
+// First k chunk of slice s of the wide products: `units` chunks dealt out to
+// ns slices as evenly as they go (slices differ by one chunk at most).
+__host__ __device__ inline int slice_begin(int s, int units, int ns) {
+  return (int)((int64_t)s * units / ns);
+}
+
 // ---- FP64 block product for 32..64 columns: P streamed through LDS
 //
 // With 64 columns the FP64 product does 128 flops per E entry and is bound
@@ -295,24 +302,30 @@ __global__ __launch_bounds__(64 * MR_WAVES) void block_matvec_rows_kernel(
 // 16-row tile. Workgroup = 4 waves x F64_RW row tiles of 16 rows (F64_ROWS
 // rows) and one k slice; per chunk of F64_KC columns of E the workgroup
 // copies the matching 16 NG x F64_KC block of P into LDS once (double
-// buffered, one barrier per chunk) and every wave takes its B operands from
-// there while its own E rows stream from HBM (F64_U chunks in flight).
-// v_mfma_f64_16x16x4f64: lane (lr, lg) supplies A = E[row lr][k 4 lg + t]
-// and B = P[column lr][k 4 lg + t] for t = 0..3 of each 16-k step.
+// buffered, one barrier per chunk) and every wave takes its operands of P
+// from there while its own E rows stream from HBM (F64_U chunks in flight).
+// v_mfma_f64_16x16x4f64 with P as the first operand: lane (lr, lg) supplies
+// A = P[column lr][k 4 lg + t] and B = E[row lr][k 4 lg + t] for t = 0..3 of
+// each 16-k step and receives D[column 4 v + lg][row lr], so that a store of
+// register v covers 16 consecutive rows of four columns.
+// Every load of the chunk loop is unconditional (indices clamped to the last
+// chunk), so the loop body is one straight path: a load under a condition
+// made the compiler wait for all loads in flight at each join.
 constexpr int F64_RW = 2;
 constexpr int F64_ROWS = 4 * 16 * F64_RW;   // rows per workgroup
 constexpr int F64_KC = 32;                  // k per chunk
 constexpr int F64_PR = F64_KC + 4;          // LDS row length of the P chunk (doubles)
 constexpr int F64_U = 2;                    // E chunks in flight per wave
+template <int NG> constexpr int f64_waves() { return NG <= 2 ? 3 : 2; }   // per SIMD
 
-template <int NG>
-__global__ __launch_bounds__(256) void block_matvec_f64s_kernel(
+template <int NG, bool PV>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(f64_waves<NG>(), f64_waves<NG>()))) void
+block_matvec_f64s_kernel(
     const double *__restrict__ E, int64_t ld, const double *__restrict__ P,
-    double *__restrict__ part, int64_t kslice, int64_t split_stride,
+    double *__restrict__ part, int units, int64_t split_stride,
     double *__restrict__ pv_part, const int *__restrict__ gate, int *__restrict__ mark) {
   constexpr int COLS = 16 * NG;
   __shared__ __align__(16) double ps[2][COLS][F64_PR];
-  __shared__ double pvs[4][COLS];
   const bool first = blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0;
   if (gate != nullptr && *gate == 0) {
     if (mark != nullptr && first) *mark = 0;
@@ -321,35 +334,39 @@ __global__ __launch_bounds__(256) void block_matvec_f64s_kernel(
   if (mark != nullptr && first) *mark = 1;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int lr = lane & 15, lg = lane >> 4;
-  const int64_t tile = blockIdx.x, sl = blockIdx.y;
+  const int64_t tile = blockIdx.x;
   const int64_t row0 = tile * F64_ROWS + wave * 16 * F64_RW;
-  const int64_t kbeg = sl * kslice;
-  const int64_t kend = min(ld, kbeg + kslice);
-  const int nch = (int)((kend - kbeg) / F64_KC);
-  // P loader: thread -> (column tid / 4, 8 consecutive k); 64 columns x 32 k per chunk
-  const int pcol = tid >> 2, pk = (tid & 3) * 8;
-  const bool ploader = pcol < COLS;
-  const double *pbase = P + (int64_t)(ploader ? pcol : 0) * ld + kbeg + pk;
+  const int c0 = slice_begin(blockIdx.y, units, gridDim.y);
+  const int nch = slice_begin(blockIdx.y + 1, units, gridDim.y) - c0;   // >= 1
+  const int64_t kbeg = (int64_t)c0 * F64_KC;
+  // P loader: piece u of a thread is two consecutive k of one column
+  const double *pbase = P + (int64_t)(tid >> 4) * ld + kbeg + (tid & 15) * 2;
+  const int64_t pstep = 16 * ld;   // pieces u and u + 1 are 16 columns apart
   // E: row tile a, chunk u holds k = 16 s + 4 lg + t for s = 0, 1
-  // row tile a starts erow_stride * a after erow0
   const double *erow0 = E + (row0 + lr) * ld + kbeg + lg * 4;
   const int64_t erow_stride = 16 * ld;
-  double4 ring[F64_U][F64_RW][2];
+  d4 ring[F64_U][F64_RW][2];
 #pragma unroll
   for (int u = 0; u < F64_U; ++u)
-    if (u < nch)
 #pragma unroll
-      for (int a = 0; a < F64_RW; ++a)
+    for (int a = 0; a < F64_RW; ++a)
 #pragma unroll
-        for (int st = 0; st < 2; ++st)
-          ring[u][a][st] = *reinterpret_cast<const double4 *>(erow0 + a * erow_stride + u * F64_KC + st * 16);
-  double4 pn0 = make_double4(0, 0, 0, 0), pn1 = pn0;
-  if (nch > 0 && ploader) {
-    pn0 = *reinterpret_cast<const double4 *>(pbase);
-    pn1 = *reinterpret_cast<const double4 *>(pbase + 4);
-    *reinterpret_cast<double4 *>(&ps[0][pcol][pk]) = pn0;
-    *reinterpret_cast<double4 *>(&ps[0][pcol][pk + 4]) = pn1;
-  }
+      for (int st = 0; st < 2; ++st)
+        ring[u][a][st] = *reinterpret_cast<const d4 *>(
+            erow0 + a * erow_stride + min(u, nch - 1) * F64_KC + st * 16);
+  d2 pn[NG];
+  auto load_p = [&](int ch) {
+#pragma unroll
+    for (int u = 0; u < NG; ++u)
+      pn[u] = *reinterpret_cast<const d2 *>(pbase + u * pstep + (int64_t)ch * F64_KC);
+  };
+  auto store_p = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < NG; ++u)
+      *reinterpret_cast<d2 *>(&ps[buf][16 * u + (tid >> 4)][(tid & 15) * 2]) = pn[u];
+  };
+  load_p(0);
+  store_p(0);
   __syncthreads();
   d4 acc[F64_RW][NG];
 #pragma unroll
@@ -360,72 +377,80 @@ __global__ __launch_bounds__(256) void block_matvec_f64s_kernel(
   // ring stays in registers)
   auto chunk = [&](auto slot, int ch) {
     constexpr int U = decltype(slot)::value;
-    const int buf = ch & 1;
-    const bool more = ch + 1 < nch;
-    if (more && ploader) {
-      pn0 = *reinterpret_cast<const double4 *>(pbase + (int64_t)(ch + 1) * F64_KC);
-      pn1 = *reinterpret_cast<const double4 *>(pbase + (int64_t)(ch + 1) * F64_KC + 4);
-    }
+    constexpr int buf = U & 1;   // U == ch mod 2
+    load_p(min(ch + 1, nch - 1));
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int st = 0; st < 2; ++st)
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
-        const double4 b = *reinterpret_cast<const double4 *>(&ps[buf][g * 16 + lr][st * 16 + lg * 4]);
+        const d4 b = *reinterpret_cast<const d4 *>(&ps[buf][g * 16 + lr][st * 16 + lg * 4]);
 #pragma unroll
-        for (int a = 0; a < F64_RW; ++a) {
-          const double4 e = ring[U][a][st];
-          acc[a][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(e.x, b.x, acc[a][g], 0, 0, 0);
-          acc[a][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(e.y, b.y, acc[a][g], 0, 0, 0);
-          acc[a][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(e.z, b.z, acc[a][g], 0, 0, 0);
-          acc[a][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(e.w, b.w, acc[a][g], 0, 0, 0);
-        }
+        for (int a = 0; a < F64_RW; ++a)
+          acc[a][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(b.x, ring[U][a][st].x, acc[a][g], 0, 0, 0);
+#pragma unroll
+        for (int a = 0; a < F64_RW; ++a)
+          acc[a][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(b.y, ring[U][a][st].y, acc[a][g], 0, 0, 0);
+#pragma unroll
+        for (int a = 0; a < F64_RW; ++a)
+          acc[a][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(b.z, ring[U][a][st].z, acc[a][g], 0, 0, 0);
+#pragma unroll
+        for (int a = 0; a < F64_RW; ++a)
+          acc[a][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(b.w, ring[U][a][st].w, acc[a][g], 0, 0, 0);
       }
-    if (ch + F64_U < nch) {
-#pragma unroll
-      for (int a = 0; a < F64_RW; ++a)
-#pragma unroll
-        for (int st = 0; st < 2; ++st)
-          ring[U][a][st] =
-              *reinterpret_cast<const double4 *>(erow0 + a * erow_stride + (int64_t)(ch + F64_U) * F64_KC + st * 16);
-    }
-    if (more && ploader) {
-      *reinterpret_cast<double4 *>(&ps[buf ^ 1][pcol][pk]) = pn0;
-      *reinterpret_cast<double4 *>(&ps[buf ^ 1][pcol][pk + 4]) = pn1;
-    }
-    __syncthreads();
-  };
-  static_assert(F64_U == 2, "two ring slots");
-  for (int ch0 = 0; ch0 < nch; ch0 += F64_U) {
-    chunk(std::integral_constant<int, 0>(), ch0);
-    if (ch0 + 1 < nch) chunk(std::integral_constant<int, 1>(), ch0 + 1);
-  }
-  // lane (lr, lg) holds rows 4 v + lg of column lr of each tile
-  double *out = part + sl * split_stride;
-  double pv[NG];
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    pv[g] = 0.0;
-    const int64_t c = g * 16 + lr;
+    const int64_t kn = (int64_t)min(ch + F64_U, nch - 1) * F64_KC;
 #pragma unroll
     for (int a = 0; a < F64_RW; ++a)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t row = row0 + a * 16 + 4 * v + lg;
-        out[c * ld + row] = acc[a][g][v];
-        if (pv_part) pv[g] += P[c * ld + row] * acc[a][g][v];
-      }
+      for (int st = 0; st < 2; ++st)
+        ring[U][a][st] = *reinterpret_cast<const d4 *>(erow0 + a * erow_stride + kn + st * 16);
+    __builtin_amdgcn_sched_barrier(0);
+    store_p(buf ^ 1);
+    __syncthreads();
+  };
+  static_assert(F64_U == 2, "two ring slots");
+  int ch0 = 0;
+  for (; ch0 + 2 <= nch; ch0 += 2) {
+    chunk(std::integral_constant<int, 0>(), ch0);
+    chunk(std::integral_constant<int, 1>(), ch0 + 1);
   }
-  if (pv_part == nullptr) return;
+  if (ch0 < nch) chunk(std::integral_constant<int, 0>(), ch0);
+  // lane (lr, lg) holds row lr of columns 4 v + lg of each tile
+  const int64_t o0 = (int64_t)lg * ld + row0 + lr;
+  double *out = part + (int64_t)blockIdx.y * split_stride + o0;
 #pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    pv[g] += __shfl_xor(pv[g], 16, 64);
-    pv[g] += __shfl_xor(pv[g], 32, 64);
-    if (lg == 0) pvs[wave][g * 16 + lr] = pv[g];
+  for (int g = 0; g < NG; ++g)
+#pragma unroll
+    for (int a = 0; a < F64_RW; ++a)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) out[(int64_t)(g * 16 + 4 * v) * ld + a * 16] = acc[a][g][v];
+  if constexpr (PV) {
+    // p.v over the workgroup's rows: the wave's 16 F64_RW rows, then the
+    // four waves through LDS, in a fixed order
+    double pown[NG][F64_RW][4];
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+      for (int a = 0; a < F64_RW; ++a)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) pown[g][a][v] = P[o0 + (int64_t)(g * 16 + 4 * v) * ld + a * 16];
+    double *pvs = &ps[0][0][0];   // the chunks are done (barrier above)
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        double s = 0.0;
+#pragma unroll
+        for (int a = 0; a < F64_RW; ++a) s += pown[g][a][v] * acc[a][g][v];
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off, 16);
+        if (lr == 0) pvs[wave * COLS + g * 16 + 4 * v + lg] = s;
+      }
+    __syncthreads();
+    if (tid < COLS)
+      pv_part[((int64_t)blockIdx.y * gridDim.x + tile) * COLS + tid] =
+          ((pvs[tid] + pvs[COLS + tid]) + pvs[2 * COLS + tid]) + pvs[3 * COLS + tid];
   }
-  __syncthreads();
-  if (tid < COLS)
-    pv_part[(sl * gridDim.x + tile) * COLS + tid] =
-        ((pvs[0][tid] + pvs[1][tid]) + pvs[2][tid]) + pvs[3][tid];
 }
 
 // ---- block product on bf16 matrix cores (32..64 columns, FP32 or BF16 E)
@@ -452,6 +477,7 @@ constexpr int SP_PR = SP_KC + 8;             // LDS row length of a P part (bf16
 // E chunks in flight per wave: 2 up to 32 columns (three waves per SIMD fit
 // beside the FP64 sums: 12.3 ms against 14.4 with 4 at N = 131072), 4 for 64
 template <int NG> constexpr int sp_ring() { return NG <= 2 ? 2 : 4; }
+template <int NG> constexpr int sp_waves() { return NG <= 2 ? 3 : 2; }   // per SIMD
 
 __device__ inline uint32_t cvt_bf16x2(float a, float b) {
   const f2v v = {a, b};
@@ -460,11 +486,12 @@ __device__ inline uint32_t cvt_bf16x2(float a, float b) {
 __device__ inline float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ inline float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// 8 FP32 values -> three bf16 parts (4 packed words each), x = x0 + x1 + x2
-__device__ inline void split3(const float (&x)[8], uint32_t (&w0)[4], uint32_t (&w1)[4],
-                              uint32_t (&w2)[4]) {
+// K FP32 values -> three bf16 parts (K / 2 packed words each), x = x0 + x1 + x2
+template <int K>
+__device__ inline void split3(const float (&x)[K], uint32_t (&w0)[K / 2], uint32_t (&w1)[K / 2],
+                              uint32_t (&w2)[K / 2]) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < K / 2; ++j) {
     const float a = x[2 * j], b = x[2 * j + 1];
     w0[j] = cvt_bf16x2(a, b);
     const float ra = a - bf16_lo(w0[j]), rb = b - bf16_hi(w0[j]);
@@ -494,17 +521,22 @@ template <> struct Sp<float> {
     o.v[0] = a.x; o.v[1] = a.y; o.v[2] = a.z; o.v[3] = a.w;
     o.v[4] = b.x; o.v[5] = b.y; o.v[6] = b.z; o.v[7] = b.w;
   }
-  // acc += E P over one chunk for one 16 x 16 block, small products first
-  __device__ static inline f4 madd(const Raw &e, const bf16x8 (&pp)[3], f4 acc) {
+  // the three parts of the lane's eight entries
+  __device__ static inline void parts(const Raw &e, bf16x8 (&o)[3]) {
     uint32_t w0[4], w1[4], w2[4];
-    split3(e.v, w0, w1, w2);
-    const bf16x8 e0 = as_bf16x8(w0), e1 = as_bf16x8(w1), e2 = as_bf16x8(w2);
-    acc = mfma_bf16(e2, pp[0], acc);
-    acc = mfma_bf16(e1, pp[1], acc);
-    acc = mfma_bf16(e0, pp[2], acc);
-    acc = mfma_bf16(e1, pp[0], acc);
-    acc = mfma_bf16(e0, pp[1], acc);
-    return mfma_bf16(e0, pp[0], acc);
+    split3<8>(e.v, w0, w1, w2);
+    o[0] = as_bf16x8(w0);
+    o[1] = as_bf16x8(w1);
+    o[2] = as_bf16x8(w2);
+  }
+  // acc += E P over one chunk for one 16 x 16 block, small products first
+  __device__ static inline f4 madd(const bf16x8 (&e)[3], const bf16x8 (&pp)[3], f4 acc) {
+    acc = mfma_bf16(pp[0], e[2], acc);
+    acc = mfma_bf16(pp[1], e[1], acc);
+    acc = mfma_bf16(pp[2], e[0], acc);
+    acc = mfma_bf16(pp[0], e[1], acc);
+    acc = mfma_bf16(pp[1], e[0], acc);
+    return mfma_bf16(pp[0], e[0], acc);
   }
 };
 template <> struct Sp<uint16_t> {
@@ -513,28 +545,25 @@ template <> struct Sp<uint16_t> {
   __device__ static inline void load(const uint16_t *p, Raw &o) {
     o.w = *reinterpret_cast<const uint4 *>(p);
   }
-  __device__ static inline f4 madd(const Raw &e, const bf16x8 (&pp)[3], f4 acc) {
-    const bf16x8 a = as_bf16x8(e.w);
-    acc = mfma_bf16(a, pp[2], acc);
-    acc = mfma_bf16(a, pp[1], acc);
-    return mfma_bf16(a, pp[0], acc);
+  __device__ static inline void parts(const Raw &e, bf16x8 (&o)[1]) { o[0] = as_bf16x8(e.w); }
+  __device__ static inline f4 madd(const bf16x8 (&e)[1], const bf16x8 (&pp)[3], f4 acc) {
+    acc = mfma_bf16(pp[2], e[0], acc);
+    acc = mfma_bf16(pp[1], e[0], acc);
+    return mfma_bf16(pp[0], e[0], acc);
   }
 };
 
 template <typename T, int NG>
-__global__ __launch_bounds__(256) void block_matvec_split_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sp_waves<NG>(), sp_waves<NG>()))) void
+block_matvec_split_kernel(
     const T *__restrict__ E, int64_t ld, const float *__restrict__ P, float *__restrict__ part,
-    int64_t kslice, int64_t split_stride, double *__restrict__ pv_part,
+    int units, int64_t split_stride, double *__restrict__ pv_part,
     const int *__restrict__ gate, int *__restrict__ mark) {
   using SP = Sp<T>;
   constexpr int COLS = 16 * NG;
   constexpr int SP_U = sp_ring<NG>();
-  // one LDS buffer: the P parts during the k loop, the output tile after it
-  constexpr int PS_BYTES = 2 * 3 * COLS * SP_PR * 2;
-  constexpr int OUT_BYTES = COLS * (SP_ROWS + 1) * 4;
-  __shared__ __align__(16) unsigned char smem[PS_BYTES > OUT_BYTES ? PS_BYTES : OUT_BYTES];
-  auto ps = reinterpret_cast<uint16_t(*)[3][COLS][SP_PR]>(smem);
-  auto outs = reinterpret_cast<float(*)[SP_ROWS + 1]>(smem);
+  static_assert(SP_U % 2 == 0, "the LDS buffer of a chunk is its ring slot mod 2");
+  __shared__ __align__(16) uint16_t ps[2][3][COLS][SP_PR];
 
   const bool first = blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0;
   if (gate != nullptr && *gate == 0) {
@@ -545,33 +574,39 @@ __global__ __launch_bounds__(256) void block_matvec_split_kernel(
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int lr = lane & 15, lg = lane >> 4;
-  const int64_t tile = blockIdx.x, sl = blockIdx.y;
-  const int64_t row0 = tile * SP_ROWS;
-  const int64_t kbeg = sl * kslice;
-  const int64_t kend = min(ld, kbeg + kslice);
-  const int nch = (int)((kend - kbeg) / SP_KC);
+  const int64_t tile = blockIdx.x;
+  const int64_t row0 = tile * SP_ROWS + wave * 16 * SP_RW;
+  const int c0 = slice_begin(blockIdx.y, units, gridDim.y);
+  const int nch = slice_begin(blockIdx.y + 1, units, gridDim.y) - c0;   // >= 1
+  const int64_t kbeg = (int64_t)c0 * SP_KC;
 
-  // P loader: thread -> (column, 8 consecutive k)
-  const int pcol = tid >> 2, pk = (tid & 3) * 8;
-  const bool ploader = pcol < COLS;
-  const float *pbase = P + (int64_t)(ploader ? pcol : 0) * ld + pk;
-  auto load_p = [&](int64_t k0, float (&x)[8]) {
-    const float4 a = *reinterpret_cast<const float4 *>(pbase + k0);
-    const float4 b = *reinterpret_cast<const float4 *>(pbase + k0 + 4);
-    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
-    x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
-  };
-  auto store_p = [&](int buf, const float (&x)[8]) {
-    uint32_t w0[4], w1[4], w2[4];
-    split3(x, w0, w1, w2);
-    *reinterpret_cast<uint4 *>(&ps[buf][0][pcol][pk]) = make_uint4(w0[0], w0[1], w0[2], w0[3]);
-    *reinterpret_cast<uint4 *>(&ps[buf][1][pcol][pk]) = make_uint4(w1[0], w1[1], w1[2], w1[3]);
-    *reinterpret_cast<uint4 *>(&ps[buf][2][pcol][pk]) = make_uint4(w2[0], w2[1], w2[2], w2[3]);
-  };
-
-  const T *erow[SP_RW];
+  // P loader: thread -> (column, PK consecutive k); with 48 columns the last
+  // 64 threads repeat the last column (the same values to the same words)
+  constexpr int PK = NG == 2 ? 4 : 8, PTH = SP_KC / PK;
+  const int pcol = min(tid / PTH, COLS - 1), pk = (tid % PTH) * PK;
+  const float *pbase = P + (int64_t)pcol * ld + kbeg + pk;
+  float xn[PK];
+  auto load_p = [&](int ch) {
+    const float *q = pbase + (int64_t)ch * SP_KC;
 #pragma unroll
-  for (int a = 0; a < SP_RW; ++a) erow[a] = E + (row0 + wave * 16 * SP_RW + a * 16 + lr) * ld + kbeg + lg * 8;
+    for (int j = 0; j < PK; j += 4) {
+      const float4 a = *reinterpret_cast<const float4 *>(q + j);
+      xn[j] = a.x; xn[j + 1] = a.y; xn[j + 2] = a.z; xn[j + 3] = a.w;
+    }
+  };
+  auto store_p = [&](int buf) {
+    uint32_t w0[PK / 2], w1[PK / 2], w2[PK / 2];
+    split3<PK>(xn, w0, w1, w2);
+#pragma unroll
+    for (int j = 0; j < PK / 2; j += 2) {
+      *reinterpret_cast<uint2 *>(&ps[buf][0][pcol][pk + 2 * j]) = make_uint2(w0[j], w0[j + 1]);
+      *reinterpret_cast<uint2 *>(&ps[buf][1][pcol][pk + 2 * j]) = make_uint2(w1[j], w1[j + 1]);
+      *reinterpret_cast<uint2 *>(&ps[buf][2][pcol][pk + 2 * j]) = make_uint2(w2[j], w2[j + 1]);
+    }
+  };
+
+  const T *erow0 = E + (row0 + lr) * ld + kbeg + lg * 8;
+  const int64_t erow_stride = 16 * ld;
 
   // the matrix cores accumulate in FP32 over SP_U chunks, then the sums move
   // to FP64 registers: a running FP32 sum over a k slice of ~40000 would
@@ -589,43 +624,37 @@ __global__ __launch_bounds__(256) void block_matvec_split_kernel(
   typename SP::Raw ring[SP_U][SP_RW];
 #pragma unroll
   for (int u = 0; u < SP_U; ++u)
-    if (u < nch) {
 #pragma unroll
-      for (int a = 0; a < SP_RW; ++a) SP::load(erow[a] + u * SP_KC, ring[u][a]);
-    }
-  if (nch > 0 && ploader) {
-    float x[8];
-    load_p(kbeg, x);
-    store_p(0, x);
-  }
+    for (int a = 0; a < SP_RW; ++a)
+      SP::load(erow0 + a * erow_stride + min(u, nch - 1) * SP_KC, ring[u][a]);
+  load_p(0);
+  store_p(0);
   __syncthreads();
 
-  for (int ch0 = 0; ch0 < nch; ch0 += SP_U) {
+  auto chunk = [&](auto slot, int ch) {
+    constexpr int u = decltype(slot)::value, buf = u & 1;   // u == ch mod SP_U
+    load_p(min(ch + 1, nch - 1));
+    __builtin_amdgcn_sched_barrier(0);
+    bf16x8 ep[SP_RW][SP::EP];
 #pragma unroll
-    for (int u = 0; u < SP_U; ++u) {
-      const int ch = ch0 + u;
-      if (ch < nch) {
-        const int buf = u & 1;   // SP_U is even, so buf == ch & 1
-        float xn[8];
-        const bool more = ch + 1 < nch;
-        if (more && ploader) load_p(kbeg + (int64_t)(ch + 1) * SP_KC, xn);
+    for (int a = 0; a < SP_RW; ++a) SP::parts(ring[u][a], ep[a]);
 #pragma unroll
-        for (int g = 0; g < NG; ++g) {
-          bf16x8 pp[3];
+    for (int a = 0; a < SP_RW; ++a)
+      SP::load(erow0 + a * erow_stride + (int64_t)min(ch + SP_U, nch - 1) * SP_KC, ring[u][a]);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int q = 0; q < 3; ++q)
-            pp[q] = as_bf16x8(*reinterpret_cast<const uint4 *>(&ps[buf][q][g * 16 + lr][lg * 8]));
+    for (int g = 0; g < NG; ++g) {
+      bf16x8 pp[3];
 #pragma unroll
-          for (int a = 0; a < SP_RW; ++a) acc[a][g] = SP::madd(ring[u][a], pp, acc[a][g]);
-        }
-        if (ch + SP_U < nch) {
+      for (int q = 0; q < 3; ++q)
+        pp[q] = as_bf16x8(*reinterpret_cast<const uint4 *>(&ps[buf][q][g * 16 + lr][lg * 8]));
 #pragma unroll
-          for (int a = 0; a < SP_RW; ++a) SP::load(erow[a] + (int64_t)(ch + SP_U) * SP_KC, ring[u][a]);
-        }
-        if (more && ploader) store_p(buf ^ 1, xn);
-        __syncthreads();
-      }
+      for (int a = 0; a < SP_RW; ++a) acc[a][g] = SP::madd(ep[a], pp, acc[a][g]);
     }
+    store_p(buf ^ 1);
+    __syncthreads();
+  };
+  auto flush = [&]() {
 #pragma unroll
     for (int a = 0; a < SP_RW; ++a)
 #pragma unroll
@@ -634,35 +663,62 @@ __global__ __launch_bounds__(256) void block_matvec_split_kernel(
         for (int v = 0; v < 4; ++v) accd[a][g][v] += (double)acc[a][g][v];
         acc[a][g] = f4{0, 0, 0, 0};
       }
-  }
-
-  // this workgroup's partial product through LDS: coalesced rows per column
-#pragma unroll
-  for (int a = 0; a < SP_RW; ++a)
-#pragma unroll
-    for (int g = 0; g < NG; ++g)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        outs[g * 16 + lr][wave * 16 * SP_RW + a * 16 + 4 * lg + v] = (float)accd[a][g][v];
-  __syncthreads();
-  float *out = part + sl * split_stride;
-  for (int c = tid / SP_ROWS; c < COLS; c += 256 / SP_ROWS) {
-    const int r = tid % SP_ROWS;
-    out[(int64_t)c * ld + row0 + r] = outs[c][r];
-  }
-  if (pv_part) {
-    // p.v share of the workgroup's rows: 4 threads per column, fixed order
-    constexpr int RPT = SP_ROWS / 4;
-    if (tid < COLS * 4) {
-      const int c = tid >> 2, r0 = (tid & 3) * RPT;
-      const float *pc = P + (int64_t)c * ld + row0 + r0;
-      double s = 0.0;
-      for (int r = 0; r < RPT; ++r) s += (double)pc[r] * (double)outs[c][r0 + r];
-      s += __shfl_xor(s, 1, 64);
-      s += __shfl_xor(s, 2, 64);
-      if ((tid & 3) == 0) pv_part[(sl * gridDim.x + tile) * COLS + c] = s;
+  };
+  int ch0 = 0;
+  for (; ch0 + SP_U <= nch; ch0 += SP_U) {
+    chunk(std::integral_constant<int, 0>(), ch0);
+    chunk(std::integral_constant<int, 1>(), ch0 + 1);
+    if constexpr (SP_U == 4) {
+      chunk(std::integral_constant<int, 2>(), ch0 + 2);
+      chunk(std::integral_constant<int, 3>(), ch0 + 3);
     }
+    flush();
   }
+  if (ch0 < nch) chunk(std::integral_constant<int, 0>(), ch0);
+  if constexpr (SP_U == 4) {
+    if (ch0 + 1 < nch) chunk(std::integral_constant<int, 1>(), ch0 + 1);
+    if (ch0 + 2 < nch) chunk(std::integral_constant<int, 2>(), ch0 + 2);
+  }
+  flush();
+
+  // lane (lr, lg) holds row lr of columns 4 lg + v of each tile
+  const int64_t o0 = (int64_t)(4 * lg) * ld + row0 + lr;
+  float *out = part + (int64_t)blockIdx.y * split_stride + o0;
+#pragma unroll
+  for (int g = 0; g < NG; ++g)
+#pragma unroll
+    for (int a = 0; a < SP_RW; ++a)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        acc[a][g][v] = (float)accd[a][g][v];
+        out[(int64_t)(g * 16 + v) * ld + a * 16] = acc[a][g][v];
+      }
+  if (pv_part == nullptr) return;
+  // p.v over the workgroup's rows: the wave's 16 SP_RW rows, then the four
+  // waves through LDS, in a fixed order
+  float pown[NG][SP_RW][4];
+#pragma unroll
+  for (int g = 0; g < NG; ++g)
+#pragma unroll
+    for (int a = 0; a < SP_RW; ++a)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) pown[g][a][v] = P[o0 + (int64_t)(g * 16 + v) * ld + a * 16];
+  double *pvs = reinterpret_cast<double *>(&ps[0][0][0][0]);   // the chunks are done
+#pragma unroll
+  for (int g = 0; g < NG; ++g)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      double s = 0.0;
+#pragma unroll
+      for (int a = 0; a < SP_RW; ++a) s += (double)pown[g][a][v] * (double)acc[a][g][v];
+#pragma unroll
+      for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off, 16);
+      if (lr == 0) pvs[wave * COLS + g * 16 + 4 * lg + v] = s;
+    }
+  __syncthreads();
+  if (tid < COLS)
+    pv_part[((int64_t)blockIdx.y * gridDim.x + tile) * COLS + tid] =
+        ((pvs[tid] + pvs[COLS + tid]) + pvs[2 * COLS + tid]) + pvs[3 * COLS + tid];
 }
 
 // Sum over the block (RED_THREADS = 4 waves): butterfly within each wave,
@@ -1849,22 +1905,34 @@ template <typename T> constexpr int prec_of() {
 }
 
 // k slices of a wide block product (128-row workgroups, k in steps of 32):
-// about 3072 workgroups, several per resident slot (3 workgroups of 4 waves
-// per CU): with one per tile (1024 at N = 131072, 768 slots) the last round
-// left two thirds of the chip idle, 15.5 -> 11.9 ms for the FP32 product and
-// 31.8 -> 24.7 ms for the FP64 one at that size. The slices' partial sums
-// (slices x cols x ld of vsize bytes) stay under 1/16 of the bytes of E.
-int64_t wide_slices(int64_t ld, int64_t cols, int64_t esize, int64_t vsize, int64_t &kslice) {
-  constexpr int64_t kRowsPerWg = 128, kStep = 32, kTargetWgs = 3072;
+// the number whose workgroups fill whole rounds of `slots` best, against the
+// partial sums that each slice writes and the vector kernels read back
+// (2 cols vsize / (ld esize) of E's own bytes per slice). The FP64 product is
+// bound by the matrix cores, which one wave per SIMD keeps busy: slots = one
+// workgroup per CU; the split product streams E and needs two. Measured
+// (HIP events around the launch, slots 256 / 512 / 1024): FP64, 64 columns,
+// N = 4608: 54 / 57 / 69 us; N = 32768: 2.26 / 2.25 / 2.25 ms; FP32, 64
+// columns, N = 32768: 1157 / 825 / 847 us; BF16, 48 columns, N = 5275:
+// 26 / 22 / 28 us. (With at least 3072 workgroups but partials below 1/16 of
+// E, and waits for every load in flight, these took 114 us, 2.72 ms, 1057 us
+// and 50 us.)
+int64_t wide_slices(int64_t ld, int64_t cols, int64_t esize, int64_t vsize, int64_t slots) {
+  constexpr int64_t kRowsPerWg = 128, kStep = 32;
   static_assert(SP_ROWS == kRowsPerWg && F64_ROWS == kRowsPerWg, "128-row workgroups");
   static_assert(SP_KC == kStep && F64_KC == kStep, "k steps of 32");
   const int64_t tiles = ld / kRowsPerWg;
-  const int64_t units = ld / kStep;
-  int64_t want = std::max<int64_t>(1, (kTargetWgs + tiles - 1) / tiles);
-  want = std::min<int64_t>(want, std::max<int64_t>(1, (ld * esize) / (16 * cols * vsize)));
-  want = std::min<int64_t>(want, units);
-  kslice = (units + want - 1) / want * kStep;
-  return (ld + kslice - 1) / kslice;
+  const double per_slice = 2.0 * (double)(cols * vsize) / (double)(ld * esize);
+  int64_t best = 1;
+  double cost = 1e300;
+  for (int64_t sl = 1; sl <= std::min<int64_t>(ld / kStep, 64); ++sl) {
+    const int64_t wgs = tiles * sl, rounds = (wgs + slots - 1) / slots;
+    const double c = (double)(rounds * slots) / (double)wgs + per_slice * (double)sl;
+    if (c < cost) {
+      cost = c;
+      best = sl;
+    }
+  }
+  return best;
 }
 // the split-bf16 kernel serves FP32 and BF16 E with 32..64 columns
 template <typename T> constexpr bool uses_split(int64_t cols) {
@@ -1876,11 +1944,11 @@ template <typename T> constexpr bool uses_f64s(int64_t cols) {
   return sizeof(T) == 8 && cols >= 32;
 }
 
-int64_t split_slices(int64_t ld, int64_t cols, int64_t esize, int64_t &kslice) {
-  return wide_slices(ld, cols, esize, sizeof(float), kslice);
+int64_t split_slices(int64_t ld, int64_t cols, int64_t esize) {
+  return wide_slices(ld, cols, esize, sizeof(float), 512);
 }
-int64_t f64s_slices(int64_t ld, int64_t cols, int64_t &kslice) {
-  return wide_slices(ld, cols, sizeof(double), sizeof(double), kslice);
+int64_t f64s_slices(int64_t ld, int64_t cols) {
+  return wide_slices(ld, cols, sizeof(double), sizeof(double), 256);
 }
 
 // k slices of the row-split kernel (16 columns): about 432 workgroups, each
@@ -1898,16 +1966,16 @@ template <typename T> int64_t rows_slices(int64_t ld, int64_t &kslice) {
 // partials per column
 template <typename T> int64_t matvec_npv(int64_t ld, int64_t cols) {
   int64_t k = 0;
-  if (uses_split<T>(cols)) return split_slices(ld, cols, sizeof(T), k) * (ld / SP_ROWS);
-  if (uses_f64s<T>(cols)) return f64s_slices(ld, cols, k) * (ld / F64_ROWS);
+  if (uses_split<T>(cols)) return split_slices(ld, cols, sizeof(T)) * (ld / SP_ROWS);
+  if (uses_f64s<T>(cols)) return f64s_slices(ld, cols) * (ld / F64_ROWS);
   return rows_slices<T>(ld, k) * (ld / (16 * MR_WAVES));   // 16 columns
 }
 
 // slices of the kernel that serves c columns of an E of type T
 template <typename T> int64_t slices_for(int64_t ld, int64_t c) {
   int64_t k = 0;
-  if (uses_split<T>(c)) return split_slices(ld, c, sizeof(T), k);
-  if (uses_f64s<T>(c)) return f64s_slices(ld, c, k);
+  if (uses_split<T>(c)) return split_slices(ld, c, sizeof(T));
+  if (uses_f64s<T>(c)) return f64s_slices(ld, c);
   return rows_slices<T>(ld, k);   // 16 columns
 }
 
@@ -1937,8 +2005,8 @@ hipError_t launch_matvec_t(hipStream_t st, const T *E, int64_t ld, const typenam
   constexpr bool f64s = uses_f64s<T>(NG * 16);
   static_assert(split || f64s || NG == 1, "16 columns or an FP32/BF16/FP64 wide kernel");
   int64_t kslice = 0;
-  slices = split ? (int)split_slices(ld, NG * 16, sizeof(T), kslice)
-           : f64s ? (int)f64s_slices(ld, NG * 16, kslice)
+  slices = split ? (int)split_slices(ld, NG * 16, sizeof(T))
+           : f64s ? (int)f64s_slices(ld, NG * 16)
                   : (int)rows_slices<T>(ld, kslice);
   const int64_t tiles = split ? ld / SP_ROWS : f64s ? ld / F64_ROWS : ld / (16 * MR_WAVES);
   hipEvent_t ea = nullptr, eb = nullptr;
@@ -1953,14 +2021,16 @@ hipError_t launch_matvec_t(hipStream_t st, const T *E, int64_t ld, const typenam
     if (gate) mark = t_prof->take_mark(r);
   }
   if constexpr (f64s) {
-    hipExtLaunchKernelGGL((block_matvec_f64s_kernel<NG>), dim3((unsigned)tiles, (unsigned)slices),
-                          dim3(256), 0, st, ea, eb, 0, reinterpret_cast<const double *>(E), ld,
+    auto kern = pv_part ? block_matvec_f64s_kernel<NG, true> : block_matvec_f64s_kernel<NG, false>;
+    hipExtLaunchKernelGGL(kern, dim3((unsigned)tiles, (unsigned)slices), dim3(256), 0, st, ea, eb,
+                          0, reinterpret_cast<const double *>(E), ld,
                           reinterpret_cast<const double *>(P), reinterpret_cast<double *>(part),
-                          kslice, (int64_t)(NG * 16) * ld, pv_part, gate, mark);
+                          (int)(ld / F64_KC), (int64_t)(NG * 16) * ld, pv_part, gate, mark);
   } else if constexpr (split) {
     hipExtLaunchKernelGGL((block_matvec_split_kernel<T, NG>),
                           dim3((unsigned)tiles, (unsigned)slices), dim3(256), 0, st, ea, eb, 0, E,
-                          ld, P, part, kslice, (int64_t)(NG * 16) * ld, pv_part, gate, mark);
+                          ld, P, part, (int)(ld / SP_KC), (int64_t)(NG * 16) * ld, pv_part, gate,
+                          mark);
   } else {
     const size_t lds = sizeof(typename Mv<T>::VT) * 16 * (size_t)(kslice + mr_pad<T>());
     hipExtLaunchKernelGGL((block_matvec_rows_kernel<T>), dim3((unsigned)tiles, (unsigned)slices),
