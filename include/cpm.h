@@ -220,7 +220,7 @@ cpm_status cpm_solve(cpm_system *s, const double *b_dev, const double *qsol_dev,
  * beyond rcut). The solver uses the symmetric part (P + P^T) / 2. Built once
  * per system: the neighbourhoods on host threads, the local matrices and
  * their FP64 Cholesky factorisations on the device (rocSOLVER, batched);
- * kept on the device in a block-dense form (tiles of 64 atoms over the
+ * kept on the device in a block-dense form (tiles of 32 atoms over the
  * union of their columns) that cpm_solve applies with CPM_PRECOND_DC on the
  * FP64 matrix cores. The paper's choice for graphene electrodes is
  * g = 0.083 / A, rcut = 8 A. Errors: CPM_EINVAL (g or rcut not finite and

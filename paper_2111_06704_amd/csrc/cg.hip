@@ -1092,241 +1092,227 @@ __global__ __launch_bounds__(RED_THREADS) void colsum_kernel(const double *__res
   if (threadIdx.x == 0) rsum[c] = acc;
 }
 
-// Preconditioner apply for small systems (fewer than kPcBlockTiles tiles of
-// the block-dense form, whose few workgroups would leave most of the chip
-// idle): z = P r with P in row-major ELL form whose
-// row t is the row of atom order[t] (entry k at t * width + k), r in the
-// row-interleaved layout of rows_kernel. One wavefront per row (rows taken
-// in the spatial order) and column group (grid.y); lane = 8 e + h takes
-// entries k = e, e + 8, ... and the column pair (2h, 2h + 1), so every
-// gather of the wavefront reads eight whole 128-byte lines. Each wavefront
-// stages its row of P in LDS with all its loads in flight at once (the ELL
-// row does not depend on order[t], so that load overlaps them), and the
-// vector memory path then serves only the gathers. The eight entry lanes of
-// each pair are summed by shuffles in a fixed order. Active columns only
-// (scal == nullptr: all); set_p: p = z. bpart (may be null): per workgroup
-// and column (r.r, r.z), column-major (bpart[(c * gridDim.x + block) * 2 +
-// {0, 1}]) so that the kernels summing one column read it contiguously.
-constexpr int PC_ROWS = 4;                  // rows (waves) per workgroup
-constexpr int PC_THREADS = 64 * PC_ROWS;
-constexpr int PC_CHUNK = 256;               // entries per row staged at a time
-constexpr int PC_PER_LANE = PC_CHUNK / 64;
-
-template <typename VT>
-__global__ __launch_bounds__(PC_THREADS) void precond_kernel(
-    const double *__restrict__ rt, double *__restrict__ z, VT *__restrict__ p,
-    const int32_t *__restrict__ pidx, const double *__restrict__ pval, int width,
-    const int32_t *__restrict__ order, int64_t ld, int64_t n, int cols,
-    const double *__restrict__ scal, int slot, double *__restrict__ bpart, int set_p,
-    double gap, const double *__restrict__ rsum, const int *__restrict__ gate,
-    double *__restrict__ zt) {
-  __shared__ double red[PC_ROWS][kColGroup][2];
-  __shared__ double sval[PC_ROWS][PC_CHUNK];
-  __shared__ int32_t sidx[PC_ROWS][PC_CHUNK];
-  if (gate != nullptr && *gate == 0) return;
-  const int g = blockIdx.y;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int e = lane >> 3, h = lane & 7;
-  const int64_t t = (int64_t)blockIdx.x * PC_ROWS + wave;
-  const bool live = t < n;
-  const int64_t i = live ? (int64_t)order[t] : -1;
-  const int32_t *ix = pidx + (live ? t : 0) * width;
-  const double *vx = pval + (live ? t : 0) * width;
-  const double *rg = rt + (int64_t)g * ld * kColGroup;
-  const int c0 = g * kColGroup + 2 * h;
-  const bool act0 = scal == nullptr || (scal[S_ACT * cols + c0] != 0.0 &&
-                                         scal[(S_HOLD0 + slot) * cols + c0] == 0.0);
-  const bool act1 = scal == nullptr || (scal[S_ACT * cols + c0 + 1] != 0.0 &&
-                                         scal[(S_HOLD0 + slot) * cols + c0 + 1] == 0.0);
-  double2 ri = make_double2(0.0, 0.0);
-  double a0 = 0.0, a1 = 0.0;
-  for (int k0 = 0; k0 < width; k0 += PC_CHUNK) {
-    const int cw = min(PC_CHUNK, width - k0);
-    int32_t li[PC_PER_LANE];
-    double lv[PC_PER_LANE];
-#pragma unroll
-    for (int u = 0; u < PC_PER_LANE; ++u) {
-      const int k = lane + 64 * u;
-      li[u] = 0;
-      lv[u] = 0.0;
-      if (live && k < cw) {
-        li[u] = ix[k0 + k];
-        lv[u] = vx[k0 + k];
-      }
-    }
-    if (k0 == 0 && i >= 0) ri = *reinterpret_cast<const double2 *>(rg + i * kColGroup + 2 * h);
-    if (k0 > 0) __syncthreads();
-#pragma unroll
-    for (int u = 0; u < PC_PER_LANE; ++u) {
-      const int k = lane + 64 * u;
-      if (k < cw) {
-        sidx[wave][k] = li[u];
-        sval[wave][k] = lv[u];
-      }
-    }
-    __syncthreads();
-    if (i >= 0) {
-#pragma unroll 4
-      for (int k = e; k < cw; k += 8) {
-        const int64_t j = sidx[wave][k];
-        const double v = sval[wave][k];
-        const double2 x = *reinterpret_cast<const double2 *>(rg + j * kColGroup + 2 * h);
-        a0 += v * x.x;
-        a1 += v * x.y;
-      }
-    }
-  }
-#pragma unroll
-  for (int off = 8; off < 64; off <<= 1) {
-    a0 += __shfl_xor(a0, off, 64);
-    a1 += __shfl_xor(a1, off, 64);
-  }
-  // lanes 0..7 hold columns (2h, 2h + 1)
-  if (zt != nullptr) {
-    // raw output (the coarse correction's inner apply): every column, in the
-    // row-interleaved layout, no dots
-    if (lane < 8 && i >= 0) {
-      const double add0 = rsum != nullptr ? gap * rsum[c0] : 0.0;
-      const double add1 = rsum != nullptr ? gap * rsum[c0 + 1] : 0.0;
-      double *o = zt + ((int64_t)g * ld + i) * kColGroup + 2 * h;
-      o[0] = a0 + add0;
-      o[1] = a1 + add1;
-    }
-    return;
-  }
-  if (lane < 8) {
-    double d[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
-    if (i >= 0) {
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        // the Eq. 37 fill: P's zeros hold gap, its pattern P - gap
-        const double zi = (u ? a1 : a0) + (rsum != nullptr ? gap * rsum[c0 + u] : 0.0);
-        const double rv = u ? ri.y : ri.x;
-        if (u ? act1 : act0) {
-          const int64_t idx = (int64_t)(c0 + u) * ld + i;
-          z[idx] = zi;
-          if (set_p || (scal != nullptr && scal[S_RST * cols + c0 + u] != 0.0)) p[idx] = (VT)zi;
-          d[u][0] = rv * rv;
-          d[u][1] = rv * zi;
-        }
-      }
-    }
-    if (bpart != nullptr) {
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        red[wave][2 * h + u][0] = d[u][0];
-        red[wave][2 * h + u][1] = d[u][1];
-      }
-    }
-  }
-  if (bpart == nullptr) return;
-  __syncthreads();
-  if (threadIdx.x < 2 * kColGroup) {
-    const int c = threadIdx.x >> 1, s2 = threadIdx.x & 1;
-    double v = 0.0;
-#pragma unroll
-    for (int w = 0; w < PC_ROWS; ++w) v += red[w][c][s2];
-    bpart[((int64_t)(g * kColGroup + c) * gridDim.x + blockIdx.x) * 2 + s2] = v;
-  }
-}
-
 // Preconditioner apply (Sec. III.B.2): z = P r with P in its block-dense
 // form: tile t (one workgroup) holds the kPcTile rows of atoms
-// order[t kPcTile ..] over U_t, the union of their columns, so z of the tile
-// is the product [64 rows x |U_t|] . [|U_t| x cols] on the FP64 matrix cores
+// order[kPcTile t ..] over U_t, the union of their columns, so z of the tile
+// is the product [rows x |U_t|] . [|U_t| x cols] on the FP64 matrix cores
 // and every row of r is read once per tile (where a row-by-row sparse
-// product reads it once per entry). Wave w takes rows 16 w .. 16 w + 15 and
-// every column group; per step of 4 entries of U_t lane (lr, lg) gives
-// A = P(row lr, U_t[k + lg]) and, per group g, B = r(U_t[k + lg], column
-// 16 g + lr) from the row-interleaved copy rt (16 columns of an atom in one
-// 128-byte line). Active columns only (scal == nullptr: all); set_p: p = z;
-// with the Eq. 37 fill z += gap (1^T r). bpart (may be null): per tile and
-// column (r.r, r.z), column-major (bpart[(c * gridDim.x + tile) * 2 +
-// {0, 1}]), summed in a fixed order.
-template <typename VT, int NG>
-__global__ __launch_bounds__(256) void precond_block_kernel(
+// product reads it once per entry). The W waves split U_t into contiguous
+// ranges and each takes every row and column group, so an entry of P and a
+// row of r are read by one wave only; their sums are added in LDS in wave
+// order. Per step of 4 entries of U_t lane (lr, lg) gives
+// A = P(row, U_t[k + lg]) for the rows RT lr .. RT lr + RT - 1 (one load;
+// row block q is the rows with r mod RT = q) and, per group g,
+// B = r(U_t[k + lg], column 16 g + lr) from the row-interleaved copy rt (16
+// columns of an atom in one 128-byte line). The loads run one batch of UB
+// steps ahead of the products and the indices of U_t two batches, without
+// conditions (clamped to the tile's last step; entries of P past a wave's
+// range enter as 0); the gate is tested after the first loads are under way.
+//
+// Bound by the reads of P and r from memory and, at 64 columns, about equally
+// by the matrix cores; at small N by the chain of dependent loads (offsets,
+// indices, r), which is why a few tiles per CU get more waves. 32 rows per
+// tile: 16 read more of r, 64 leave CUs idle at N = 4608 and need too many
+// registers at 64 columns. Measured per apply, N = 4608, r_cut 12 A, 16
+// columns: 10 us (11 with 16-row tiles, 17 with 64; one wave per row of an
+// ELL form took 16); N = 5275, r_cut 10 A, 48 columns: 24 us (ELL 37);
+// N = 32768, r_cut 14 A, 64 columns: 162 us (535 when every step waited for
+// its three dependent loads and each wave read r for 16 of 64 rows).
+// Waves (small / large systems): 16 / 8 at 16 and 32 columns (10.1 against
+// 10.8 and 81.4 against 83.7 us), 8 / 4 at 48 and 64 (28.4 against 31.0 and
+// 162 against 176 us); small: fewer than two tiles per CU.
+//
+// Active columns only (scal == nullptr: all); set_p: p = z; with the Eq. 37
+// fill z += gap (1^T r). bpart (may be null): per tile and column (r.r, r.z),
+// column-major (bpart[(c * gridDim.x + tile) * 2 + {0, 1}]), summed in a
+// fixed order. zt (may be null): raw output of every column into this
+// row-interleaved array instead (the coarse correction's inner apply).
+constexpr int PC_RT = kPcTile / 16;
+constexpr int64_t kPcFewTiles = 512;
+template <int NG> constexpr int pc_waves(bool few) { return (NG <= 2 ? 8 : 4) * (few ? 2 : 1); }
+template <int NG> constexpr int pc_batch() { return NG <= 2 ? 2 : NG == 3 ? 6 : 4; }
+template <int NG> constexpr int pc_occ() { return NG <= 2 ? 4 : 2; }   // waves per SIMD
+
+template <typename VT, int NG, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(pc_occ<NG>(), pc_occ<NG>()))) void
+precond_block_kernel(
     const double *__restrict__ rt, double *__restrict__ z, VT *__restrict__ p,
     const int64_t *__restrict__ uoff, const int32_t *__restrict__ uidx,
     const double *__restrict__ blk, const int32_t *__restrict__ order, int64_t ld, int64_t n,
     int cols, const double *__restrict__ scal, int slot, double *__restrict__ bpart, int set_p,
     double gap, const double *__restrict__ rsum, const int *__restrict__ gate,
     double *__restrict__ zt) {
-  __shared__ double red[4][16 * NG][2];
-  if (gate != nullptr && *gate == 0) return;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  constexpr int RT = PC_RT, UB = pc_batch<NG>(), ROWS = kPcTile;
+  constexpr int ITEMS = RT * 4;                       // (row block, register) pairs of a group
+  constexpr int PER = (ITEMS + W - 1) / W;            // pairs of a wave in the epilogue
+  typedef double av __attribute__((ext_vector_type(RT)));
+  __shared__ double part[W][ITEMS][64];
+  __shared__ double red[W][16][2];
+  const int go = gate != nullptr ? *gate : 1;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int lr = lane & 15, lg = lane >> 4;
   const int64_t tile = blockIdx.x;
-  const int64_t k0 = uoff[tile], K = uoff[tile + 1] - k0;
-  const int32_t *U = uidx + k0;
-  const double *A = blk + k0 * kPcTile + wave * 16 + lr;
-  d4 acc[NG];
+  const int64_t k0 = uoff[tile];
+  const int steps = (int)(uoff[tile + 1] - k0) >> 2;   // >= 1
+  const int s0 = wave * steps / W, ns = (wave + 1) * steps / W - s0;
+  const int32_t *U = uidx + k0 + lg;
+  const double *A = blk + (k0 + lg) * ROWS + lr * RT;
+  const double *B = rt + lr;
+  // the wave's output rows (atom, -1 past the end)
+  int64_t row[PER];
 #pragma unroll
-  for (int g = 0; g < NG; ++g) acc[g] = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-  for (int64_t k = lg; k < K; k += 4) {
-    const double a = A[k * kPcTile];
-    const int64_t j = U[k];
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      const double b = rt[((int64_t)g * ld + j) * kColGroup + lr];
-      acc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[g], 0, 0, 0);
-    }
+  for (int q = 0; q < PER; ++q) {
+    const int it = wave * PER + q, v = it & 3, rb = it >> 2;
+    const int64_t t = tile * ROWS + RT * (4 * v + lg) + rb;
+    row[q] = it < ITEMS && t < n ? (int64_t)order[t] : -1;
   }
-  // D[i][j] (row i of the wave's 16, column j of the group) in lane
-  // j + 16 (i % 4), register i / 4
-  if (zt != nullptr) {
-    // raw output (the coarse correction's inner apply): every column, in the
-    // row-interleaved layout, no dots
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      const double add = rsum != nullptr ? gap * rsum[g * 16 + lr] : 0.0;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t t = tile * kPcTile + wave * 16 + 4 * v + lg;
-        if (t < n) zt[((int64_t)g * ld + order[t]) * kColGroup + lr] = acc[g][v] + add;
-      }
-    }
-    return;
-  }
+  // per column of the lane: active, p = z wanted, the fill's term (loaded
+  // here, together, so that the epilogue waits for none of them)
+  bool act[NG], rst[NG];
+  double add[NG];
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
-    const int c = g * 16 + lr;
-    const bool act = scal == nullptr || (scal[S_ACT * cols + c] != 0.0 &&
-                                         scal[(S_HOLD0 + slot) * cols + c] == 0.0);
-    const bool rst = set_p || (scal != nullptr && scal[S_RST * cols + c] != 0.0);
-    const double add = rsum != nullptr ? gap * rsum[c] : 0.0;
-    double rr = 0.0, rz = 0.0;
+    act[g] = true;
+    rst[g] = set_p != 0;
+    add[g] = 0.0;
+  }
+  if (scal != nullptr) {
+    double sa[NG], sh[NG], sr[NG];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int64_t t = tile * kPcTile + wave * 16 + 4 * v + lg;
-      if (t < n && act) {
-        const int64_t i = order[t];
-        const double zi = acc[g][v] + add;
-        const int64_t idx = (int64_t)c * ld + i;
-        z[idx] = zi;
-        if (rst) p[idx] = (VT)zi;
-        const double ri = rt[((int64_t)g * ld + i) * kColGroup + lr];
-        rr += ri * ri;
-        rz += ri * zi;
+    for (int g = 0; g < NG; ++g) {
+      sa[g] = scal[S_ACT * cols + g * kColGroup + lr];
+      sh[g] = scal[(S_HOLD0 + slot) * cols + g * kColGroup + lr];
+      sr[g] = scal[S_RST * cols + g * kColGroup + lr];
+    }
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      act[g] = (sa[g] != 0.0) & (sh[g] == 0.0);
+      rst[g] = rst[g] | (sr[g] != 0.0);
+    }
+  }
+  if (rsum != nullptr)
+#pragma unroll
+    for (int g = 0; g < NG; ++g) add[g] = gap * rsum[g * kColGroup + lr];
+  d4 acc[RT][NG];
+#pragma unroll
+  for (int q = 0; q < RT; ++q)
+#pragma unroll
+    for (int g = 0; g < NG; ++g) acc[q][g] = d4{0.0, 0.0, 0.0, 0.0};
+  int32_t j[2][UB];
+  av pa[2][UB];
+  double pb[2][UB][NG];
+  auto load_j = [&](auto buf, int b) {
+#pragma unroll
+    for (int u = 0; u < UB; ++u) j[buf.value][u] = U[4 * min(s0 + b * UB + u, steps - 1)];
+  };
+  auto load_a = [&](auto buf, int b) {
+#pragma unroll
+    for (int u = 0; u < UB; ++u)
+      pa[buf.value][u] = *reinterpret_cast<const av *>(
+          A + (int64_t)min(s0 + b * UB + u, steps - 1) * (4 * ROWS));
+  };
+  auto load_b = [&](auto buf) {
+#pragma unroll
+    for (int u = 0; u < UB; ++u)
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+        pb[buf.value][u][g] = B[((int64_t)g * ld + j[buf.value][u]) * kColGroup];
+  };
+  // batch b from buffer `buf`: the next batch's loads, the indices after
+  // them, then the products
+  auto batch = [&](auto buf, int b) {
+    constexpr int X = decltype(buf)::value;
+    const std::integral_constant<int, X ^ 1> other;
+    load_b(other);
+    load_a(other, b + 1);
+    load_j(buf, b + 2);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      const bool in = b * UB + u < ns;
+#pragma unroll
+      for (int q = 0; q < RT; ++q) {
+        const double a = in ? pa[X][u][q] : 0.0;
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+          acc[q][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, pb[X][u][g], acc[q][g], 0, 0, 0);
       }
     }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const std::integral_constant<int, 0> even;
+  const std::integral_constant<int, 1> odd;
+  load_j(even, 0);
+  load_j(odd, 1);
+  load_a(even, 0);
+  if (go == 0) return;
+  load_b(even);
+  const int nb = (ns + UB - 1) / UB;
+  for (int b = 0; b < nb; b += 2) {
+    batch(even, b);
+    if (b + 1 == nb) break;
+    batch(odd, b + 1);
+  }
+  // the waves' sums in wave order; wave w finishes the pairs w PER ..;
+  // D[i][j] (row i of a block, column j of a group) is in lane j + 16 (i % 4),
+  // register i / 4
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    const int c = g * kColGroup + lr;
+    double ri[PER];
+    if (zt == nullptr)
+#pragma unroll
+      for (int q = 0; q < PER; ++q)
+        ri[q] = rt[((int64_t)g * ld + (row[q] < 0 ? 0 : row[q])) * kColGroup + lr];
+#pragma unroll
+    for (int q = 0; q < RT; ++q)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) part[wave][q * 4 + v][lane] = acc[q][g][v];
+    __syncthreads();
+    double zi[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int it = min(wave * PER + q, ITEMS - 1);
+      double t = part[0][it][lane];
+#pragma unroll
+      for (int w = 1; w < W; ++w) t += part[w][it][lane];
+      zi[q] = t + add[g];
+    }
+    if (zt != nullptr) {
+#pragma unroll
+      for (int q = 0; q < PER; ++q)
+        if (row[q] >= 0) zt[((int64_t)g * ld + row[q]) * kColGroup + lr] = zi[q];
+      __syncthreads();
+      continue;
+    }
+    double rr = 0.0, rz = 0.0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+      if (row[q] >= 0 && act[g]) {
+        const int64_t idx = (int64_t)c * ld + row[q];
+        z[idx] = zi[q];
+        if (rst[g]) p[idx] = (VT)zi[q];
+        rr += ri[q] * ri[q];
+        rz += ri[q] * zi[q];
+      }
     if (bpart != nullptr) {
       rr += __shfl_xor(rr, 16, 64);
       rz += __shfl_xor(rz, 16, 64);
       rr += __shfl_xor(rr, 32, 64);
       rz += __shfl_xor(rz, 32, 64);
       if (lg == 0) {
-        red[wave][c][0] = rr;
-        red[wave][c][1] = rz;
+        red[wave][lr][0] = rr;
+        red[wave][lr][1] = rz;
       }
     }
-  }
-  if (bpart == nullptr) return;
-  __syncthreads();
-  if (threadIdx.x < 2 * 16 * NG) {
-    const int c = threadIdx.x >> 1, s2 = threadIdx.x & 1;
-    const double v = ((red[0][c][s2] + red[1][c][s2]) + red[2][c][s2]) + red[3][c][s2];
-    bpart[((int64_t)c * gridDim.x + tile) * 2 + s2] = v;
+    __syncthreads();
+    if (bpart != nullptr && threadIdx.x < 2 * kColGroup) {
+      const int cc = threadIdx.x >> 1, s2 = threadIdx.x & 1;
+      double t = red[0][cc][s2];
+#pragma unroll
+      for (int w = 1; w < W; ++w) t += red[w][cc][s2];
+      bpart[((int64_t)(g * kColGroup + cc) * gridDim.x + tile) * 2 + s2] = t;
+    }
   }
 }
 
@@ -2099,7 +2085,7 @@ cpm_status ensure_workspace(cpm_system *s, int64_t cols) {
             alloc((void **)&w.sum_err, sizeof(double) * MAX_COLS) &&
             alloc((void **)&w.rsum, sizeof(double) * MAX_COLS) &&
             alloc((void **)&w.bpart,
-                  sizeof(double) * 2 * (size_t)((s->n + PC_ROWS - 1) / PC_ROWS) * cols) &&
+                  sizeof(double) * 2 * (size_t)((s->n + kPcTile - 1) / kPcTile) * cols) &&
             alloc((void **)&w.flags, sizeof(int) * F_NWORDS);
   if (ok && (hipHostMalloc((void **)&w.hstat, sizeof(int) * F_NWORDS * kStatusSlots,
                            hipHostMallocDefault) != hipSuccess ||
@@ -2159,25 +2145,18 @@ void launch_local(hipStream_t st, const cpm_system *s, const Precond &pc, const 
                   double *z, VT *p, int64_t cols, const double *scal, int slot, double *bpart,
                   bool set_p, const double *rsum, const int *gate, double *zt) {
   const int64_t ld = s->ld, n = s->n;
-  if (pc.blk == nullptr) {
-    hipLaunchKernelGGL(precond_kernel<VT>,
-                       dim3((unsigned)((n + PC_ROWS - 1) / PC_ROWS), (unsigned)(cols / kColGroup)),
-                       dim3(PC_THREADS), 0, st, rt, z, p, (const int32_t *)pc.idx,
-                       (const double *)pc.val, pc.width, s->atom_order, ld, n, (int)cols, scal,
-                       slot, bpart, set_p ? 1 : 0, pc.gap, rsum, gate, zt);
-    return;
-  }
   const dim3 grid((unsigned)pc.ntiles);
-#define CPM_PB(NGV)                                                                            \
-  hipLaunchKernelGGL((precond_block_kernel<VT, NGV>), grid, dim3(256), 0, st, rt, z, p,       \
-                     (const int64_t *)pc.uoff, (const int32_t *)pc.uidx, (const double *)pc.blk, \
-                     s->atom_order, ld, n, (int)cols, scal, slot, bpart, set_p ? 1 : 0, pc.gap,  \
-                     rsum, gate, zt)
+#define CPM_PB(NGV, FEW)                                                                       \
+  hipLaunchKernelGGL((precond_block_kernel<VT, NGV, pc_waves<NGV>(FEW)>), grid,               \
+                     dim3(64 * pc_waves<NGV>(FEW)), 0, st, rt, z, p, (const int64_t *)pc.uoff, \
+                     (const int32_t *)pc.uidx, (const double *)pc.blk, s->atom_order, ld, n,   \
+                     (int)cols, scal, slot, bpart, set_p ? 1 : 0, pc.gap, rsum, gate, zt)
+  const bool few = pc.ntiles < kPcFewTiles;
   switch (cols / kColGroup) {
-    case 1: CPM_PB(1); break;
-    case 2: CPM_PB(2); break;
-    case 3: CPM_PB(3); break;
-    default: CPM_PB(4); break;
+    case 1: if (few) CPM_PB(1, true); else CPM_PB(1, false); break;
+    case 2: if (few) CPM_PB(2, true); else CPM_PB(2, false); break;
+    case 3: if (few) CPM_PB(3, true); else CPM_PB(3, false); break;
+    default: if (few) CPM_PB(4, true); else CPM_PB(4, false); break;
   }
 #undef CPM_PB
 }
@@ -2317,7 +2296,7 @@ template <typename T> struct Solver {
   // workgroup (DC)
   int npc() const {
     if (s->cz.ready) return (int)((n + 63) / 64);   // coarse_finish_kernel's workgroups
-    return pc->blk ? (int)pc->ntiles : (int)((n + PC_ROWS - 1) / PC_ROWS);
+    return (int)pc->ntiles;
   }
   int nred() const { return pc ? npc() : nblk; }
   const double *dots() const { return pc ? s->ws.bpart : partial; }
