@@ -157,14 +157,24 @@ template <typename VT, int VEC> __device__ inline void load_vec(const VT *p, VT 
 }
 
 // Block product for 16 columns with the rows split over the waves: grid
-// (row blocks of MR_WAVES x 16 rows, k slices). The workgroup first copies
+// (row blocks of W x 16 rows, k slices). The workgroup first copies
 // its slice of P (16 columns x kslice) into LDS; each wave then streams its
-// own 16 rows of E over the slice (U load stages in flight) and takes the B
-// operands from LDS, so P is read from L2 once per workgroup and no
+// own 16 rows of E over the slice (MR_U load stages in flight) and takes its
+// operands of P from LDS, so P is read from L2 once per workgroup and no
 // reduction across waves is needed:
 //   part[s][c][row] = sum_{k in slice s} E[row][k] P[c][k]
-//   pv_part[s][workgroup][c] = sum over the workgroup's rows of P[c][row] part[s][c][row]
-constexpr int MR_WAVES = 8;
+//   pv_part[c][s][workgroup] = sum over the workgroup's rows of P[c][row] part[s][c][row]
+// Bound by the reads of E at N = 4608 (FP64 31 us, FP32 17.6 us: 6 and 5.6
+// TB/s), by latency below. P is the first matrix-core operand, so lane (lr,
+// lg) receives row lr of four columns and stores of 16 consecutive rows.
+// Two stages in flight do as well as four or better at every size (the loads
+// past a short slice's end cost as much as real ones); 4 waves per
+// workgroup up to ld = 2048 (N = 288 FP64: 3.9 us against 6.3 with 8 waves
+// and four stages, N = 1152: 5.1 against 8.2), 8 above (N = 4608: 31.5
+// against 38.9 with 4).
+constexpr int MR_U = 2;
+constexpr int MR_FLUSH = 128;
+inline int mr_waves(int64_t ld) { return ld <= 2048 ? 4 : 8; }
 extern __shared__ double mv_lds[];
 
 template <typename T> constexpr int mr_pad() { return 4; }   // keeps 32-byte alignment of LDS rows
@@ -178,13 +188,14 @@ template <typename T> constexpr int64_t mr_kmax() {
 // reliably)
 template <typename T> constexpr bool mr_lds_fits() {
   return sizeof(typename Mv<T>::VT) * 16 * (mr_kmax<T>() + mr_pad<T>()) +
-             sizeof(double) * MR_WAVES * 16 <= 65536 + 4096;
+             sizeof(double) * 8 * 16 <= 65536 + 4096;
 }
 static_assert(mr_lds_fits<double>() && mr_lds_fits<float>() && mr_lds_fits<uint16_t>(),
               "LDS of the 16-column product");
 
-template <typename T>
-__global__ __launch_bounds__(64 * MR_WAVES) void block_matvec_rows_kernel(
+template <typename T, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 4))) void
+block_matvec_rows_kernel(
     const T *__restrict__ E, int64_t ld, const typename Mv<T>::VT *__restrict__ P,
     typename Mv<T>::VT *__restrict__ part, int64_t kslice, int64_t split_stride,
     double *__restrict__ pv_part, const int *__restrict__ gate, int *__restrict__ mark) {
@@ -193,99 +204,103 @@ __global__ __launch_bounds__(64 * MR_WAVES) void block_matvec_rows_kernel(
   using Acc = typename M::Acc;
   constexpr int VEC = M::VEC;
   constexpr int KB = 4 * VEC;
-  constexpr int U = 4;
-  const bool first = blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0;
-  if (gate != nullptr && *gate == 0) {
-    if (mark != nullptr && first) *mark = 0;
-    return;
-  }
-  if (mark != nullptr && first) *mark = 1;
+  constexpr int U = MR_U;
+  typedef VT pv_t __attribute__((ext_vector_type(16 / sizeof(VT))));   // 16 bytes of P
+  const int go = gate != nullptr ? *gate : 1;
   VT *ps = reinterpret_cast<VT *>(mv_lds);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int lr = lane & 15, lg = lane >> 4;
-  const int64_t wtile = (int64_t)blockIdx.x * MR_WAVES + wave;
-  const int64_t r0 = wtile * 16;
+  const int64_t r0 = ((int64_t)blockIdx.x * W + wave) * 16;
   const int64_t sl = blockIdx.y;
   const int64_t k0 = sl * kslice;
-  const int64_t kn = min(kslice, ld - k0);   // a multiple of KB
-  const int64_t pstride = kslice + mr_pad<T>();
-  const int64_t nsteps = kn / KB;
+  const int kn = (int)min(kslice, ld - k0);   // a multiple of KB, > 0
+  const int pstride = (int)kslice + mr_pad<T>();
+  const int nsteps = kn / KB;
   const T *erow = E + (r0 + lr) * ld + k0 + lg * VEC;
-  // E ring: slot u holds step st0 + u. The loads of the prologue and of the
-  // main loop are unconditional (the prologue's clamped to the last step) so
-  // that the loop body is one straight path: the compiler then waits only
-  // for the oldest slot (vmcnt 2 (U - 1)) instead of draining every load in
-  // flight at the top of each iteration.
+  // E ring: slot u holds step st + u. Every load is unconditional (clamped to
+  // the last step), so that the loop body is one straight path and waits
+  // only for the oldest slot; the gate is tested after the first loads.
   typename M::Raw ea[U];
 #pragma unroll
-  for (int u = 0; u < U; ++u) M::load(erow + min<int64_t>(u, nsteps - 1) * KB, ea[u]);
-  // P of the wave's own rows for the p.v partial, loaded now so that the
-  // loads are complete when the epilogue needs them
-  const VT *pc = P + (int64_t)lr * ld + r0;
+  for (int u = 0; u < U; ++u) M::load(erow + min(u, nsteps - 1) * KB, ea[u]);
+  // P of the wave's own rows for the p.v partial
   VT pown[4];
   if (pv_part != nullptr)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) pown[v] = pc[M::out_row(lg, v)];
-  // P slice into LDS (16-byte pieces; kn / PV < 2^31)
-  constexpr int PV = 16 / sizeof(VT);
-  const int q = (int)(kn / PV);
-  for (int t = threadIdx.x; t < 16 * q; t += 64 * MR_WAVES) {
-    const int c = t / q, kk = (t - c * q) * PV;
-    *reinterpret_cast<uint4 *>(ps + c * pstride + kk) =
-        *reinterpret_cast<const uint4 *>(P + c * ld + k0 + kk);
+  for (int v = 0; v < 4; ++v) pown[v] = P[(int64_t)M::out_row(lg, v) * ld + r0 + lr];
+  // P slice into LDS: 4 W threads per column, four 16-byte pieces each at a
+  // time
+  {
+    constexpr int PV = 16 / sizeof(VT), TPC = 4 * W;
+    const int c = threadIdx.x / TPC, np = kn / PV;
+    const VT *src = P + (int64_t)c * ld + k0;
+    VT *dst = ps + c * pstride;
+    for (int q = threadIdx.x % TPC; q < np; q += 4 * TPC) {
+      pv_t t[4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        t[m] = *reinterpret_cast<const pv_t *>(src + min(q + m * TPC, np - 1) * PV);
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        if (q + m * TPC < np) *reinterpret_cast<pv_t *>(dst + (q + m * TPC) * PV) = t[m];
+    }
   }
+  if (mark != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *mark = go != 0;
+  if (go == 0) return;
   __syncthreads();
   Acc acc[2] = {Acc{0, 0, 0, 0}, Acc{0, 0, 0, 0}};
-  const VT *pl = ps + lr * pstride + lg * VEC;
-  auto step = [&](const typename M::Raw &e, int64_t st) {
-    VT pb[VEC];
-    load_vec<VT, VEC>(pl + st * KB, pb);
+  d4 accd = d4{0.0, 0.0, 0.0, 0.0};
+  // FP32 sums move to FP64 registers every MR_FLUSH entries of k, whatever
+  // the slice length: with one FP32 sum over 768 the recursive residual of
+  // the mixed solves drifts (44 iterations instead of 28 at N = 4608)
+  auto flush = [&]() {
 #pragma unroll
-    for (int t = 0; t < VEC; ++t) acc[t & 1] = M::mfma(M::elem(e, t), pb[t], acc[t & 1]);
+    for (int v = 0; v < 4; ++v) {
+      accd[v] += (double)acc[0][v] + (double)acc[1][v];
+      acc[0][v] = acc[1][v] = 0;
+    }
   };
-  int64_t st0 = 0;
-  for (; st0 + 2 * U <= nsteps; st0 += U) {
+  const VT *pl = ps + lr * pstride + lg * VEC;
+  for (int st = 0; st < nsteps; st += U) {
+    if (sizeof(VT) == 4 && st % (MR_FLUSH / KB) == 0) flush();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      step(ea[u], st0 + u);
-      M::load(erow + (st0 + u + U) * KB, ea[u]);
+      if (st + u < nsteps) {
+        VT pb[VEC];
+        load_vec<VT, VEC>(pl + (st + u) * KB, pb);
+#pragma unroll
+        for (int t = 0; t < VEC; ++t) acc[t & 1] = M::mfma(pb[t], M::elem(ea[u], t), acc[t & 1]);
+      }
+      M::load(erow + min(st + u + U, nsteps - 1) * KB, ea[u]);
       // keep the refill here: scheduled after the last slot, all U refills
       // would go out together and the ring would drain every iteration
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  // the last U .. 2U - 1 steps (fewer when nsteps < U)
-#pragma unroll
-  for (int u = 0; u < U; ++u)
-    if (st0 + u < nsteps) {
-      step(ea[u], st0 + u);
-      if (st0 + u + U < nsteps) M::load(erow + (st0 + u + U) * KB, ea[u]);
-    }
-  st0 += U;
-#pragma unroll
-  for (int u = 0; u < U; ++u)
-    if (st0 + u < nsteps) step(ea[u], st0 + u);
-  // lane (lr, lg) holds rows out_row(lg, v) of column lr
-  VT *out = part + sl * split_stride + (int64_t)lr * ld + r0;
+  // lane (lr, lg) holds row lr of columns out_row(lg, v)
+  VT *out = part + sl * split_stride + r0 + lr;
   VT sv[4];
 #pragma unroll
-  for (int v = 0; v < 4; ++v) sv[v] = acc[0][v] + acc[1][v];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) out[M::out_row(lg, v)] = sv[v];
+  for (int v = 0; v < 4; ++v) {
+    sv[v] = sizeof(VT) == 4 ? (VT)(accd[v] + ((double)acc[0][v] + (double)acc[1][v]))
+                            : acc[0][v] + acc[1][v];
+    out[(int64_t)M::out_row(lg, v) * ld] = sv[v];
+  }
   if (pv_part == nullptr) return;
-  double pv = 0.0;
+  __shared__ double pvs[W][16];
 #pragma unroll
-  for (int v = 0; v < 4; ++v) pv += (double)pown[v] * (double)sv[v];
-  pv += __shfl_xor(pv, 16, 64);
-  pv += __shfl_xor(pv, 32, 64);
-  __shared__ double pvs[MR_WAVES][16];
-  if (lg == 0) pvs[wave][lr] = pv;
+  for (int v = 0; v < 4; ++v) {
+    double s = (double)pown[v] * (double)sv[v];
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off, 16);
+    if (lr == 0) pvs[wave][M::out_row(lg, v)] = s;
+  }
   __syncthreads();
   if (threadIdx.x < 16) {
     double t = 0.0;
 #pragma unroll
-    for (int w = 0; w < MR_WAVES; ++w) t += pvs[w][threadIdx.x];
-    pv_part[(sl * gridDim.x + blockIdx.x) * 16 + threadIdx.x] = t;
+    for (int w = 0; w < W; ++w) t += pvs[w][threadIdx.x];
+    pv_part[(int64_t)threadIdx.x * gridDim.x * gridDim.y + sl * gridDim.x + blockIdx.x] = t;
   }
 }
 
@@ -448,7 +463,7 @@ block_matvec_f64s_kernel(
       }
     __syncthreads();
     if (tid < COLS)
-      pv_part[((int64_t)blockIdx.y * gridDim.x + tile) * COLS + tid] =
+      pv_part[(int64_t)tid * gridDim.x * gridDim.y + (int64_t)blockIdx.y * gridDim.x + tile] =
           ((pvs[tid] + pvs[COLS + tid]) + pvs[2 * COLS + tid]) + pvs[3 * COLS + tid];
   }
 }
@@ -717,7 +732,7 @@ block_matvec_split_kernel(
     }
   __syncthreads();
   if (tid < COLS)
-    pv_part[((int64_t)blockIdx.y * gridDim.x + tile) * COLS + tid] =
+    pv_part[(int64_t)tid * gridDim.x * gridDim.y + (int64_t)blockIdx.y * gridDim.x + tile] =
         ((pvs[tid] + pvs[COLS + tid]) + pvs[2 * COLS + tid]) + pvs[3 * COLS + tid];
 }
 
@@ -738,22 +753,39 @@ __device__ inline double block_sum(double v, double *red) {
   return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// sum of v[b * stride + off] over b = b0, b0 + step, ... < nb in a fixed
-// order, sixteen loads in flight (clamped indices keep the loads unconditional)
-__device__ inline double strided_sum(const double *__restrict__ v, int nb, int b0, int step,
-                                     int64_t stride, int64_t off) {
-  double s = 0.0;
-  for (int b = b0; b < nb; b += 16 * step) {
-    double t[16];
-#pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      const int bb = b + m * step;
-      t[m] = v[(int64_t)(bb < nb ? bb : nb - 1) * stride + off];
-      if (bb >= nb) t[m] = 0.0;
-    }
-#pragma unroll
-    for (int m = 0; m < 16; ++m) s += t[m];
+// two sums with one barrier
+__device__ inline void block_sum2(double &u, double &v, double *ru, double *rv) {
+  u = wave_sum(u);
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) {
+    ru[threadIdx.x >> 6] = u;
+    rv[threadIdx.x >> 6] = v;
   }
+  __syncthreads();
+  u = (ru[0] + ru[1]) + (ru[2] + ru[3]);
+  v = (rv[0] + rv[1]) + (rv[2] + rv[3]);
+}
+
+// sum of v[b] over b = b0, b0 + step, ... < nb in a fixed order (b0 < step),
+// up to sixteen loads in flight (clamped indices keep the loads
+// unconditional; a short rest takes blocks of 4)
+template <int K>
+__device__ inline double strided_block(const double *__restrict__ v, int nb, int b, int step) {
+  double t[K], s = 0.0;
+#pragma unroll
+  for (int m = 0; m < K; ++m) t[m] = v[min(b + m * step, nb - 1)];
+  // (without this the scheduler adds each value as it arrives, two in flight)
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int m = 0; m < K; ++m) s += b + m * step < nb ? t[m] : 0.0;
+  return s;
+}
+__device__ inline double strided_sum(const double *__restrict__ v, int nb, int b0, int step) {
+  double s = 0.0;
+  int done = 0;
+  const int blocks = (nb + step - 1) / step;   // values of the longest thread
+  for (; blocks - done > 8; done += 16) s += strided_block<16>(v, nb, b0 + done * step, step);
+  for (; done < blocks; done += 4) s += strided_block<4>(v, nb, b0 + done * step, step);
   return s;
 }
 
@@ -848,7 +880,8 @@ __global__ void sum_partials_kernel(const double *__restrict__ partial, int nblk
   scal[field * cols + c] = s;
 }
 
-// z = M^-1 r; if set_p, p = z; partial r.r and r.z (active columns only).
+// z = M^-1 r; if set_p, p = z; partial r.r and r.z (active columns only)
+// into partial[(c * blocks + block) * 2 + {0, 1}].
 template <typename VT>
 __global__ __launch_bounds__(RED_THREADS) void cg_refresh_kernel(
     const double *__restrict__ r, double *__restrict__ z, VT *__restrict__ p,
@@ -878,32 +911,24 @@ __global__ __launch_bounds__(RED_THREADS) void cg_refresh_kernel(
   arr = block_sum(arr, red[1]);
   arz = block_sum(arz, red[2]);
   if (threadIdx.x == 0) {
-    partial[((int64_t)blk * cols + c) * 2] = arr;
-    partial[((int64_t)blk * cols + c) * 2 + 1] = arz;
+    partial[((int64_t)c * gridDim.x + blk) * 2] = arr;
+    partial[((int64_t)c * gridDim.x + blk) * 2 + 1] = arz;
   }
 }
 
-// Index of entry (block b, column c) of a partial array of nb blocks and
-// width values per entry: row-major part[b][c][width] (cmajor = 0) or
-// column-major part[c][b][width] (the PCG-DC dots). With nb = 1 both agree.
-__device__ inline int64_t part_at(int64_t b, int64_t c, int nb, int cols, int width, int cmajor) {
-  return cmajor ? (c * nb + b) * width : (b * cols + c) * width;
-}
-
-// out[c][w] = sum over b of part(b, c)[w] (w < width) in a fixed order: one
-// workgroup per column. Serves the update and direction kernels when
-// re-reducing all partials in each of their workgroups would cost more
+// out[c][w] = sum over b of part[c][b][w] (b < nb, w < width) in a fixed
+// order: one workgroup per column. Serves the update and direction kernels
+// when re-reducing all partials in each of their workgroups would cost more
 // than this extra launch (large systems).
 __global__ __launch_bounds__(RED_THREADS) void sum_cols_kernel(const double *__restrict__ part,
-                                                               int nb, int cols, int width,
-                                                               int cmajor,
+                                                               int nb, int width,
                                                                double *__restrict__ out) {
   __shared__ double red[3][4];
   const int c = blockIdx.x;
-  const int64_t bstride = cmajor ? width : (int64_t)cols * width;
   for (int w = 0; w < width; ++w) {
-    const double v = strided_sum(part, nb, threadIdx.x, RED_THREADS, bstride,
-                                 part_at(0, c, nb, cols, width, cmajor) + w);
+    double v = 0.0;
+#pragma unroll 8
+    for (int b = threadIdx.x; b < nb; b += RED_THREADS) v += part[((int64_t)c * nb + b) * width + w];
     const double t = block_sum(v, red[w % 3]);
     if (threadIdx.x == 0) out[c * width + w] = t;
   }
@@ -912,8 +937,8 @@ __global__ __launch_bounds__(RED_THREADS) void sum_cols_kernel(const double *__r
 // Reduce (rr, rz) partials into the scalars of active columns.
 // one workgroup per column
 __global__ __launch_bounds__(RED_THREADS) void set_scalars_kernel(
-    const double *__restrict__ partial, int nblk, int cols, int cmajor, double *__restrict__ scal,
-    int slot, const int *__restrict__ gate) {
+    const double *__restrict__ partial, int nblk, int cols, double *__restrict__ scal, int slot,
+    const int *__restrict__ gate) {
   __shared__ double red[3][4];
   if (gate != nullptr && *gate == 0) return;
   const int c = blockIdx.x;
@@ -921,9 +946,9 @@ __global__ __launch_bounds__(RED_THREADS) void set_scalars_kernel(
   if (threadIdx.x == 0) scal[S_RST * cols + c] = 0.0;   // the refresh has applied it
   double rr = 0.0, rz = 0.0;
   for (int b = threadIdx.x; b < nblk; b += RED_THREADS) {
-    const int64_t o = part_at(b, c, nblk, cols, 2, cmajor);
-    rr += partial[o];
-    rz += partial[o + 1];
+    const d2 v = reinterpret_cast<const d2 *>(partial)[(int64_t)c * nblk + b];
+    rr += v.x;
+    rz += v.y;
   }
   rr = block_sum(rr, red[0]);
   rz = block_sum(rz, red[1]);
@@ -933,9 +958,57 @@ __global__ __launch_bounds__(RED_THREADS) void set_scalars_kernel(
   }
 }
 
+// The vector kernels of an iteration (update, direction) are bound by memory
+// latency, not bytes: at N = 4608 a launch moves a few MB, and each load that
+// waits for another costs about 1 us (the per-XCD L2s start a kernel cold).
+// Each thread therefore issues every load it will need, its vectors', the
+// slices', the partials' and the scalars', before the first wait.
+
+// the sum of up to SM k-slice partials (fixed order) already loaded
+template <typename VT, int SM>
+__device__ inline void load_slices(const VT *__restrict__ part, int slices, int64_t stride,
+                                   uint32_t idx, VT (&t)[SM]) {
+#pragma unroll
+  for (int m = 0; m < SM; ++m) t[m] = (part + min(m, slices - 1) * stride)[idx];
+}
+template <typename VT, int SM>
+__device__ inline double add_slices(const VT *__restrict__ part, int slices, int64_t stride,
+                                    uint32_t idx, const VT (&t)[SM]) {
+  double v = 0.0;
+#pragma unroll
+  for (int m = 0; m < SM; ++m) v += m < slices ? (double)t[m] : 0.0;
+  for (int m = SM; m < slices; ++m) v += (double)part[m * stride + idx];
+  return v;
+}
+// the smallest of 1, 2, 4, 7, 9, 12, 16 that is at least the slice count (16 above)
+template <typename F> void with_slices(int slices, F &&f) {
+  if (slices <= 1) f(std::integral_constant<int, 1>());
+  else if (slices <= 2) f(std::integral_constant<int, 2>());
+  else if (slices <= 4) f(std::integral_constant<int, 4>());
+  else if (slices <= 7) f(std::integral_constant<int, 7>());
+  else if (slices <= 9) f(std::integral_constant<int, 9>());
+  else if (slices <= 12) f(std::integral_constant<int, 12>());
+  else f(std::integral_constant<int, 16>());
+}
+
+// alpha of a column from p.v and r.z; a breakdown (p^T E p <= 0) is recorded
+// by the thread with `report`
+__device__ inline double cg_alpha(double pv, double rz, int col, bool report,
+                                  int *__restrict__ flags) {
+  if (pv > 0.0 && isfinite(pv)) return rz / pv;
+  if (report) {
+    flags[0] = 1;
+    flags[1] = col;
+    double *dbg = reinterpret_cast<double *>(flags + 2);
+    dbg[0] = pv;
+    dbg[1] = rz;
+  }
+  return 0.0;
+}
+
 // Jacobi path: alpha = rz / p.v; x += alpha p; r -= alpha v; z = M^-1 r and
-// the partial rr, rz.
-template <typename VT>
+// the partial rr, rz. One row per thread; 4.5 -> 3.5 us at N = 288, one frame.
+template <typename VT, int SM>
 __global__ __launch_bounds__(RED_THREADS) void cg_update_kernel(
     double *__restrict__ x, double *__restrict__ r, double *__restrict__ z,
     const VT *__restrict__ p, const VT *__restrict__ vpart, int slices, int64_t stride,
@@ -943,109 +1016,107 @@ __global__ __launch_bounds__(RED_THREADS) void cg_update_kernel(
     const double *__restrict__ pv_part,
     const double *__restrict__ scal, int slot, double *__restrict__ partial,
     int *__restrict__ flags) {
+  static_assert(CHUNK == RED_THREADS, "one row per thread");
   __shared__ double red[3][4];
   const int c = blockIdx.y;
   const int blk = blockIdx.x;
-  const bool act = scal[S_ACT * cols + c] != 0.0 && scal[(S_HOLD0 + slot) * cols + c] == 0.0;
+  const uint32_t i = (uint32_t)blk * (uint32_t)CHUNK + threadIdx.x;
+  const bool live = i < (uint32_t)n;
+  const uint32_t idx = live ? i : 0;   // row in the column (its base is uniform)
+  x += c * ld;
+  r += c * ld;
+  z += c * ld;
+  p += c * ld;
+  vpart += c * ld;
+  const double xi = x[idx], r0 = r[idx], di = dinv[idx];
+  const VT pi = p[idx];
+  VT sv[SM];
+  load_slices<VT, SM>(vpart, slices, stride, idx, sv);
+  const double sact = scal[S_ACT * cols + c], shold = scal[(S_HOLD0 + slot) * cols + c],
+               rz = scal[(S_RZ0 + slot) * cols + c];
+  __builtin_amdgcn_sched_barrier(0);
+  double pv = strided_sum(pv_part + (int64_t)c * npv, npv, threadIdx.x, RED_THREADS);
+  const bool act = (sact != 0.0) & (shold == 0.0);
+  pv = block_sum(pv, red[0]);
   double arr = 0.0, arz = 0.0;
   if (act) {
-    double pv = 0.0;
-    for (int b = threadIdx.x; b < npv; b += RED_THREADS) pv += pv_part[(int64_t)b * cols + c];
-    pv = block_sum(pv, red[0]);
-    const double rz = scal[(S_RZ0 + slot) * cols + c];
-    double alpha = 0.0;
-    if (pv > 0.0 && isfinite(pv)) {
-      alpha = rz / pv;
-    } else if (blk == 0 && threadIdx.x == 0) {
-      flags[0] = 1;   // breakdown: p^T E p <= 0
-      flags[1] = c;
-      double *dbg = reinterpret_cast<double *>(flags + 2);
-      dbg[0] = pv;
-      dbg[1] = rz;
-    }
-    const int64_t i0 = (int64_t)blk * CHUNK;
-    const int64_t i1 = min(n, i0 + CHUNK);
-    for (int64_t i = i0 + threadIdx.x; i < i1; i += RED_THREADS) {
-      const int64_t idx = (int64_t)c * ld + i;
-      x[idx] += alpha * (double)p[idx];
-      const double ri = r[idx] - alpha * sum_slices(vpart, slices, stride, idx);
+    const double alpha = cg_alpha(pv, rz, c, blk == 0 && threadIdx.x == 0, flags);
+    const double ri = r0 - alpha * add_slices<VT, SM>(vpart, slices, stride, idx, sv);
+    const double zi = ri * di;
+    if (live) {
+      x[idx] = xi + alpha * (double)pi;
       r[idx] = ri;
-      const double zi = ri * dinv[i];
       z[idx] = zi;
-      arr += ri * ri;
-      arz += ri * zi;
+      arr = ri * ri;
+      arz = ri * zi;
     }
   }
-  arr = block_sum(arr, red[1]);
-  arz = block_sum(arz, red[2]);
+  block_sum2(arr, arz, red[1], red[2]);
   if (threadIdx.x == 0) {
-    partial[((int64_t)blk * cols + c) * 2] = arr;
-    partial[((int64_t)blk * cols + c) * 2 + 1] = arz;
+    partial[((int64_t)c * gridDim.x + blk) * 2] = arr;
+    partial[((int64_t)c * gridDim.x + blk) * 2 + 1] = arz;
   }
 }
 
 // PCG-DC path of the update: alpha = rz / p.v; x += alpha p; r -= alpha v,
 // and r also into its row-interleaved copy rt (layout of rows_kernel).
-// Workgroup = 16 rows x one column group of 16; thread t takes column t / 16
-// and row t % 16 (column-major accesses in 128-byte pieces); the tile goes
-// through LDS so that its rt rows are written as 2 KB of whole lines.
-constexpr int UP_ROWS = 16;
-template <typename VT>
+// Workgroup = 16 R rows x one column group of 16; thread t takes column t / 16
+// and rows t % 16 + 16 q (column-major accesses in 128-byte pieces; the 16
+// threads of a column also add up its p.v partials); the tile goes
+// through LDS so that its rt rows are written as 2 KB of whole lines. R = 1
+// up to 512 workgroups, then 2 and 4, which re-reduce the p.v partials less
+// often. 6.2 -> 4.3 us at N = 4608, 16 columns.
+template <typename VT, int SM, int R>
 __global__ __launch_bounds__(RED_THREADS) void cg_update_pc_kernel(
     double *__restrict__ x, double *__restrict__ r, const VT *__restrict__ p,
     const VT *__restrict__ vpart, int slices, int64_t stride, int64_t ld, int64_t n, int cols,
     int npv, const double *__restrict__ pv_part, const double *__restrict__ scal, int slot,
     int *__restrict__ flags, double *__restrict__ rt) {
-  __shared__ double pvr[16][kColGroup + 1];
-  __shared__ double alpha_s[kColGroup];
-  __shared__ double tile[UP_ROWS][kColGroup + 1];
+  __shared__ double tile[R][16][kColGroup + 1];
   const int g = blockIdx.y;
-  const int64_t r0 = (int64_t)blockIdx.x * UP_ROWS;
-  // p.v of the group's columns: 16 threads per column over the partials
-  {
-    const int c = threadIdx.x & 15, part = threadIdx.x >> 4;
-    const int col = g * kColGroup + c;
-    pvr[part][c] = strided_sum(pv_part, npv, part, 16, cols, col);
-  }
-  __syncthreads();
-  if (threadIdx.x < kColGroup) {
-    const int c = threadIdx.x, col = g * kColGroup + c;
-    double pv = 0.0;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) pv += pvr[q][c];
-    const double rz = scal[(S_RZ0 + slot) * cols + col];
-    double alpha = 0.0;
-    if (scal[S_ACT * cols + col] != 0.0 && scal[(S_HOLD0 + slot) * cols + col] == 0.0) {
-      if (pv > 0.0 && isfinite(pv)) {
-        alpha = rz / pv;
-      } else if (blockIdx.x == 0) {
-        flags[0] = 1;   // breakdown: p^T E p <= 0
-        flags[1] = col;
-        double *dbg = reinterpret_cast<double *>(flags + 2);
-        dbg[0] = pv;
-        dbg[1] = rz;
-      }
-    }
-    alpha_s[c] = alpha;
-  }
-  __syncthreads();
+  const int64_t r0 = (int64_t)blockIdx.x * (16 * R);
   const int c = threadIdx.x >> 4, rr = threadIdx.x & 15;
   const int col = g * kColGroup + c;
-  const int64_t i = r0 + rr;
-  const int64_t idx = (int64_t)col * ld + i;
-  double ri = 0.0;
-  if (i < n) {
-    ri = r[idx];
-    if (scal[S_ACT * cols + col] != 0.0 && scal[(S_HOLD0 + slot) * cols + col] == 0.0) {
-      const double alpha = alpha_s[c];
-      x[idx] += alpha * (double)p[idx];
-      ri -= alpha * sum_slices(vpart, slices, stride, idx);
-      r[idx] = ri;
+  // element offset from the group's base (16 ld < 2^32): rows < ld, padded
+  // rows hold 0
+  const uint32_t idx0 = (uint32_t)c * (uint32_t)ld + (uint32_t)r0 + rr;
+  x += g * kColGroup * ld;
+  r += g * kColGroup * ld;
+  p += g * kColGroup * ld;
+  vpart += g * kColGroup * ld;
+  double xv[R], rv[R];
+  VT pv[R], sv[R][SM];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    xv[q] = x[idx0 + 16 * q];
+    rv[q] = r[idx0 + 16 * q];
+    pv[q] = p[idx0 + 16 * q];
+    load_slices<VT, SM>(vpart, slices, stride, idx0 + 16 * q, sv[q]);
+  }
+  const double sact = scal[S_ACT * cols + col], shold = scal[(S_HOLD0 + slot) * cols + col],
+               rz = scal[(S_RZ0 + slot) * cols + col];
+  __builtin_amdgcn_sched_barrier(0);
+  double s = strided_sum(pv_part + (int64_t)col * npv, npv, rr, 16);
+#pragma unroll
+  for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off, 16);
+  if ((sact != 0.0) & (shold == 0.0)) {
+    const double alpha = cg_alpha(s, rz, col, blockIdx.x == 0 && rr == 0, flags);
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      rv[q] -= alpha * add_slices<VT, SM>(vpart, slices, stride, idx0 + 16 * q, sv[q]);
+      if (r0 + rr + 16 * q < n) {
+        x[idx0 + 16 * q] = xv[q] + alpha * (double)pv[q];
+        r[idx0 + 16 * q] = rv[q];
+      }
     }
   }
-  tile[rr][c] = ri;
+#pragma unroll
+  for (int q = 0; q < R; ++q) tile[q][rr][c] = r0 + rr + 16 * q < n ? rv[q] : 0.0;
   __syncthreads();
-  rt[((int64_t)g * ld + r0) * kColGroup + threadIdx.x] = tile[threadIdx.x >> 4][threadIdx.x & 15];
+#pragma unroll
+  for (int q = 0; q < R; ++q)
+    rt[((int64_t)g * ld + r0 + 16 * q) * kColGroup + threadIdx.x] =
+        tile[q][threadIdx.x >> 4][threadIdx.x & 15];
 }
 
 // Row-interleaved copy of the residual for the PCG-DC apply: column group g
@@ -1604,32 +1675,36 @@ constexpr double kHold = 1e-3;
 template <typename VT>
 __global__ __launch_bounds__(RED_THREADS) void cg_direction_kernel(
     VT *__restrict__ p, const double *__restrict__ z, int64_t ld, int64_t n, int cols, int nblk,
-    const double *__restrict__ partial, int cmajor, double *__restrict__ scal, int slot, double tol,
+    const double *__restrict__ partial, double *__restrict__ scal, int slot, double tol,
     double ru, int *__restrict__ flags) {
-  __shared__ double red[3][4];
+  __shared__ double red[2][4];
   const int c = blockIdx.y;
   const int blk = blockIdx.x;
-  if (scal[S_ACT * cols + c] == 0.0) return;
-  if (scal[(S_HOLD0 + slot) * cols + c] != 0.0) {
+  const uint32_t i = (uint32_t)blk * (uint32_t)CHUNK + threadIdx.x;
+  const bool live = i < (uint32_t)n;
+  const uint32_t idx = live ? i : 0;
+  z += c * ld;
+  p += c * ld;
+  const double zi = z[idx];
+  const VT pi = p[idx];
+  const double sact = scal[S_ACT * cols + c], shold = scal[(S_HOLD0 + slot) * cols + c],
+               rz = scal[(S_RZ0 + slot) * cols + c], bn2 = scal[S_BN2 * cols + c],
+               last = scal[S_RT * cols + c];
+  const d2 *pc2 = reinterpret_cast<const d2 *>(partial) + (int64_t)c * nblk;
+  const int b0 = min((int)threadIdx.x, nblk - 1);
+  d2 s = pc2[b0];
+  if ((int)threadIdx.x >= nblk) s = d2{0.0, 0.0};
+#pragma unroll 4
+  for (int b = threadIdx.x + RED_THREADS; b < nblk; b += RED_THREADS) s += pc2[b];
+  if (sact == 0.0) return;
+  if (shold != 0.0) {
     if (blk == 0 && threadIdx.x == 0) scal[(S_HOLD0 + (slot ^ 1)) * cols + c] = 1.0;
     return;
   }
-  double rr = 0.0, rzn = 0.0;
-  for (int b = threadIdx.x; b < nblk; b += RED_THREADS) {
-    const int64_t o = part_at(b, c, nblk, cols, 2, cmajor);
-    rr += partial[o];
-    rzn += partial[o + 1];
-  }
-  rr = block_sum(rr, red[0]);
-  rzn = block_sum(rzn, red[1]);
-  const double rz = scal[(S_RZ0 + slot) * cols + c];
+  double rr = s.x, rzn = s.y;
+  block_sum2(rr, rzn, red[0], red[1]);
   const double beta = (rz != 0.0) ? rzn / rz : 0.0;
-  const int64_t i0 = (int64_t)blk * CHUNK;
-  const int64_t i1 = min(n, i0 + CHUNK);
-  for (int64_t i = i0 + threadIdx.x; i < i1; i += RED_THREADS) {
-    const int64_t idx = (int64_t)c * ld + i;
-    p[idx] = (VT)(z[idx] + beta * (double)p[idx]);
-  }
+  if (live) p[idx] = (VT)(zi + beta * (double)pi);
   if (blk == 0 && threadIdx.x == 0) {
     if (rr > 0.0 && !(rzn > 0.0)) {
       flags[0] = 2;   // breakdown: r^T P r <= 0
@@ -1641,8 +1716,7 @@ __global__ __launch_bounds__(RED_THREADS) void cg_direction_kernel(
     scal[(S_RZ0 + (slot ^ 1)) * cols + c] = rzn;
     scal[S_RR * cols + c] = rr;
     scal[S_IT * cols + c] += 1.0;
-    const double bn = sqrt(scal[S_BN2 * cols + c]);
-    const double lim = kHold * fmax(0.5 * tol * bn, ru * scal[S_RT * cols + c]);
+    const double lim = kHold * fmax(0.5 * tol * sqrt(bn2), ru * last);
     scal[(S_HOLD0 + (slot ^ 1)) * cols + c] = (sqrt(rr) <= lim) ? 1.0 : 0.0;
   }
 }
@@ -1937,14 +2011,20 @@ int64_t f64s_slices(int64_t ld, int64_t cols) {
   return wide_slices(ld, cols, sizeof(double), sizeof(double), 256);
 }
 
-// k slices of the row-split kernel (16 columns): about 432 workgroups, each
-// slice a multiple of the k step and short enough for its P copy in LDS
+// k slices of the row-split kernel (16 columns): about 216 workgroups (N =
+// 4608, FP32: 17.6 us with 216, 18.3 with 432, and fewer partial sums for
+// the update to read; FP64, whose reads need more in flight: 36 us with 360,
+// 31.3 with 432, 30.1 with 504), each slice a multiple of the k step, at least four steps,
+// and short enough for its P copy in LDS
 template <typename T> int64_t rows_slices(int64_t ld, int64_t &kslice) {
   constexpr int64_t kb = 4 * Mv<T>::VEC;
-  const int64_t blocks = ld / (16 * MR_WAVES);
-  const int64_t want = std::max<int64_t>(1, (432 + blocks - 1) / std::max<int64_t>(1, blocks));
-  kslice = (ld / want + kb - 1) / kb * kb;
-  kslice = std::min<int64_t>(std::max<int64_t>(kslice, kb), mr_kmax<T>());
+  const int64_t blocks = ld / (16 * mr_waves(ld));
+  const int64_t wgs = sizeof(T) == 8 && mr_waves(ld) == 8 ? 504 : 216;
+  const int64_t want = std::max<int64_t>(1, (wgs + blocks - 1) / blocks);
+  kslice = round_up((ld + want - 1) / want, kb);
+  kslice = std::min<int64_t>(std::max<int64_t>(kslice, 4 * kb), mr_kmax<T>());
+  const int64_t sl = (ld + kslice - 1) / kslice;
+  kslice = round_up((ld + sl - 1) / sl, kb);   // equal slices
   return (ld + kslice - 1) / kslice;
 }
 
@@ -1954,7 +2034,7 @@ template <typename T> int64_t matvec_npv(int64_t ld, int64_t cols) {
   int64_t k = 0;
   if (uses_split<T>(cols)) return split_slices(ld, cols, sizeof(T)) * (ld / SP_ROWS);
   if (uses_f64s<T>(cols)) return f64s_slices(ld, cols) * (ld / F64_ROWS);
-  return rows_slices<T>(ld, k) * (ld / (16 * MR_WAVES));   // 16 columns
+  return rows_slices<T>(ld, k) * (ld / (16 * mr_waves(ld)));   // 16 columns
 }
 
 // slices of the kernel that serves c columns of an E of type T
@@ -1994,7 +2074,7 @@ hipError_t launch_matvec_t(hipStream_t st, const T *E, int64_t ld, const typenam
   slices = split ? (int)split_slices(ld, NG * 16, sizeof(T))
            : f64s ? (int)f64s_slices(ld, NG * 16)
                   : (int)rows_slices<T>(ld, kslice);
-  const int64_t tiles = split ? ld / SP_ROWS : f64s ? ld / F64_ROWS : ld / (16 * MR_WAVES);
+  const int64_t tiles = split ? ld / SP_ROWS : f64s ? ld / F64_ROWS : ld / (16 * mr_waves(ld));
   hipEvent_t ea = nullptr, eb = nullptr;
   int *mark = nullptr;
   if (t_prof && t_prof->sample(prec_of<T>())) {
@@ -2019,9 +2099,10 @@ hipError_t launch_matvec_t(hipStream_t st, const T *E, int64_t ld, const typenam
                           mark);
   } else {
     const size_t lds = sizeof(typename Mv<T>::VT) * 16 * (size_t)(kslice + mr_pad<T>());
-    hipExtLaunchKernelGGL((block_matvec_rows_kernel<T>), dim3((unsigned)tiles, (unsigned)slices),
-                          dim3(64 * MR_WAVES), lds, st, ea, eb, 0, E, ld, P, part, kslice,
-                          (int64_t)16 * ld, pv_part, gate, mark);
+    const int w = mr_waves(ld);
+    auto kern = w == 4 ? block_matvec_rows_kernel<T, 4> : block_matvec_rows_kernel<T, 8>;
+    hipExtLaunchKernelGGL(kern, dim3((unsigned)tiles, (unsigned)slices), dim3(64 * w), lds, st, ea,
+                          eb, 0, E, ld, P, part, kslice, (int64_t)16 * ld, pv_part, gate, mark);
   }
   return hipGetLastError();
 }
@@ -2300,7 +2381,6 @@ template <typename T> struct Solver {
   }
   int nred() const { return pc ? npc() : nblk; }
   const double *dots() const { return pc ? s->ws.bpart : partial; }
-  int dots_cmajor() const { return pc ? 1 : 0; }
 
   // z = P r with the DC preconditioner; to_rows: r was written by another
   // kernel than the update, so its row-interleaved copy is made first
@@ -2321,7 +2401,7 @@ template <typename T> struct Solver {
       hipLaunchKernelGGL(cg_refresh_kernel<VT>, grid(), dim3(RED_THREADS), 0, st, r, z, p, s->dinv,
                          ld, n, (int)cols, scal, partial, set_p ? 1 : 0, gate);
     hipLaunchKernelGGL(set_scalars_kernel, dim3((unsigned)cols), dim3(RED_THREADS), 0, st, dots(),
-                       nred(), (int)cols, dots_cmajor(), scal, slot, gate);
+                       nred(), (int)cols, scal, slot, gate);
     return hipGetLastError();
   }
 
@@ -2334,33 +2414,43 @@ template <typename T> struct Solver {
     // re-reducing them would read more than kRedLoads values
     const double *pvs = pvp;
     int npvs = npv;
-    const int64_t upd_loads = pc ? (int64_t)npv * ld * cols / kColGroup : (int64_t)npv * nblk * cols;
+    const int64_t upc = (ld / 16) * (cols / kColGroup);   // workgroups of the PCG update at R = 1
+    const int R = upc <= 512 ? 1 : upc <= 1024 ? 2 : 4;
+    const int64_t upd_loads = pc ? (int64_t)npv * kColGroup * (upc / R) : (int64_t)npv * nblk * cols;
     if (upd_loads > kRedLoads) {
       hipLaunchKernelGGL(sum_cols_kernel, dim3((unsigned)cols), dim3(RED_THREADS), 0, st, pvp, npv,
-                         (int)cols, 1, 0, s->ws.red);
+                         1, s->ws.red);
       pvs = s->ws.red;
       npvs = 1;
     }
     if (pc) {
-      hipLaunchKernelGGL(cg_update_pc_kernel<VT>, dim3((unsigned)(ld / UP_ROWS), (unsigned)(cols / kColGroup)),
-                         dim3(RED_THREADS), 0, st, x, r, (const VT *)p, (const VT *)v, sl, ld * cols,
-                         ld, n, (int)cols, npvs, pvs, scal, slot, flags, rt);
+      with_slices(sl, [&](auto sm) {
+        constexpr int SM = decltype(sm)::value;
+        auto kern = R == 1   ? cg_update_pc_kernel<VT, SM, 1>
+                    : R == 2 ? cg_update_pc_kernel<VT, SM, 2>
+                             : cg_update_pc_kernel<VT, SM, 4>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(ld / (16 * R)), (unsigned)(cols / kColGroup)),
+                           dim3(RED_THREADS), 0, st, x, r, (const VT *)p, (const VT *)v, sl,
+                           ld * cols, ld, n, (int)cols, npvs, pvs, scal, slot, flags, rt);
+      });
       precondition(false, flags + F_ANY, false);
     } else {
-      hipLaunchKernelGGL(cg_update_kernel<VT>, grid(), dim3(RED_THREADS), 0, st, x, r, z, p,
-                         v, sl, ld * cols, s->dinv, ld, n, (int)cols, npvs, pvs, scal, slot, partial,
-                         flags);
+      with_slices(sl, [&](auto sm) {
+        hipLaunchKernelGGL((cg_update_kernel<VT, decltype(sm)::value>), grid(), dim3(RED_THREADS),
+                           0, st, x, r, z, p, v, sl, ld * cols, s->dinv, ld, n, (int)cols, npvs,
+                           pvs, scal, slot, partial, flags);
+      });
     }
     const double *ds = dots();
     int nds = nred();
     if (2 * (int64_t)nds * nblk * cols > kRedLoads) {
       hipLaunchKernelGGL(sum_cols_kernel, dim3((unsigned)cols), dim3(RED_THREADS), 0, st, ds, nds,
-                         (int)cols, 2, dots_cmajor(), s->ws.red + MAX_COLS);
+                         2, s->ws.red + MAX_COLS);
       ds = s->ws.red + MAX_COLS;
       nds = 1;
     }
     hipLaunchKernelGGL(cg_direction_kernel<VT>, grid(), dim3(RED_THREADS), 0, st, p, z, ld, n,
-                       (int)cols, nds, ds, dots_cmajor(), scal, slot, tol, ru, flags);
+                       (int)cols, nds, ds, scal, slot, tol, ru, flags);
     slot ^= 1;
     return hipGetLastError();
   }
