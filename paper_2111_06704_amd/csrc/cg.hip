@@ -1875,23 +1875,20 @@ __global__ void ctl_update_kernel(const double *__restrict__ partial, int nblk,
   }
 }
 
-template <typename VT>
-__global__ void sum_slices_kernel(const VT *__restrict__ part, int slices, int64_t stride,
-                                  double *__restrict__ out, int64_t count) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) out[i] = sum_slices(part, slices, stride, i);
-}
-
-__global__ void f64_to_f32_kernel(const double *__restrict__ a, float *__restrict__ b,
-                                  int64_t count) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) b[i] = (float)a[i];
-}
-
-__global__ void f32_to_f64_kernel(const float *__restrict__ a, double *__restrict__ b,
-                                  int64_t count) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) b[i] = (double)a[i];
+// out[f][i] = sum over the slices of column f (fixed order) - qsol_f d_i
+// (qsol may be null: no shift), written in the caller's (f, n) layout
+template <typename VT, int SM>
+__global__ __launch_bounds__(RED_THREADS) void sum_slices_kernel(
+    const VT *__restrict__ part, int slices, int64_t stride, int64_t ld, int64_t n,
+    const double *__restrict__ qsol, const double *__restrict__ d, double *__restrict__ out) {
+  const int c = blockIdx.y;
+  const uint32_t i = blockIdx.x * RED_THREADS + threadIdx.x;
+  if (i >= (uint32_t)n) return;
+  part += c * ld;
+  VT sv[SM];
+  load_slices<VT, SM>(part, slices, stride, i, sv);
+  const double shift = qsol != nullptr ? qsol[c] * d[i] : 0.0;
+  out[c * n + i] = add_slices<VT, SM>(part, slices, stride, i, sv) - shift;
 }
 
 __global__ void zero_kernel(double *__restrict__ a, int64_t count) {
@@ -1900,12 +1897,13 @@ __global__ void zero_kernel(double *__restrict__ a, int64_t count) {
 }
 
 // Copy rows of a frame-major (f, n) array into (cols, ld) with zero padding.
+template <typename VT>
 __global__ void pack_kernel(const double *__restrict__ src, int64_t n, int64_t f,
-                            double *__restrict__ dst, int64_t ld, int64_t cols) {
+                            VT *__restrict__ dst, int64_t ld, int64_t cols) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t c = blockIdx.y;
   if (i >= ld || c >= cols) return;
-  dst[c * ld + i] = (c < f && i < n) ? src[c * n + i] : 0.0;
+  dst[c * ld + i] = (c < f && i < n) ? (VT)src[c * n + i] : (VT)0;
 }
 
 // Two-step neutralisation (Eq. 35): q = x - (sum(x) + Q_sol) d, one block per
@@ -2725,14 +2723,14 @@ cpm_status solve_block(cpm_system *s, const double *b_dev, const double *qsol_de
     const int64_t cols = round_up(fc, kColGroup);
     cpm_status stt = ensure_workspace(s, cols);
     if (stt != CPM_OK) return stt;
-    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((ld + 255) / 256), (unsigned)cols), dim3(256),
+    hipLaunchKernelGGL(pack_kernel<double>, dim3((unsigned)((ld + 255) / 256), (unsigned)cols), dim3(256),
                        0, st, b_dev + f0 * n, n, (int64_t)fc, s->ws.bx, ld, cols);
     if (x0_dev) {
-      hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((ld + 255) / 256), (unsigned)cols),
+      hipLaunchKernelGGL(pack_kernel<double>, dim3((unsigned)((ld + 255) / 256), (unsigned)cols),
                          dim3(256), 0, st, x0_dev + f0 * n, n, (int64_t)fc, (double *)s->ws.x, ld,
                          cols);
       if (r0_dev)
-        hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((ld + 255) / 256), (unsigned)cols),
+        hipLaunchKernelGGL(pack_kernel<double>, dim3((unsigned)((ld + 255) / 256), (unsigned)cols),
                            dim3(256), 0, st, r0_dev + f0 * n, n, (int64_t)fc, (double *)s->ws.r,
                            ld, cols);
     } else {
@@ -2777,13 +2775,35 @@ cpm_status solve_block(cpm_system *s, const double *b_dev, const double *qsol_de
   return result;
 }
 
+namespace {
+
+// out = V = E P of the packed columns, minus the shift of sum_slices_kernel
+template <typename T>
+cpm_status product_out(cpm_system *s, const T *E, int64_t cols, int fc,
+                       const typename Mv<T>::VT *in, typename Mv<T>::VT *v, const double *qsol,
+                       const double *d, double *out) {
+  using VT = typename Mv<T>::VT;
+  int sl = 0;
+  CPM_HIP_CHECK(launch_matvec<T>(s->stream, E, s->ld, cols, in, v, nullptr, sl));
+  with_slices(sl, [&](auto sm) {
+    hipLaunchKernelGGL((sum_slices_kernel<VT, decltype(sm)::value>),
+                       dim3((unsigned)((s->n + RED_THREADS - 1) / RED_THREADS), (unsigned)fc),
+                       dim3(RED_THREADS), 0, s->stream, (const VT *)v, sl, s->ld * cols, s->ld,
+                       s->n, qsol, d, out);
+  });
+  return CPM_OK;
+}
+
+}  // namespace
+
 cpm_status matvec_cols(cpm_system *s, int precision, const double *p_dev, int64_t f,
                        double *v_dev) {
-  return matvec_cols_with(s, precision, nullptr, p_dev, f, v_dev);
+  return matvec_cols_with(s, precision, nullptr, p_dev, f, v_dev, nullptr, nullptr);
 }
 
 cpm_status matvec_cols_with(cpm_system *s, int precision, const double *M64, const double *p_dev,
-                            int64_t f, double *v_dev) {
+                            int64_t f, double *v_dev, const double *qsol_dev,
+                            const double *shift_dev) {
   t_prof = &s->prof;
   t_n = s->n;
   if (M64 == nullptr) M64 = s->E64;
@@ -2794,30 +2814,23 @@ cpm_status matvec_cols_with(cpm_system *s, int precision, const double *M64, con
     const int64_t cols = round_up(fc, kColGroup);
     cpm_status stt = ensure_workspace(s, cols);
     if (stt != CPM_OK) return stt;
-    double *in = s->ws.bres;   // packed input (double)
-    double *out = (double *)s->ws.v;
-    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((ld + 255) / 256), (unsigned)cols), dim3(256),
-                       0, st, p_dev + f0 * n, n, (int64_t)fc, in, ld, cols);
-    int sl = 0;
-    double *res = s->ws.bx;   // summed product (double)
+    const dim3 pg((unsigned)((ld + 255) / 256), (unsigned)cols);
+    const double *src = p_dev + f0 * n, *qs = qsol_dev ? qsol_dev + f0 : nullptr;
+    double *out = v_dev + f0 * n;
     if (precision == CPM_PREC_F64) {
-      CPM_HIP_CHECK(launch_matvec<double>(st, M64, ld, cols, in, out, nullptr, sl));
-      hipLaunchKernelGGL(sum_slices_kernel<double>, elem_grid(ld * cols), dim3(256), 0, st,
-                         (const double *)out, sl, ld * cols, res, ld * cols);
+      double *in = s->ws.bres, *v = (double *)s->ws.v;
+      hipLaunchKernelGGL(pack_kernel<double>, pg, dim3(256), 0, st, src, n, (int64_t)fc, in, ld,
+                         cols);
+      stt = product_out<double>(s, M64, cols, fc, in, v, qs, shift_dev, out);
     } else {
-      float *pf = (float *)s->ws.pf, *vf = (float *)s->ws.vf;
-      hipLaunchKernelGGL(f64_to_f32_kernel, elem_grid(ld * cols), dim3(256), 0, st, in, pf,
-                         ld * cols);
-      if (precision == CPM_PREC_F32)
-        CPM_HIP_CHECK(launch_matvec<float>(st, s->E32, ld, cols, pf, vf, nullptr, sl));
-      else
-        CPM_HIP_CHECK(launch_matvec<uint16_t>(st, s->E16, ld, cols, pf, vf, nullptr, sl));
-      hipLaunchKernelGGL(sum_slices_kernel<float>, elem_grid(ld * cols), dim3(256), 0, st,
-                         (const float *)vf, sl, ld * cols, res, ld * cols);
+      float *in = (float *)s->ws.pf, *v = (float *)s->ws.vf;
+      hipLaunchKernelGGL(pack_kernel<float>, pg, dim3(256), 0, st, src, n, (int64_t)fc, in, ld,
+                         cols);
+      stt = precision == CPM_PREC_F32
+                ? product_out<float>(s, s->E32, cols, fc, in, v, qs, shift_dev, out)
+                : product_out<uint16_t>(s, s->E16, cols, fc, in, v, qs, shift_dev, out);
     }
-    out = res;
-    CPM_HIP_CHECK(hipMemcpy2DAsync(v_dev + f0 * n, sizeof(double) * n, out, sizeof(double) * ld,
-                                   sizeof(double) * n, fc, hipMemcpyDeviceToDevice, st));
+    if (stt != CPM_OK) return stt;
   }
   CPM_HIP_CHECK(hipGetLastError());
   return CPM_OK;

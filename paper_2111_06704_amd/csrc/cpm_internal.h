@@ -340,9 +340,11 @@ cpm_status solve_block(cpm_system *s, const double *b_dev, const double *qsol_de
 cpm_status solve_dprime(cpm_system *s, double tol, int max_iter);
 cpm_status matvec_cols(cpm_system *s, int precision, const double *p_dev, int64_t f,
                        double *v_dev);
-// V = M P with an ld x ld FP64 matrix M instead of E (precision CPM_PREC_F64)
+// V = M P with an ld x ld FP64 matrix M instead of E (precision CPM_PREC_F64);
+// qsol_dev (f,) and shift_dev (n,), may be null: V - qsol_f shift
 cpm_status matvec_cols_with(cpm_system *s, int precision, const double *M64, const double *p_dev,
-                            int64_t f, double *v_dev);
+                            int64_t f, double *v_dev, const double *qsol_dev,
+                            const double *shift_dev);
 // z = P r (PCG-DC preconditioner) for f vectors (f, n), the CG's own apply kernel
 cpm_status precond_cols(cpm_system *s, const double *r_dev, int64_t f, double *z_dev);
 // slices of the coarse Z^T-side product for mp padded patches

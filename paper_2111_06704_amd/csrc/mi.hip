@@ -22,14 +22,6 @@ __global__ void unit_rhs_kernel(double *__restrict__ b, int64_t n, int64_t row0,
   if (i < n && c < f) b[c * n + i] = (i == row0 + c) ? 1.0 : 0.0;
 }
 
-// q[f][i] -= Q_sol[f] d_i
-__global__ void mi_shift_kernel(double *__restrict__ q, const double *__restrict__ qsol,
-                                const double *__restrict__ d, int64_t n, int64_t f) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n * f) return;
-  q[idx] -= qsol[idx / n] * d[idx % n];
-}
-
 }  // namespace
 }  // namespace cpm
 
@@ -109,12 +101,8 @@ cpm_status cpm_mi_solve(cpm_system *s, const double *b_dev, const double *qsol_d
     set_error("cpm_mi_build first");
     return CPM_ESTATE;
   }
-  cpm_status rc = matvec_cols_with(s, CPM_PREC_F64, s->S, b_dev, f, q_out_dev);
-  if (rc != CPM_OK) return rc;
-  hipLaunchKernelGGL(mi_shift_kernel, dim3((unsigned)((s->n * f + 255) / 256)), dim3(256), 0,
-                     s->stream, q_out_dev, qsol_dev, s->dvec, s->n, f);
-  CPM_HIP_CHECK(hipGetLastError());
-  return CPM_OK;
+  // q = S b - Q_sol d: the shift goes with the sum over the product's slices
+  return matvec_cols_with(s, CPM_PREC_F64, s->S, b_dev, f, q_out_dev, qsol_dev, s->dvec);
 }
 
 }  // extern "C"

@@ -37,21 +37,32 @@ constexpr int OW1 = 0, OB1 = OW1 + NIN * NH, OW2 = OB1 + NH, OB2 = OW2 + NH * NH
 
 __device__ inline float sigm(float a) { return 1.0f / (1.0f + __expf(-a)); }
 
+// One workgroup of FT threads per frame: with few frames these kernels are
+// bound by the latency of each thread's loads, so a frame gets a whole CU's
+// worth of threads (N = 4608, 16 frames, 256 threads -> 1024: the neutral
+// shift 8.6 -> 4.8 us, the Lagrange shift 7.5 -> 6.8 us).
+constexpr int FT = 1024;
+__device__ inline double frame_sum(double v) {
+  __shared__ double red[FT / 64];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double s = 0.0;
+#pragma unroll
+  for (int w = 0; w < FT / 64; ++w) s += red[w];
+  return s;
+}
+
 // per-frame mean of b (fixed-order block reduction)
-__global__ __launch_bounds__(256) void frame_mean_kernel(const double *__restrict__ b, int64_t n,
-                                                         double *__restrict__ mean) {
-  __shared__ double red[256];
+__global__ __launch_bounds__(FT) void frame_mean_kernel(const double *__restrict__ b, int64_t n,
+                                                        double *__restrict__ mean) {
   const int64_t f = blockIdx.x;
   double s = 0.0;
 #pragma unroll 8
-  for (int64_t i = threadIdx.x; i < n; i += 256) s += b[f * n + i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) mean[f] = red[0] / (double)n;
+  for (int64_t i = threadIdx.x; i < n; i += FT) s += b[f * n + i];
+  s = frame_sum(s);
+  if (threadIdx.x == 0) mean[f] = s / (double)n;
 }
 
 // features of rows; row r is (frame, atom) = (id / n, id % n) with id =
@@ -336,61 +347,42 @@ __global__ void targets_kernel(const double *__restrict__ q, const int64_t *__re
 }
 
 // q0 = q_scale * y, frame-wise shift to sum(q0) = -Q_sol (one block per frame)
-__global__ __launch_bounds__(256) void neutral_shift_kernel(const float *__restrict__ y,
-                                                            const double *__restrict__ qchi,
-                                                            int64_t n, double qs,
-                                                            const double *__restrict__ qsol,
-                                                            double *__restrict__ q0) {
-  __shared__ double red[256];
+__global__ __launch_bounds__(FT) void neutral_shift_kernel(const float *__restrict__ y,
+                                                           const double *__restrict__ qchi,
+                                                           int64_t n, double qs,
+                                                           const double *__restrict__ qsol,
+                                                           double *__restrict__ q0) {
   const int64_t f = blockIdx.x;
+  const double qsf = qsol[f];
   double s = 0.0;
 #pragma unroll 8
-  for (int64_t i = threadIdx.x; i < n; i += 256) {
-    const double v = y ? qs * (double)y[f * n + i] : qchi[i];
-    q0[f * n + i] = v;
-    s += v;
-  }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
-  }
-  const double shift = (red[0] + qsol[f]) / (double)n;
-  __syncthreads();
+  for (int64_t i = threadIdx.x; i < n; i += FT) s += y ? qs * (double)y[f * n + i] : qchi[i];
+  const double shift = (frame_sum(s) + qsf) / (double)n;
 #pragma unroll 8
-  for (int64_t i = threadIdx.x; i < n; i += 256) q0[f * n + i] -= shift;
+  for (int64_t i = threadIdx.x; i < n; i += FT)
+    q0[f * n + i] = (y ? qs * (double)y[f * n + i] : qchi[i]) - shift;
 }
 
 // x0 = q0 + mu0 d' with mu0 = mean(b - E q0) (Eq = E q0 given in eq)
 // x0 += mu d' with mu = mean(b - E x0) (the Lagrange shift), and when r0 is
 // given also the residual of the shifted start, r0 = (b - E x0) - mu 1
 // (E d' = 1), so that the solver needs no product of its own for it.
-__global__ __launch_bounds__(256) void lagrange_shift_kernel(const double *__restrict__ b,
-                                                             const double *__restrict__ eq,
-                                                             const double *__restrict__ dprime,
-                                                             int64_t n, double *__restrict__ x0,
-                                                             double *__restrict__ r0) {
-  __shared__ double red[256];
+__global__ __launch_bounds__(FT) void lagrange_shift_kernel(const double *__restrict__ b,
+                                                            const double *__restrict__ eq,
+                                                            const double *__restrict__ dprime,
+                                                            int64_t n, double *__restrict__ x0,
+                                                            double *__restrict__ r0) {
   const int64_t f = blockIdx.x;
   double s = 0.0;
 #pragma unroll 8
-  for (int64_t i = threadIdx.x; i < n; i += 256) s += b[f * n + i] - eq[f * n + i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
+  for (int64_t i = threadIdx.x; i < n; i += FT) s += b[f * n + i] - eq[f * n + i];
+  const double mu = frame_sum(s) / (double)n;
+#pragma unroll 4
+  for (int64_t i = threadIdx.x; i < n; i += FT) {
+    x0[f * n + i] += mu * dprime[i];
+    if (r0 != nullptr) r0[f * n + i] = (b[f * n + i] - eq[f * n + i]) - mu;
   }
-  const double mu = red[0] / (double)n;
-  __syncthreads();
-#pragma unroll 8
-  for (int64_t i = threadIdx.x; i < n; i += 256) x0[f * n + i] += mu * dprime[i];
-  if (r0 != nullptr)
-#pragma unroll 8
-    for (int64_t i = threadIdx.x; i < n; i += 256) r0[f * n + i] = (b[f * n + i] - eq[f * n + i]) - mu;
 }
-
 
 // Host 12-neighbour list: order by distance, then azimuth about +z from +x,
 // then index; distance and angle compared after rounding to 1e-6.
@@ -720,7 +712,7 @@ static cpm_status features_impl(cpm_system *s, const double *b, int64_t f,
   const Mlp &M = s->mlp;
   hipStream_t st = s->stream;
   if (compute_mean)
-    hipLaunchKernelGGL(frame_mean_kernel, dim3((unsigned)f), dim3(256), 0, st, b, s->n, mean_buf);
+    hipLaunchKernelGGL(frame_mean_kernel, dim3((unsigned)f), dim3(FT), 0, st, b, s->n, mean_buf);
   const float inv_layers = M.n_layers > 1 ? 1.0f / (float)(M.n_layers - 1) : 0.0f;
   hipLaunchKernelGGL(features_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, b,
                      mean_buf, s->n, M.nbr, M.nbr_r, M.layer, inv_layers, 1.0f / M.b_scale,
@@ -746,7 +738,7 @@ cpm_status warm_start_impl(cpm_system *s, bool use_mlp, const double *b, const d
     cpm_status rc = ensure_rows(s, f * n);
     if (rc != CPM_OK) return rc;
     const Mlp &M = s->mlp;
-    hipLaunchKernelGGL(frame_mean_kernel, dim3((unsigned)f), dim3(256), 0, st, b, n, mean);
+    hipLaunchKernelGGL(frame_mean_kernel, dim3((unsigned)f), dim3(FT), 0, st, b, n, mean);
     const float inv_layers = M.n_layers > 1 ? 1.0f / (float)(M.n_layers - 1) : 0.0f;
     hipLaunchKernelGGL(mlp_infer_kernel<true>, dim3(infer_blocks(f * n)), dim3(TT), 0, st,
                        (const float *)M.params, (const float *)nullptr, b, (const double *)mean, n,
@@ -754,7 +746,7 @@ cpm_status warm_start_impl(cpm_system *s, bool use_mlp, const double *b, const d
                        inv_layers, 1.0f / M.b_scale, 1.0f / M.r_scale, f * n, M.yout);
     y = s->mlp.yout;
   }
-  hipLaunchKernelGGL(neutral_shift_kernel, dim3((unsigned)f), dim3(256), 0, st, y, s->qchi, n,
+  hipLaunchKernelGGL(neutral_shift_kernel, dim3((unsigned)f), dim3(FT), 0, st, y, s->qchi, n,
                      (double)s->mlp.q_scale, qsol, x0);
   // E q0 for the Lagrange shift: FP64 when the start's residual r0 is wanted
   // too (it is then the solver's first residual), else the FP32 copy of E
@@ -762,7 +754,7 @@ cpm_status warm_start_impl(cpm_system *s, bool use_mlp, const double *b, const d
   cpm_status rc =
       matvec_cols(s, (r0 == nullptr && s->E32) ? CPM_PREC_F32 : CPM_PREC_F64, x0, f, eq);
   if (rc == CPM_OK)
-    hipLaunchKernelGGL(lagrange_shift_kernel, dim3((unsigned)f), dim3(256), 0, st, b, eq,
+    hipLaunchKernelGGL(lagrange_shift_kernel, dim3((unsigned)f), dim3(FT), 0, st, b, eq,
                        s->dprime, n, x0, r0);
   CPM_HIP_CHECK(hipGetLastError());
   return rc;
@@ -972,7 +964,7 @@ cpm_status cpm_mlp_train_epoch(cpm_system *s, const double *b_dev, const double 
       return CPM_EINVAL;
     }
   }
-  hipLaunchKernelGGL(frame_mean_kernel, dim3((unsigned)f), dim3(256), 0, st, b_dev, s->n, mean);
+  hipLaunchKernelGGL(frame_mean_kernel, dim3((unsigned)f), dim3(FT), 0, st, b_dev, s->n, mean);
   const double inv_qs = 1.0 / (double)s->mlp.q_scale;
   double *lhist = (double *)aux;
   for (int64_t bi = 0; bi < nb; ++bi) {
