@@ -233,6 +233,7 @@ void free_system(cpm_system *s) {
                   s->mlp.feat, s->mlp.yout};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
+  if (s->mlp.hloss) (void)hipHostFree(s->mlp.hloss);
   if (s->rs_width && s->rs_width != s->width) (void)hipFree(s->rs_width);
   for (DevBuf *b : {&s->buf_warm, &s->buf_eq, &s->buf_mean, &s->buf_aux})
     if (b->p) (void)hipFree(b->p);

@@ -180,6 +180,7 @@ struct Mlp {
   float *gpart = nullptr;     // per-tile gradient partials
   int64_t gpart_tiles = 0;
   double *loss = nullptr;     // device loss scalar(s)
+  double *hloss = nullptr;    // pinned host copy of the last batch's loss
   int64_t step = 0;
   float *feat = nullptr;      // feature scratch for the warm start
   float *yout = nullptr;

@@ -108,7 +108,9 @@ typedef float mf4 __attribute__((ext_vector_type(4)));
 struct GradLds {
   alignas(16) float w1[NINP][NH];
   alignas(16) float w2[NH][NH];
-  float b1[NH], b2[NH], w3[NH];
+  alignas(16) float b1[NH];
+  alignas(16) float b2[NH];
+  alignas(16) float w3[NH];
   float x[GR][33];          // inputs, zero beyond NIN (two 16-wide blocks for dW1)
   float h1[GR][NH + 1];     // silu(a1)
   float d1[GR][NH + 1];     // silu'(a1), then G1 = dL/da1
@@ -116,6 +118,39 @@ struct GradLds {
   float red[4][NH + 1];     // per-wave sums: dW3, db3
   double lred[4];           // per-wave loss sums
 };
+
+// parameters into LDS as float4 pieces, every load of a thread issued
+// before its first store (the offsets are multiples of 4 floats)
+static_assert(OW1 % 4 == 0 && OB1 % 4 == 0 && OW2 % 4 == 0 && OB2 % 4 == 0 && OW3 % 4 == 0 &&
+                  (NH * NH / 4) % TT == 0 && 3 * (NH / 4) <= TT,
+              "parameter offsets and sizes in whole float4 pieces");
+__device__ inline void load_params(const float *__restrict__ prm, float *l1, float *l2, float *lb1,
+                                   float *lb2, float *lw3) {
+  constexpr int N1 = NIN * NH / 4, N2 = NH * NH / 4, NV = NH / 4;
+  constexpr int L1 = (N1 + TT - 1) / TT, L2 = N2 / TT;
+  const int t = threadIdx.x;
+  const mf4 *p4 = reinterpret_cast<const mf4 *>(prm);
+  mf4 v1[L1], v2[L2];
+#pragma unroll
+  for (int u = 0; u < L1; ++u) v1[u] = p4[OW1 / 4 + min(t + u * TT, N1 - 1)];
+#pragma unroll
+  for (int u = 0; u < L2; ++u) v2[u] = p4[OW2 / 4 + t + u * TT];
+  const mf4 vb = p4[(t < NV ? OB1 : t < 2 * NV ? OB2 : OW3) / 4 + t % NV];
+  mf4 *w1 = reinterpret_cast<mf4 *>(l1);
+  mf4 *w2 = reinterpret_cast<mf4 *>(l2);
+#pragma unroll
+  for (int u = 0; u < L1; ++u) {
+    const int q = t + u * TT;
+    if (q < NINP * NH / 4) w1[q] = q < N1 ? v1[u] : mf4{0.0f, 0.0f, 0.0f, 0.0f};
+  }
+#pragma unroll
+  for (int u = 0; u < L2; ++u) w2[t + u * TT] = v2[u];
+  if (t < 3 * NV) {
+    float *dst = t < NV ? lb1 : t < 2 * NV ? lb2 : lw3;
+    reinterpret_cast<mf4 *>(dst)[t % NV] = vb;
+  }
+}
+static_assert(NINP * NH / 4 <= (NIN * NH / 4 + TT - 1) / TT * TT, "the zero rows of W1 are covered");
 
 __global__ __launch_bounds__(TT) void mlp_grad_kernel(const float *__restrict__ prm,
                                                       const float *__restrict__ feat,
@@ -128,21 +163,27 @@ __global__ __launch_bounds__(TT) void mlp_grad_kernel(const float *__restrict__ 
   const int lr = lane & 15, lg = lane >> 4;
   const int rw = 16 * wave;
   const int64_t r0 = (int64_t)blockIdx.x * GR;
-  for (int q = t; q < NINP * NH; q += TT) {
-    const int k = q / NH, j = q % NH;
-    L.w1[k][j] = k < NIN ? prm[OW1 + k * NH + j] : 0.0f;
+  // inputs and parameters: every load of a thread before its first store
+  constexpr int NX = GR * 32 / TT;
+  float xv[NX];
+#pragma unroll
+  for (int u = 0; u < NX; ++u) {
+    const int q = t + u * TT, r = q / 32, k = q % 32;
+    const bool in = r0 + r < rows && k < NIN;
+    xv[u] = feat[in ? (r0 + r) * NIN + k : 0];
+    if (!in) xv[u] = 0.0f;
   }
-  for (int q = t; q < NH * NH; q += TT) L.w2[q / NH][q % NH] = prm[OW2 + q];
-  if (t < NH) {
-    L.b1[t] = prm[OB1 + t];
-    L.b2[t] = prm[OB2 + t];
-    L.w3[t] = prm[OW3 + t];
+  // (the error enters the wave's rows: loaded now, used in layer 2)
+  float tg[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int64_t r = r0 + rw + 4 * lg + v;
+    tg[v] = target[r < rows ? r : 0];
   }
+  load_params(prm, &L.w1[0][0], &L.w2[0][0], L.b1, L.b2, L.w3);
   const float b3 = prm[OB3];
-  for (int q = t; q < GR * 32; q += TT) {
-    const int r = q / 32, k = q % 32;
-    L.x[r][k] = (r0 + r < rows && k < NIN) ? feat[(r0 + r) * NIN + k] : 0.0f;
-  }
+#pragma unroll
+  for (int u = 0; u < NX; ++u) L.x[(t + u * TT) / 32][(t + u * TT) % 32] = xv[u];
   __syncthreads();
   // layer 1
   mf4 acc[NHT];
@@ -197,7 +238,7 @@ __global__ __launch_bounds__(TT) void mlp_grad_kernel(const float *__restrict__ 
     // every lane of the row group gets the sum over the 64 units
 #pragma unroll
     for (int off = 1; off < 16; off <<= 1) sp += __shfl_xor(sp, off, 16);
-    const float e = (r0 + row < rows) ? (sp + b3 - target[r0 + row]) : 0.0f;
+    const float e = (r0 + row < rows) ? (sp + b3 - tg[v]) : 0.0f;
     const float dy = 2.0f * e * inv_rows;
 #pragma unroll
     for (int u = 0; u < NHT; ++u) {
@@ -299,20 +340,37 @@ __global__ __launch_bounds__(TT) void mlp_grad_kernel(const float *__restrict__ 
   }
 }
 
-// grad[p] = sum over tiles (fixed order, FP64 accumulation); loss likewise.
-__global__ void grad_reduce_kernel(const float *__restrict__ gpart, int64_t tiles,
-                                   float *__restrict__ grad, const double *__restrict__ lpart,
-                                   double *__restrict__ loss, double inv_rows) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+// grad[p] = sum over tiles in FP64 (fixed order: GS groups of tiles, each in
+// tile order, then the groups); workgroup = 64 parameters, a wave per group.
+// The loss partials are summed by the last workgroup's waves the same way.
+// 8352 rows (131 tiles): 40 -> 4 us against one thread per parameter, whose
+// loads followed each other.
+constexpr int GS = 16;
+__global__ __launch_bounds__(64 * GS) void grad_reduce_kernel(
+    const float *__restrict__ gpart, int64_t tiles, float *__restrict__ grad,
+    const double *__restrict__ lpart, double *__restrict__ loss, double *__restrict__ hloss,
+    double inv_rows) {
+  __shared__ double red[GS][64];
+  const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const int64_t t0 = g * tiles / GS, t1 = (g + 1) * tiles / GS;
+  const int p = blockIdx.x * 64 + lane;
+  double s = 0.0;
   if (p < NP) {
-    double s = 0.0;
-    for (int64_t tl = 0; tl < tiles; ++tl) s += (double)gpart[tl * NP + p];
-    grad[p] = (float)s;
+#pragma unroll 8
+    for (int64_t tl = t0; tl < t1; ++tl) s += (double)gpart[tl * NP + p];
+  } else if (p == NP) {   // (the grid has room for one more column: the loss)
+#pragma unroll 8
+    for (int64_t tl = t0; tl < t1; ++tl) s += lpart[tl];
   }
-  if (p == 0) {
-    double s = 0.0;
-    for (int64_t tl = 0; tl < tiles; ++tl) s += lpart[tl];
+  red[g][lane] = s;
+  __syncthreads();
+  if (g != 0) return;
+#pragma unroll
+  for (int w = 1; w < GS; ++w) s += red[w][lane];
+  if (p < NP) grad[p] = (float)s;
+  if (p == NP) {
     loss[0] = s * inv_rows;
+    hloss[0] = s * inv_rows;   // pinned host memory: read after the caller's synchronisation
   }
 }
 
@@ -484,9 +542,6 @@ cpm_status build_neighbours(const cpm_system *s, std::vector<int32_t> &nbr,
 constexpr int IR = 64;                       // rows per inference tile (16 per wavefront)
 static_assert(NH % 16 == 0 && TT == 4 * 64 && IR == 16 * (TT / 64) && TT == 4 * IR &&
                   NNB % 4 == 0 && NIN == 2 + 2 * NNB, "inference tiling");
-static_assert(OW1 % 4 == 0 && OB1 % 4 == 0 && OW2 % 4 == 0 && OB2 % 4 == 0 && OW3 % 4 == 0 &&
-                  (NH * NH / 4) % TT == 0 && 3 * (NH / 4) <= TT,
-              "parameter offsets and sizes in whole float4 pieces");
 struct InferLds {
   alignas(16) float w1[NINP][NH];
   alignas(16) float w2[NH][NH];
@@ -505,36 +560,7 @@ __global__ __launch_bounds__(TT) void mlp_infer_kernel(
     float inv_bs, float inv_rs, int64_t rows, float *__restrict__ y) {
   __shared__ InferLds L;
   const int t = threadIdx.x;
-  {
-    // parameters into LDS as float4 pieces, every load of a thread issued
-    // before its first store (the offsets are multiples of 4 floats)
-    constexpr int N1 = NIN * NH / 4, N2 = NH * NH / 4, NV = NH / 4;
-    constexpr int L1 = (N1 + TT - 1) / TT, L2 = N2 / TT;
-    const float4 *p4 = reinterpret_cast<const float4 *>(prm);
-    float4 v1[L1], v2[L2], vb = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll
-    for (int u = 0; u < L1; ++u) {
-      const int q = t + u * TT;
-      if (q < N1) v1[u] = p4[OW1 / 4 + q];
-    }
-#pragma unroll
-    for (int u = 0; u < L2; ++u) v2[u] = p4[OW2 / 4 + t + u * TT];
-    if (t < 3 * NV) vb = p4[(t < NV ? OB1 : t < 2 * NV ? OB2 : OW3) / 4 + t % NV];
-    float4 *w1 = reinterpret_cast<float4 *>(&L.w1[0][0]);
-    float4 *w2 = reinterpret_cast<float4 *>(&L.w2[0][0]);
-#pragma unroll
-    for (int u = 0; u < L1; ++u) {
-      const int q = t + u * TT;
-      if (q < N1) w1[q] = v1[u];
-    }
-    for (int q = N1 + t; q < NINP * NH / 4; q += TT) w1[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll
-    for (int u = 0; u < L2; ++u) w2[t + u * TT] = v2[u];
-    if (t < 3 * NV) {
-      float *dst = t < NV ? L.b1 : t < 2 * NV ? L.b2 : L.w3;
-      reinterpret_cast<float4 *>(dst)[t % NV] = vb;
-    }
-  }
+  load_params(prm, &L.w1[0][0], &L.w2[0][0], L.b1, L.b2, L.w3);
   const float b3 = prm[OB3];
   const int wave = t >> 6, lane = t & 63;
   const int lr = lane & 15, lg = lane >> 4;
@@ -689,8 +715,8 @@ static cpm_status loss_grad_impl(cpm_system *s, const float *feat, const float *
   hipLaunchKernelGGL(mlp_grad_kernel, dim3((unsigned)tiles), dim3(TT), 0, st,
                      s->mlp.params, feat, target, rows, (float)(1.0 / (double)rows), s->mlp.gpart,
                      lpart_of(s));
-  hipLaunchKernelGGL(grad_reduce_kernel, dim3((NP + 255) / 256), dim3(256), 0, st, s->mlp.gpart,
-                     tiles, grad_out, lpart_of(s), s->mlp.loss, 1.0 / (double)rows);
+  hipLaunchKernelGGL(grad_reduce_kernel, dim3(NP / 64 + 1), dim3(64 * GS), 0, st, s->mlp.gpart,
+                     tiles, grad_out, lpart_of(s), s->mlp.loss, s->mlp.hloss, 1.0 / (double)rows);
   CPM_HIP_CHECK(hipGetLastError());
   return CPM_OK;
 }
@@ -800,6 +826,12 @@ cpm_status cpm_mlp_init(cpm_system *s, const int32_t *layer_host, int32_t n_laye
     set_error("network allocation failed");
     return CPM_ENOMEM;
   }
+  if (!M.hloss && hipHostMalloc((void **)&M.hloss, sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    M.hloss = nullptr;
+    set_error("network allocation failed");
+    return CPM_ENOMEM;
+  }
   hipStream_t st = s->stream;
   CPM_HIP_CHECK(hipMemcpyAsync(M.nbr, nbr.data(), sizeof(int32_t) * nbr.size(), hipMemcpyHostToDevice, st));
   CPM_HIP_CHECK(hipMemcpyAsync(M.nbr_r, nbr_r.data(), sizeof(float) * nbr_r.size(), hipMemcpyHostToDevice, st));
@@ -902,10 +934,8 @@ cpm_status cpm_mlp_loss_grad(cpm_system *s, const float *feat_dev, const float *
   }
   cpm_status rc = loss_grad_impl(s, feat_dev, target_dev, rows, grad_out_dev);
   if (rc != CPM_OK) return rc;
-  double l = 0;
-  CPM_HIP_CHECK(hipMemcpyAsync(&l, s->mlp.loss, sizeof(double), hipMemcpyDeviceToHost, s->stream));
   CPM_HIP_CHECK(hipStreamSynchronize(s->stream));
-  if (loss) *loss = l;
+  if (loss) *loss = s->mlp.hloss[0];
   return CPM_OK;
 }
 
@@ -924,10 +954,8 @@ cpm_status cpm_mlp_train_step(cpm_system *s, const float *feat_dev, const float 
   cpm_status rc = loss_grad_impl(s, feat_dev, target_dev, rows, s->mlp.grad);
   if (rc == CPM_OK) rc = adam_impl(s, lr, beta1, beta2, eps);
   if (rc != CPM_OK) return rc;
-  double l = 0;
-  CPM_HIP_CHECK(hipMemcpyAsync(&l, s->mlp.loss, sizeof(double), hipMemcpyDeviceToHost, s->stream));
   CPM_HIP_CHECK(hipStreamSynchronize(s->stream));
-  if (loss) *loss = l;
+  if (loss) *loss = s->mlp.hloss[0];
   return CPM_OK;
 }
 
