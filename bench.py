@@ -37,16 +37,16 @@ FP64_PEAK_TFLOPS = 78.6
 CALIB_BYTES = 1 << 30
 K_E = 14.3996454784   # V*A/e: cpm_rhs divides chi by it, so 1 V is 1/K_E in b units
 # 16 columns run on the row-split kernel
-KERNEL_OF_KIND = {"matvec_f64": "block_matvec_rows_kernel<double>",
-                  "matvec_f32": "block_matvec_rows_kernel<float>",
-                  "matvec_bf16": "block_matvec_rows_kernel<unsigned short>"}
+KERNEL_OF_KIND = {"matvec_f64": "block_matvec_rows_kernel<double, 8>",
+                  "matvec_f32": "block_matvec_rows_kernel<float, 8>",
+                  "matvec_bf16": "block_matvec_rows_kernel<unsigned short, 8>"}
 # 32..64 columns of an FP32 / BF16 E run on the split-bf16 kernel
-KERNEL_OF_KIND_WIDE = {"matvec_f64": "block_matvec_f64s_kernel<{ng}>",
+KERNEL_OF_KIND_WIDE = {"matvec_f64": "block_matvec_f64s_kernel<{ng}, false>",
                        "matvec_f32": "block_matvec_split_kernel<float, {ng}>",
                        "matvec_bf16": "block_matvec_split_kernel<unsigned short, {ng}>"}
 
 
-# the ion structure factors of the right-hand side (|n_z| <= 47: every workload here)
+# the ion structure factors of the right-hand side where they are a direct product (|n_z| <= 47)
 SF_KERNEL = "sf_gemm_kernel"
 
 
@@ -580,6 +580,9 @@ def main():
              "kernel_share_of_step": PROFILE_STRIDE * prof[k]["ms"] / (elapsed * 1e3)}
         if k == 4:
             achieved = work / (avg_ms * 1e-3) / 1e12
+            if abs(work - 4.0 * desc["n_kvec"] * t_ipos.shape[1] * nf) > 1e-6 * work:
+                # structure factors through a grid: its own flops and kernels
+                r.update({"kernel": "nu_spread_kernel, nu_dftz/y/x_kernel", "traffic": None})
             r.update({"bound": "mfma", "achieved": achieved, "peak": FP64_PEAK_TFLOPS,
                       "unit": "TFLOP/s", "frac": achieved / FP64_PEAK_TFLOPS,
                       "flops_per_launch": work})

@@ -440,7 +440,10 @@ cpm_status cpm_warm_start(cpm_system *s, int warm_start, const double *b_dev,
  *           s = 8/4/2 for FP64/FP32/BF16 E, s_v = 8 (FP64) or 4 (FP32 vectors);
  *   assembly: flops 4 * n_k * n (n + 1) / 2 for a chunk of n_k k-vectors;
  *   structure factors: flops 4 * n_k * m * f (one complex multiply-add of
- *           q e^{iK.r} per k-vector, ion and frame) for f frames of m ions.
+ *           q e^{iK.r} per k-vector, ion and frame) for f frames of m ions;
+ *           where they go through a grid (many ions and vectors), that path's
+ *           own: 65536 per ion (16^3 grid points, 8 tiles) and the dense
+ *           transforms along z, y and x, for its kernels from first to last.
  * cpm_profile_enable(s, on) starts a new window (clears earlier records):
  * on = 0 stops timing, on = 1 times every launch, on = k > 1 times every
  * k-th launch of each kind (the bracketing

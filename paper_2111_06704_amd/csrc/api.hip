@@ -234,6 +234,8 @@ void free_system(cpm_system *s) {
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   if (s->mlp.hloss) (void)hipHostFree(s->mlp.hloss);
+  if (s->nu.tab) (void)hipFree(s->nu.tab);
+  if (s->nu.col) (void)hipFree(s->nu.col);
   if (s->rs_width && s->rs_width != s->width) (void)hipFree(s->rs_width);
   for (DevBuf *b : {&s->buf_warm, &s->buf_eq, &s->buf_mean, &s->buf_aux})
     if (b->p) (void)hipFree(b->p);
@@ -396,6 +398,7 @@ cpm_status cpm_build_E(const double *pos_host, int64_t n, const double *box_host
   s->rcut = params->rcut;
   s->kmax = kmax;
   s->kset = make_kset(box_host, beta, kmax);
+  nu_sizes(s);
   s->slab = params->slab_correction != 0;
   s->point_self = point_self;
   s->prof.enabled = (params->store_mask & CPM_PROFILE_BUILD) != 0;
@@ -615,8 +618,18 @@ cpm_status cpm_rhs(cpm_system *s, const double *ion_pos_dev, const double *ion_q
   }
   const int64_t fchunk = 1024;
   // scratch for the largest of the chunk sizes used (full chunks and the tail)
-  int64_t need = rhs_scratch_elems(s, m, std::min(f, fchunk));
-  if (f > fchunk && f % fchunk) need = std::max(need, rhs_scratch_elems(s, m, f % fchunk));
+  const int64_t tail = f > fchunk ? f % fchunk : 0;
+  if (rhs_uses_grid(s, m, std::min(f, fchunk)) || (tail && rhs_uses_grid(s, m, tail))) {
+    // no room for the tables: the direct product, as for the scratch below
+    cpm_status rc = ensure_nu(s);
+    if (rc == CPM_ENOMEM) s->nu.off = true;
+    else if (rc != CPM_OK) return rc;
+  }
+  auto scratch = [&]() {
+    const int64_t e = rhs_scratch_elems(s, m, std::min(f, fchunk));
+    return tail ? std::max(e, rhs_scratch_elems(s, m, tail)) : e;
+  };
+  int64_t need = scratch();
   if (s->rhs_S_elems < need) {
     if (s->rhs_S) {
       (void)hipFree(s->rhs_S);
@@ -625,6 +638,12 @@ cpm_status cpm_rhs(cpm_system *s, const double *ion_pos_dev, const double *ion_q
       s->rhs_S_elems = 0;
     }
     cpm_status rc = dev_alloc(s, &s->rhs_S, need);
+    if (rc == CPM_ENOMEM && !s->nu.off) {
+      // the grid path's scratch is the larger one: try without it
+      s->nu.off = true;
+      need = scratch();
+      rc = dev_alloc(s, &s->rhs_S, need);
+    }
     if (rc != CPM_OK) return rc;
     s->rhs_S_elems = need;
   }

@@ -157,6 +157,19 @@ constexpr int64_t kMaxCoarse = 8192;  // most patches (E_c^-1: 512 MB)
 constexpr double kSlabGap = 1.0;      // z gap (A) that starts a new slab
 void free_coarse(Coarse &c);
 
+// Structure factors through a grid (rhs.hip): grid points g and largest mode
+// m per box edge, and the tables on the device (built on first use)
+struct NuGrid {
+  int g[3] = {0, 0, 0}, m[3] = {0, 0, 0};
+  int zrows = 0, zpasses = 1, passes[2] = {1, 1};   // padded rows and passes of the transforms
+  double *tab = nullptr;        // the allocation behind mat, coef and inv
+  const double *mat[3] = {nullptr, nullptr, nullptr};
+  double *coef = nullptr;       // window polynomials
+  const double *inv = nullptr;  // 1 / Phi per axis
+  int2 *col = nullptr;          // (k index of n_z = 0, largest |n_z|) by (n_x, n_y)
+  bool off = false;             // no room for the scratch: the direct product
+};
+
 struct Gcd {                 // capacitance coefficients (Supplementary Eq. S22-S24)
   bool ready = false;
   int m = 0;                  // electrodes
@@ -265,6 +278,7 @@ struct cpm_system {
   double *S = nullptr;        // ld*ld: S = E^-1 (I - 1 d^T) of the MI path (Eq. 33), or null
   bool qchi_ready = false;
   double *rhs_S = nullptr;    // structure-factor scratch
+  cpm::NuGrid nu;
   int64_t rhs_S_elems = 0;
   std::vector<double> pos_host;   // n*3 wrapped positions (host copy)
   cpm::Workspace ws;
@@ -318,6 +332,10 @@ constexpr int kErfcTerms = 12;
 constexpr int kErfcTab = kErfcIntervals * kErfcTerms;
 void erfc_table(double *out);
 int64_t rhs_scratch_elems(const cpm_system *s, int64_t m, int64_t f);
+// sizes of the grid path (system set-up), whether this call takes it, its tables
+void nu_sizes(cpm_system *s);
+bool rhs_uses_grid(const cpm_system *s, int64_t m, int64_t f);
+cpm_status ensure_nu(cpm_system *s);
 // scratch of the plan limited to limit doubles (fewer partial buffers), and
 // the static scratch of cpm_rhs_noalloc: its size and this device's address
 int64_t rhs_scratch_elems_capped(const cpm_system *s, int64_t m, int64_t f, int64_t limit);
