@@ -325,10 +325,12 @@ hipError_t launch_finalize(hipStream_t st, const double *pos, const double *widt
                            uint16_t *E16);
 
 // ---- rhs.hip
-// erfc on [0, 6.5): kErfcIntervals intervals of width 1/8, kErfcTerms
-// Taylor coefficients each (about the midpoint, in units of the width)
-constexpr int kErfcIntervals = 52;
-constexpr int kErfcTerms = 12;
+// erfc on [0, 6.5): kErfcIntervals intervals of width 1 / kErfcPer, a
+// polynomial of kErfcTerms coefficients each (about the midpoint, in units
+// of the width)
+constexpr int kErfcPer = 16;
+constexpr int kErfcIntervals = 104;
+constexpr int kErfcTerms = 9;
 constexpr int kErfcTab = kErfcIntervals * kErfcTerms;
 void erfc_table(double *out);
 int64_t rhs_scratch_elems(const cpm_system *s, int64_t m, int64_t f);

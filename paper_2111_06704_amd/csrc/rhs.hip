@@ -31,22 +31,22 @@ constexpr int FG = 16;        // frames per thread in the back-projection
 constexpr int BP_AT = 2;      // atoms per thread in the back-projection
 constexpr int BP_KCH = 32;    // k-vectors per LDS chunk in the back-projection
 constexpr double kErfcZero = 6.5;   // erfc(x) < 4e-20 beyond: below any FP64 sum it enters
-static_assert(kErfcIntervals == 8 * 6.5, "erfc table intervals of width 1/8 up to kErfcZero");
+static_assert(kErfcIntervals == kErfcPer * 6.5, "erfc table intervals up to kErfcZero");
 
 // erfc(x) for 0 <= x from the table (0 for x >= kErfcZero): interval j =
-// floor(8 x), u = 8 x - (j + 1/2) in [-1/2, 1/2), Horner over the Taylor
-// coefficients c_jk = f^(k)(x_j) / (8^k k!). Every lane runs the same
-// instructions (no range branches); absolute error below 3e-16.
-__device__ inline double erfc_pw(const double *__restrict__ tab, double x) {
-  if (!(x < kErfcZero)) return 0.0;
-  const double s = 8.0 * x;
-  const int j = (int)s;
+// floor(16 x), u = 16 x - (j + 1/2) in [-1/2, 1/2), Horner. Every lane runs
+// the same instructions (no range branches); absolute error below 1.2e-16
+// (twelve Taylor terms on intervals of 1/8: 1.2e-16 too, a third more reads).
+// Rows of nine doubles start in all banks of LDS.
+__device__ inline double erfc_pw(const double *tab, double x) {
+  const double s = kErfcPer * fmin(x, kErfcZero);
+  const int j = min((int)s, kErfcIntervals - 1);
   const double u = s - ((double)j + 0.5);
   const double *c = tab + j * kErfcTerms;
-  double p = c[kErfcTerms - 1];
+  double v = c[kErfcTerms - 1];
 #pragma unroll
-  for (int k = kErfcTerms - 2; k >= 0; --k) p = fma(p, u, c[k]);
-  return p;
+  for (int k = kErfcTerms - 2; k >= 0; --k) v = fma(v, u, c[k]);
+  return x < kErfcZero ? v : 0.0;
 }
 
 __global__ void fill_zero_kernel(double *__restrict__ v, int64_t len) {
@@ -1002,106 +1002,6 @@ __global__ void assemble_b_kernel(const double *__restrict__ bp, int ksplits,
   b[idx] = v;
 }
 
-// Images of a displacement d (already reduced to the minimum image) along
-// one box edge L with |d + m L| < rcut: m in [lo, hi]. When L >= 2 rcut only
-// m = 0 can qualify.
-__device__ inline void image_range(double d, double L, double invL, double rcut, bool wide,
-                                   int &lo, int &hi) {
-  if (wide) {
-    lo = 0;
-    hi = (fabs(d) < rcut) ? 0 : -1;
-  } else {
-    lo = (int)ceil((-rcut - d) * invL);
-    hi = (int)floor((rcut - d) * invL);
-  }
-}
-
-// One thread per (electrode atom, frame, ion group); ions stream through LDS.
-// rs[g][f][i] = sum_{I in group g} q_I sum_images [erfc(beta d) - erfc(a_i d)] / d.
-// Thread t takes atom order[t] (compact spatial tiles), so a wavefront's
-// atoms are close together and the branch into the erfc terms is taken by
-// all lanes or none for most ions.
-__global__ __launch_bounds__(RB) void real_space_ions_kernel(
-    const double *__restrict__ pos, const double *__restrict__ width,
-    const int32_t *__restrict__ order, int64_t n, const double *__restrict__ ion_pos,
-    const double *__restrict__ ion_q, int64_t m, int64_t ipg, double lx, double ly, double lz,
-    double beta, double rcut, int64_t f_total, const double *__restrict__ etab,
-    double *__restrict__ rs) {
-  __shared__ double si[RB][4];
-  __shared__ double et[kErfcTab];
-  for (int q = threadIdx.x; q < kErfcTab; q += RB) et[q] = etab[q];
-  __syncthreads();
-  const int64_t f = blockIdx.y, g = blockIdx.z;
-  const int64_t t = (int64_t)blockIdx.x * RB + threadIdx.x;
-  const int64_t i = t < n ? (int64_t)order[t] : -1;
-  double xi = 0, yi = 0, zi = 0, ai = 1.0;
-  if (i >= 0) {
-    xi = pos[3 * i];
-    yi = pos[3 * i + 1];
-    zi = pos[3 * i + 2];
-    ai = width[i];
-  }
-  const double ilx = 1.0 / lx, ily = 1.0 / ly, ilz = 1.0 / lz;
-  const bool wx = lx >= 2.0 * rcut, wy = ly >= 2.0 * rcut, wz = lz >= 2.0 * rcut;
-  const double rc2 = rcut * rcut;
-  // limit of [erfc(beta d) - erfc(a d)] / d at d -> 0
-  const double lim0 = 2.0 * (ai - beta) * 0.56418958354775628695;
-  double acc = 0.0;
-  const double *pf = ion_pos + f * m * 3;
-  const double *qf = ion_q + f * m;
-  const int64_t i0 = g * ipg, i1 = min(m, i0 + ipg);
-  for (int64_t base = i0; base < i1; base += RB) {
-    const int64_t I = base + threadIdx.x;
-    if (I < i1) {
-      si[threadIdx.x][0] = pf[3 * I];
-      si[threadIdx.x][1] = pf[3 * I + 1];
-      si[threadIdx.x][2] = pf[3 * I + 2];
-      si[threadIdx.x][3] = qf[I];
-    }
-    __syncthreads();
-    const int cnt = (int)((i1 - base) < RB ? (i1 - base) : RB);
-    if (i >= 0) {
-      for (int j = 0; j < cnt; ++j) {
-        double dz = zi - si[j][2];
-        dz -= lz * rint(dz * ilz);
-        int za, zb;
-        image_range(dz, lz, ilz, rcut, wz, za, zb);
-        if (za > zb) continue;
-        double dx = xi - si[j][0];
-        double dy = yi - si[j][1];
-        dx -= lx * rint(dx * ilx);
-        dy -= ly * rint(dy * ily);
-        int xa, xb, ya, yb;
-        image_range(dx, lx, ilx, rcut, wx, xa, xb);
-        image_range(dy, ly, ily, rcut, wy, ya, yb);
-        const double q = si[j][3];
-        for (int a = xa; a <= xb; ++a) {
-          const double ex = dx + (double)a * lx;
-          for (int bb = ya; bb <= yb; ++bb) {
-            const double ey = dy + (double)bb * ly;
-            const double exy = ex * ex + ey * ey;
-            if (exy >= rc2) continue;
-            for (int c = za; c <= zb; ++c) {
-              const double ez = dz + (double)c * lz;
-              const double d2 = exy + ez * ez;
-              if (d2 < rc2) {
-                if (d2 > 0.0) {
-                  const double d = sqrt(d2);
-                  acc += q * ((erfc_pw(et, beta * d) - erfc_pw(et, ai * d)) / d);
-                } else {
-                  acc += q * lim0;
-                }
-              }
-            }
-          }
-        }
-      }
-    }
-    __syncthreads();
-  }
-  if (i >= 0) rs[(g * f_total + f) * n + i] = acc;
-}
-
 // ---- real space over a cell list of the ions of each frame
 //
 // The box is cut into ncx x ncy x ncz cells (edges h_d = L_d / nc_d >=
@@ -1115,7 +1015,7 @@ __global__ __launch_bounds__(RB) void real_space_ions_kernel(
 //                           chunks (per cell) and over the cells
 //   cell_scatter_kernel     every ion to cell start + earlier chunks' count +
 //                           its rank in its chunk, as (x, y, z, q)
-// real_space_cell_kernel then gives each wavefront of 64 spatially compact
+// real_space_kernel<true> then gives each wavefront of 64 spatially compact
 // atoms the cells that overlap its bounding box widened by rcut: one
 // contiguous range of the sorted ions per (cz, cy) row (two where the x
 // range wraps), so the sum runs in a fixed order.
@@ -1279,20 +1179,43 @@ __device__ inline int wrap_cell(int c, int nc) {
   return c < 0 ? c + nc : c;
 }
 
-__global__ __launch_bounds__(64) void real_space_cell_kernel(
+// rs[g][f][i] = sum over the ions of group g (with the cell list: over the
+// ions in its rows of cells) of q sum_images [erfc(beta d) - erfc(a_i d)] / d,
+// d < rcut. One wave per 64 spatially compact atoms order[..], frame and
+// group. The wave looks at 64 ions at a time, one per lane: every periodic
+// image within rcut of the tile's bounding box goes to a list in LDS (ballot,
+// in order), and each listed image is then paired with the 64 atoms by three
+// subtractions; a box narrower than the widened tile only lists an ion more
+// than once. Four waves share the table of erfc, so that LDS holds as many
+// waves as the registers (with a table per wave the largest case below takes
+// 750 us). Bound by the FP64 vector unit and the reads of the table (55 and
+// 50 % of the time, half the lanes within rcut). Measured, before (each pair
+// with its own minimum image, an atom per thread against groups of 256 ions;
+// with the cell list all ions of the cells) and now: 4608 atoms, 2000 ions,
+// 1 frame 64 and 12 us, 16 frames 125 and 48 us; 288 atoms, 200 ions, 1 frame
+// 131 and 15 us; 8192 atoms, 32 frames of 50000 ions 1890 and 600 us.
+constexpr int RS_W = 4;   // waves per workgroup, which share the table
+// LDS written by this wave before is read by it after (its accesses are in order)
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+template <bool CELL>
+__global__ __launch_bounds__(64 * RS_W) void real_space_kernel(
     const double *__restrict__ pos, const double *__restrict__ width,
-    const int32_t *__restrict__ order, int64_t n, const double4 *__restrict__ sorted,
+    const int32_t *__restrict__ order, int64_t n, const double *__restrict__ ion_pos,
+    const double *__restrict__ ion_q, int64_t ipg, const double4 *__restrict__ sorted,
     const int32_t *__restrict__ cstart, int64_t m, int ncx, int ncy, int ncz, double lx,
     double ly, double lz, double beta, double rcut, int64_t f_total,
     const double *__restrict__ etab, double *__restrict__ rs) {
-  __shared__ double4 si[64];
+  __shared__ double4 lists[RS_W][128];
   __shared__ double et[kErfcTab];
-  for (int q = threadIdx.x; q < kErfcTab; q += 64) et[q] = etab[q];
-  __syncthreads();
-  const int64_t f = blockIdx.y;
-  const int lane = threadIdx.x;
-  const int64_t t = (int64_t)blockIdx.x * 64 + lane;
+  const int64_t f = blockIdx.y, grp = blockIdx.z;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double4 *lst = lists[wave];
+  const int64_t t = ((int64_t)blockIdx.x * RS_W + wave) * 64 + lane;
   const int64_t i = t < n ? (int64_t)order[t] : -1;
+  for (int q = threadIdx.x; q < kErfcTab; q += 64 * RS_W) et[q] = etab[q];
   double xi = 0, yi = 0, zi = 0, ai = 1.0;
   if (i >= 0) {
     xi = pos[3 * i];
@@ -1301,15 +1224,14 @@ __global__ __launch_bounds__(64) void real_space_cell_kernel(
     ai = width[i];
   }
   const double ilx = 1.0 / lx, ily = 1.0 / ly, ilz = 1.0 / lz;
-  const bool wx = lx >= 2.0 * rcut, wy = ly >= 2.0 * rcut, wz = lz >= 2.0 * rcut;
-  // bounding box of the tile about its first atom (lane 0 always holds one)
+  // the images of the tile's atoms next to its first (lane 0 always holds
+  // one) and their bounding box
   const double xr = __shfl(xi, 0, 64), yr = __shfl(yi, 0, 64), zr = __shfl(zi, 0, 64);
-  double ex0 = xi - xr, ey0 = yi - yr, ez0 = zi - zr;
-  ex0 -= lx * rint(ex0 * ilx);
-  ey0 -= ly * rint(ey0 * ily);
-  ez0 -= lz * rint(ez0 * ilz);
-  if (i < 0) ex0 = ey0 = ez0 = 0.0;
-  double xmin = ex0, xmax = ex0, ymin = ey0, ymax = ey0, zmin = ez0, zmax = ez0;
+  xi -= lx * rint((xi - xr) * ilx);
+  yi -= ly * rint((yi - yr) * ily);
+  zi -= lz * rint((zi - zr) * ilz);
+  if (i < 0) xi = xr, yi = yr, zi = zr;
+  double xmin = xi, xmax = xi, ymin = yi, ymax = yi, zmin = zi, zmax = zi;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     xmin = fmin(xmin, __shfl_xor(xmin, o, 64));
@@ -1319,83 +1241,101 @@ __global__ __launch_bounds__(64) void real_space_cell_kernel(
     zmin = fmin(zmin, __shfl_xor(zmin, o, 64));
     zmax = fmax(zmax, __shfl_xor(zmax, o, 64));
   }
-  // cells meeting the box widened by rcut (and a hair for rounding at cell
-  // edges; the distance test below is exact)
+  // its centre, half its edges and these widened by rcut (and a hair for
+  // rounding; the distance test below is exact), and the most images an ion
+  // can have inside
   const double rw = rcut * (1.0 + 1e-9) + 1e-9;
-  int xa, xb, ya, yb, za, zb;
-  cell_span(xr + xmin - rw, xr + xmax + rw, ncx * ilx, ncx, xa, xb);
-  cell_span(yr + ymin - rw, yr + ymax + rw, ncy * ily, ncy, ya, yb);
-  cell_span(zr + zmin - rw, zr + zmax + rw, ncz * ilz, ncz, za, zb);
-  const int32_t *cs = cstart + f * ((int64_t)ncx * ncy * ncz + 1);
-  const double4 *sf = sorted + f * m;
+  const double cx = 0.5 * (xmin + xmax), cy = 0.5 * (ymin + ymax), cz = 0.5 * (zmin + zmax);
+  const double bx = 0.5 * (xmax - xmin), by = 0.5 * (ymax - ymin), bz = 0.5 * (zmax - zmin);
+  const double hx = bx + rw, hy = by + rw, hz = bz + rw;
+  const int ma = (int)(2.0 * hx * ilx) + 1, mb = (int)(2.0 * hy * ily) + 1,
+            mc = (int)(2.0 * hz * ilz) + 1;
   const double rc2 = rcut * rcut;
   const double lim0 = 2.0 * (ai - beta) * 0.56418958354775628695;
-  const int xlen = xb - xa + 1, xw0 = wrap_cell(xa, ncx);
   double acc = 0.0;
-  for (int cz = za; cz <= zb; ++cz) {
-    const int czw = wrap_cell(cz, ncz);
-    for (int cy = ya; cy <= yb; ++cy) {
-      const int64_t row = ((int64_t)czw * ncy + wrap_cell(cy, ncy)) * ncx;
-      for (int part = 0; part < 2; ++part) {
-        int c0, c1;   // cells [c0, c1) of the row
-        if (part == 0) {
-          c0 = xw0;
-          c1 = min(ncx, xw0 + xlen);
-        } else {
-          c0 = 0;
-          c1 = xw0 + xlen - ncx;
-          if (c1 <= 0) break;
+  auto process = [&](int cnt) {   // the first cnt listed images
+    for (int j = 0; j < cnt; ++j) {
+      const double4 ion = lst[j];
+      const double dx = xi - ion.x, dy = yi - ion.y, dz = zi - ion.z;
+      const double d2 = fma(dz, dz, fma(dy, dy, dx * dx));
+      if (!(d2 < rc2)) continue;
+      // 1 / d by one third-order step from the hardware estimate
+      const double e2 = d2 > 0.0 ? d2 : 1.0;
+      const double y0 = __builtin_amdgcn_rsq(e2), e = fma(-e2 * y0, y0, 1.0);
+      const double y = fma(y0 * e, fma(0.375, e, 0.5), y0), d = e2 * y;
+      double v = erfc_pw(et, beta * d);
+      if (ai * d < kErfcZero) v -= erfc_pw(et, ai * d);
+      acc += ion.w * (d2 > 0.0 ? v * y : lim0);
+    }
+  };
+  int cnt = 0;
+  auto push = [&](double4 ion, bool in) {   // full lists of 64 are processed
+    const uint64_t mask = __ballot(in);
+    if (in) lst[cnt + __popcll(mask & ((1ull << lane) - 1))] = ion;
+    cnt += __popcll(mask);
+    if (cnt < 64) return;
+    wave_sync();
+    process(64);
+    wave_sync();
+    cnt -= 64;
+    const double4 rest = lst[64 + lane];
+    wave_sync();
+    if (lane < cnt) lst[lane] = rest;
+  };
+  auto offer = [&](double4 ion, bool valid) {   // one ion per lane (valid: it exists)
+    const double ex = ion.x - cx, ey = ion.y - cy, ez = ion.z - cz;
+    const double a0 = ceil((-hx - ex) * ilx), b0 = ceil((-hy - ey) * ily),
+                 c0 = ceil((-hz - ez) * ilz);
+    for (int a = 0; a < ma; ++a)
+      for (int b = 0; b < mb; ++b)
+        for (int c = 0; c < mc; ++c) {
+          const double sx = (a0 + a) * lx, sy = (b0 + b) * ly, sz = (c0 + c) * lz;
+          const double gx = fmax(fabs(ex + sx) - bx, 0.0), gy = fmax(fabs(ey + sy) - by, 0.0),
+                       gz = fmax(fabs(ez + sz) - bz, 0.0);   // from the box
+          push(make_double4(ion.x + sx, ion.y + sy, ion.z + sz, ion.w),
+               valid && fma(gx, gx, fma(gy, gy, gz * gz)) < rw * rw);
         }
-        const int64_t s0 = cs[row + c0], s1 = cs[row + c1];
-        for (int64_t base = s0; base < s1; base += 64) {
-          const int64_t q = base + lane;
-          if (q < s1) si[lane] = sf[q];
-          __syncthreads();
-          const int cnt = (int)((s1 - base) < 64 ? (s1 - base) : 64);
-          if (i >= 0) {
-            for (int j = 0; j < cnt; ++j) {
-              const double4 ion = si[j];
-              double dz = zi - ion.z;
-              dz -= lz * rint(dz * ilz);
-              int iza, izb;
-              image_range(dz, lz, ilz, rcut, wz, iza, izb);
-              if (iza > izb) continue;
-              double dx = xi - ion.x;
-              double dy = yi - ion.y;
-              dx -= lx * rint(dx * ilx);
-              dy -= ly * rint(dy * ily);
-              int ixa, ixb, iya, iyb;
-              image_range(dx, lx, ilx, rcut, wx, ixa, ixb);
-              image_range(dy, ly, ily, rcut, wy, iya, iyb);
-              const double qv = ion.w;
-              for (int a = ixa; a <= ixb; ++a) {
-                const double ex = dx + (double)a * lx;
-                for (int bb = iya; bb <= iyb; ++bb) {
-                  const double ey = dy + (double)bb * ly;
-                  const double exy = ex * ex + ey * ey;
-                  if (exy >= rc2) continue;
-                  for (int c = iza; c <= izb; ++c) {
-                    const double ez = dz + (double)c * lz;
-                    const double d2 = exy + ez * ez;
-                    if (d2 < rc2) {
-                      if (d2 > 0.0) {
-                        const double d = sqrt(d2);
-                        acc += qv * ((erfc_pw(et, beta * d) - erfc_pw(et, ai * d)) / d);
-                      } else {
-                        acc += qv * lim0;
-                      }
-                    }
-                  }
-                }
-              }
-            }
-          }
-          __syncthreads();
+  };
+  __syncthreads();
+  if ((t & ~(int64_t)63) >= n) return;
+  if constexpr (CELL) {
+    // cells meeting the widened box
+    int xa, xb, ya, yb, za, zb;
+    cell_span(cx - hx, cx + hx, ncx * ilx, ncx, xa, xb);
+    cell_span(cy - hy, cy + hy, ncy * ily, ncy, ya, yb);
+    cell_span(cz - hz, cz + hz, ncz * ilz, ncz, za, zb);
+    const int32_t *cs = cstart + f * ((int64_t)ncx * ncy * ncz + 1);
+    const double4 *sf = sorted + f * m;
+    int turn = (int)(gridDim.z - grp) - 1;   // the group takes each gridDim.z-th row
+    const int xlen = xb - xa + 1, xw0 = wrap_cell(xa, ncx);
+    for (int az = za; az <= zb; ++az) {
+      const int azw = wrap_cell(az, ncz);
+      for (int ay = ya; ay <= yb; ++ay) {
+        if (++turn < (int)gridDim.z) continue;
+        turn = 0;
+        const int64_t row = ((int64_t)azw * ncy + wrap_cell(ay, ncy)) * ncx;
+        for (int part = 0; part < 2; ++part) {
+          const int c0 = part == 0 ? xw0 : 0;
+          const int c1 = part == 0 ? min(ncx, xw0 + xlen) : xw0 + xlen - ncx;
+          if (c1 <= c0) break;
+          const int64_t s0 = cs[row + c0], s1 = cs[row + c1];
+          for (int64_t base = s0; base < s1; base += 64)
+            offer(sf[min(base + lane, s1 - 1)], base + lane < s1);
         }
       }
     }
+  } else {
+    const double *pf = ion_pos + f * m * 3;
+    const double *qf = ion_q + f * m;
+    const int64_t i0 = grp * ipg, i1 = min(m, i0 + ipg);
+    for (int64_t base = i0; base < i1; base += 64) {
+      const int64_t I = min(base + lane, i1 - 1);
+      offer(make_double4(pf[3 * I], pf[3 * I + 1], pf[3 * I + 2], qf[I]), base + lane < i1);
+    }
   }
-  if (i >= 0) rs[f * n + i] = acc;
+  wave_sync();
+  process(cnt);
+  if (i >= 0) rs[(grp * f_total + f) * n + i] = acc;
 }
 
 }  // namespace
@@ -1453,6 +1393,19 @@ constexpr double kNuDirect = 1.0 / 38e12, kNuSpread = 1.0 / 33e12, kNuPoint = 2.
 int64_t groups_for(int64_t blocks, int64_t items, int64_t cap, int64_t &per) {
   int64_t g = (kTargetBlocks + blocks - 1) / std::max<int64_t>(1, blocks);
   g = std::min<int64_t>({g, std::max<int64_t>(1, items / RB), 64, std::max<int64_t>(1, cap)});
+  g = std::max<int64_t>(1, g);
+  per = (items + g - 1) / g;
+  return per > 0 ? (items + per - 1) / per : 1;
+}
+
+// the same for workgroups of one wave: with work as uneven as the real-space
+// sums of atoms near and far from the ions, two waves for each of the ~4096
+// that are resident (13 frames of 1999 ions and 4599 atoms: 131 us with 2048
+// waves, 100 with 4096, 78 with 8192, 71 with 16384, 81 with 32768; 16 frames
+// of 2000 and 4608: 90, 70, 60, 62, 76; a table per wave in all of them)
+int64_t wave_groups(int64_t waves, int64_t items, int64_t least, int64_t cap, int64_t &per) {
+  int64_t g = (8192 + waves - 1) / std::max<int64_t>(1, waves);
+  g = std::min<int64_t>({g, std::max<int64_t>(1, items / least), 64, std::max<int64_t>(1, cap)});
   g = std::max<int64_t>(1, g);
   per = (items + g - 1) / g;
   return per > 0 ? (items + per - 1) / per : 1;
@@ -1535,9 +1488,11 @@ RhsPlan rhs_plan_capped(const cpm_system *s, int64_t m, int64_t f, int64_t cap_s
     p.rs_cell = true;
     cell_grid(s->box, s->rcut, p.nc);
     p.nchunks = (m + kChunk - 1) / kChunk;
-    p.rs_groups = 1;
+    p.rs_groups = wave_groups((n + 63) / 64 * f, (int64_t)p.nc[1] * p.nc[2], 4,
+                              std::min(cap_rs, kPartialCap / (f * n)), p.rs_ipg);
   } else if (m > 0) {
-    p.rs_groups = groups_for(iblocks * f, m, std::min(cap_rs, kPartialCap / (f * n)), p.rs_ipg);
+    p.rs_groups = wave_groups((n + 63) / 64 * f, m, 16, std::min(cap_rs, kPartialCap / (f * n)),
+                              p.rs_ipg);
   }
   const int64_t ncell = (int64_t)p.nc[0] * p.nc[1] * p.nc[2];
   p.off_sg = 2 * nk * f;
@@ -1898,15 +1853,19 @@ hipError_t launch_rhs(hipStream_t st, const cpm_system *s, const double *ion_pos
   if (p.rs_cell) {
     const double4 *sorted = reinterpret_cast<const double4 *>(buf + p.off_sorted);
     const int32_t *cstart = reinterpret_cast<const int32_t *>(buf + p.off_cstart);
-    hipLaunchKernelGGL(real_space_cell_kernel, dim3((unsigned)((n + 63) / 64), (unsigned)f),
-                       dim3(64), 0, st, s->pos, s->rs_width, s->atom_order, n,
-                       sorted, cstart, m, p.nc[0], p.nc[1],
-                       p.nc[2], s->box[0], s->box[1], s->box[2], s->beta, s->rcut, f,
-                       (const double *)s->erfc_tab, rs);
+    hipLaunchKernelGGL(real_space_kernel<true>,
+                       dim3((unsigned)((n + 64 * RS_W - 1) / (64 * RS_W)), (unsigned)f,
+                            (unsigned)p.rs_groups),
+                       dim3(64 * RS_W), 0, st, s->pos, s->rs_width, s->atom_order, n, ion_pos, ion_q,
+                       (int64_t)0, sorted, cstart, m, p.nc[0], p.nc[1], p.nc[2], s->box[0],
+                       s->box[1], s->box[2], s->beta, s->rcut, f, (const double *)s->erfc_tab, rs);
   } else if (p.rs_groups > 0) {
-    hipLaunchKernelGGL(real_space_ions_kernel, dim3((unsigned)iblocks, (unsigned)f, (unsigned)p.rs_groups),
-                       dim3(RB), 0, st, s->pos, s->rs_width, s->atom_order, n, ion_pos, ion_q, m,
-                       p.rs_ipg, s->box[0], s->box[1], s->box[2], s->beta, s->rcut, f,
+    hipLaunchKernelGGL(real_space_kernel<false>,
+                       dim3((unsigned)((n + 64 * RS_W - 1) / (64 * RS_W)), (unsigned)f,
+                            (unsigned)p.rs_groups),
+                       dim3(64 * RS_W), 0, st, s->pos, s->rs_width, s->atom_order, n, ion_pos, ion_q,
+                       p.rs_ipg, (const double4 *)nullptr, (const int32_t *)nullptr, m, 1, 1, 1,
+                       s->box[0], s->box[1], s->box[2], s->beta, s->rcut, f,
                        (const double *)s->erfc_tab, rs);
   }
   hipLaunchKernelGGL(assemble_b_kernel, dim3((unsigned)((n * f + 255) / 256)), dim3(256), 0, st,
@@ -1915,28 +1874,42 @@ hipError_t launch_rhs(hipStream_t st, const cpm_system *s, const double *ion_pos
   return hipGetLastError();
 }
 
-// Coefficients of erfc_pw. About x_j = (j + 1/2) / 8: c_j0 = erfc(x_j) and,
-// from d^(k+1)/dx^(k+1) erfc(x) = -(2/sqrt(pi)) (-1)^k H_k(x) exp(-x^2) with
-// the Hermite recurrence H_(k+1) = 2 x H_k - 2 k H_(k-1), c_j(k+1) = that
-// derivative / ((k+1)! 8^(k+1)); long double arithmetic. The truncation
-// after degree 11 on |x - x_j| <= 1/16 is below 1e-17.
+// Coefficients of erfc_pw. About x_j = (j + 1/2) / kErfcPer: c_0 = erfc(x_j)
+// and, from d^(k+1)/dx^(k+1) erfc(x) = -(2/sqrt(pi)) (-1)^k H_k(x) exp(-x^2)
+// with the Hermite recurrence H_(k+1) = 2 x H_k - 2 k H_(k-1), c_(k+1) = that
+// derivative / ((k+1)! kErfcPer^(k+1)), taken to degree NT - 1 in long double
+// and reduced to kErfcTerms terms one degree at a time: subtract the multiple
+// of the Chebyshev polynomial T_n(2u) that cancels u^n (it adds at most
+// |c_n| / 2^(2n-1) on [-1/2, 1/2]).
 void erfc_table(double *out) {
+  constexpr int NT = 16;
   const long double c2 = 2.0L / std::sqrt(3.14159265358979323846264338327950288L);
+  long double cheb[NT][NT] = {};   // T_n(2u) in powers of u
+  cheb[0][0] = 1.0L;
+  cheb[1][1] = 2.0L;
+  for (int n = 2; n < NT; ++n)
+    for (int k = 0; k <= n; ++k)
+      cheb[n][k] = (k > 0 ? 4.0L * cheb[n - 1][k - 1] : 0.0L) - cheb[n - 2][k];
   for (int j = 0; j < kErfcIntervals; ++j) {
-    const long double x = ((long double)j + 0.5L) / 8.0L;
+    const long double x = ((long double)j + 0.5L) / kErfcPer;
     const long double e = std::exp(-x * x);
-    double *c = out + j * kErfcTerms;
-    c[0] = std::erfc((double)x);   // x_j is exact in double
+    long double c[NT];
+    c[0] = std::erfc(x);
     long double hprev = 0.0L, hcur = 1.0L, fact = 1.0L, scale = 1.0L;
-    for (int k = 0; k + 1 < kErfcTerms; ++k) {
+    for (int k = 0; k + 1 < NT; ++k) {
       const long double sign = (k % 2 == 0) ? -1.0L : 1.0L;
       fact *= (long double)(k + 1);
-      scale /= 8.0L;
-      c[k + 1] = (double)(sign * c2 * hcur * e * scale / fact);
+      scale /= kErfcPer;
+      c[k + 1] = sign * c2 * hcur * e * scale / fact;
       const long double hnext = 2.0L * x * hcur - 2.0L * (long double)k * hprev;
       hprev = hcur;
       hcur = hnext;
     }
+    for (int n = NT - 1; n >= kErfcTerms; --n) {
+      const long double w = c[n] / cheb[n][n];
+      for (int k = 0; k <= n; ++k) c[k] -= w * cheb[n][k];
+    }
+    for (int k = 0; k < kErfcTerms; ++k) out[j * kErfcTerms + k] = (double)c[k];
   }
 }
 
