@@ -46,9 +46,10 @@ struct Kset {
 
 constexpr int kSfTile = 64;    // columns per workgroup of the structure-factor product
 
-// electrode atoms on at most kMaxPlanes exact z-planes (graphite layers)
-// take the factored back-projection; its n_z sums keep a table of
-// |n_z| <= kMaxPlaneS per plane in LDS; kPlaneTile atoms per wave tile
+// electrode atoms in few thin layers along z take the factored
+// back-projection: at most kMaxPlanes exact z-planes, or layers with a few
+// interpolation nodes each; its tables hold |n_z| <= kMaxPlaneS per node;
+// kPlaneTile atoms per wave tile
 constexpr int kMaxPlanes = 64;
 constexpr int kMaxPlaneS = 1023;
 constexpr int kPlaneTile = 16;
@@ -56,6 +57,25 @@ constexpr int kRun = 24;       // longest run of consecutive n_z (phase recurren
 
 // Half-space reciprocal vectors with |K| <= kmax, K != 0 (host).
 Kset make_kset(const double box[3], double beta, double kmax);
+
+// The atoms in layers (host): per tile of kPlaneTile atoms {first node, node
+// count, offset into the weights / kPlaneTile, 0}, its atoms (-1 pads), z of
+// every node. Node counts are 1 (all atoms at the node) or multiples of four.
+struct LayerPlan {
+  std::vector<int32_t> tile, atom;
+  std::vector<double> node_z;
+  int64_t weights = 0;          // sum of the tiles' node counts
+};
+// the same on the device, in one block (nodes = 0: no layers)
+struct Layers {
+  int nodes = 0, nodes_pad = 0;
+  int64_t ntiles = 0;
+  bool multi = false;           // some layer has more than one node
+  double *buf = nullptr;
+  int32_t *tile = nullptr, *atom = nullptr;
+  double *zt = nullptr;         // [smax + 1][nodes_pad] exp(2 pi i s z / L_z)
+  double *lw = nullptr;         // Lagrange weights [offset + node][atom of the tile]
+};
 
 struct Workspace {            // CG scratch, grown on demand
   int64_t cols = 0;           // padded number of columns the buffers hold
@@ -257,14 +277,7 @@ struct cpm_system {
   int32_t *krun = nullptr;    // nruns*2 device (Kset::runs)
   int32_t *kcol = nullptr;    // ncols_pad*4 device (Kset::cols)
   int32_t *atom_order = nullptr;  // n device: atoms in compact spatial tiles (real-space sums)
-  // the atoms' z-planes when there are at most kMaxPlanes of them (else
-  // nplanes = 0): z / L_z per plane, and tiles of kPlaneTile atoms of one
-  // plane each (atom -1 pads a plane's last tile)
-  int nplanes = 0;
-  int64_t plane_ntiles = 0;
-  double *plane_uz = nullptr;
-  int32_t *plane_tile = nullptr;  // plane_ntiles: plane of the tile
-  int32_t *plane_atom = nullptr;  // plane_ntiles * kPlaneTile
+  cpm::Layers layer;            // of the atoms, for the factored back-projection
   double *E64 = nullptr;      // ld*ld device (rows >= n and cols >= n are zero)
   float *E32 = nullptr;
   uint16_t *E16 = nullptr;
@@ -333,6 +346,8 @@ constexpr int kErfcIntervals = 104;
 constexpr int kErfcTerms = 9;
 constexpr int kErfcTab = kErfcIntervals * kErfcTerms;
 void erfc_table(double *out);
+int64_t layers_elems(const LayerPlan &lp, int smax);
+hipError_t set_layers(cpm_system *s, hipStream_t st, const LayerPlan &lp, double *buf);
 int64_t rhs_scratch_elems(const cpm_system *s, int64_t m, int64_t f);
 // sizes of the grid path (system set-up), whether this call takes it, its tables
 void nu_sizes(cpm_system *s);

@@ -16,6 +16,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <mutex>
 #include <type_traits>
 #include <vector>
@@ -94,12 +95,12 @@ __global__ __launch_bounds__(RB) void qsum_kernel(const double *__restrict__ q, 
 // complex product with exp(2 pi i z_I / L_z), the following ones by the
 // three-term recurrence of the cosine and sine, so kRun vectors cost one
 // sincospi and about kRun FMAs per part and ion. Ions stream through LDS.
-// Output layout: Sg[((g * nk + k) * f_total + f) * 2 + {0: Re, 1: Im}].
+// Output layout: Sg[(g * nk * f_total + k * sk + f * sf) * 2 + {0: Re, 1: Im}].
 __global__ __launch_bounds__(RB) void structure_factor_kernel(
     const double *__restrict__ ion_pos, const double *__restrict__ ion_q, int64_t m, int64_t ipg,
     const int32_t *__restrict__ kinfo, const int32_t *__restrict__ runs, int64_t nruns,
-    int64_t nk, double inv_lx, double inv_ly, double inv_lz, int64_t f_total,
-    double *__restrict__ Sg) {
+    int64_t nk, double inv_lx, double inv_ly, double inv_lz, int64_t f_total, int64_t sk,
+    int64_t sf, double *__restrict__ Sg) {
   __shared__ double su[RB][6];   // x/L, y/L, z/L, q, cos and sin of 2 pi z/L
   const int64_t f = blockIdx.y, g = blockIdx.z;
   const int64_t r = (int64_t)blockIdx.x * RB + threadIdx.x;
@@ -177,12 +178,12 @@ __global__ __launch_bounds__(RB) void structure_factor_kernel(
     __syncthreads();
   }
   if (r < nruns) {
-    double *out = Sg + ((g * nk + k0) * f_total + f) * 2;
+    double *out = Sg + (g * nk * f_total + k0 * sk + f * sf) * 2;
 #pragma unroll
     for (int st = 0; st < kRun; ++st)
       if (st < len) {
-        out[st * f_total * 2] = ar[st];
-        out[st * f_total * 2 + 1] = ai[st];
+        out[st * sk * 2] = ar[st];
+        out[st * sk * 2 + 1] = ai[st];
       }
   }
 }
@@ -254,7 +255,8 @@ __device__ __forceinline__ void sf_gemm_body(SfLds &L, const double *__restrict_
                                              int64_t ipg, const int4 *__restrict__ kcol,
                                              int64_t cbase, int64_t f, int64_t g, double inv_lx,
                                              double inv_ly, double inv_lz, int64_t nk,
-                                             int64_t f_total, double *__restrict__ Sg) {
+                                             int64_t f_total, int64_t sk, int64_t sf,
+                                             double *__restrict__ Sg) {
   constexpr int NS = 16 * NSB;        // s values of the tables
   constexpr int PER = NS / 8;         // s values per table thread
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -293,11 +295,11 @@ __device__ __forceinline__ void sf_gemm_body(SfLds &L, const double *__restrict_
     double t = (double)(tj * PER) * uz;
     t -= rint(t);
     double sn, cs;
-    sincospi(2.0 * t, &sn, &cs);
+    phase_cs(L.tw, t, cs, sn);
     L.zt[buf][ti][tj * PER] = make_double2(cs, sn);
     if (PER > 1) {
       double t1 = uz - rint(uz), s1, c1;
-      sincospi(2.0 * t1, &s1, &c1);
+      phase_cs(L.tw, t1, c1, s1);
 #pragma unroll
       for (int u = 1; u < PER; ++u) {
         const double c2 = cs * c1 - sn * s1;
@@ -307,14 +309,15 @@ __device__ __forceinline__ void sf_gemm_body(SfLds &L, const double *__restrict_
       }
     }
   };
-  // the exp(2 pi i j / kTw) table (read after the first barrier below)
+  // the exp(2 pi i j / kTw) table
   if (tid < kTw) {
     double sj, cj;
     sincospi(2.0 * (double)tid / kTw, &sj, &cj);
     L.tw[tid] = make_double2(cj, sj);
   }
+  if (nchunks > 0) fetch(0);
+  __syncthreads();
   if (nchunks > 0) {
-    fetch(0);
     table(0);
   }
   for (int c = 0; c < nchunks; ++c) {
@@ -353,12 +356,12 @@ __device__ __forceinline__ void sf_gemm_body(SfLds &L, const double *__restrict_
                    BZ = acc[sb][3][v];
       const bool half = col.x == 0 && col.y == 0;   // n_z = 1..m only
       if (!(half && sv == 0)) {
-        double *o = Sg + ((g * nk + col.w + sv) * f_total + f) * 2;
+        double *o = Sg + (g * nk * f_total + (col.w + sv) * sk + f * sf) * 2;
         o[0] = AZ - BW;
         o[1] = AW + BZ;
       }
       if (!half && sv > 0) {
-        double *o = Sg + ((g * nk + col.w - sv) * f_total + f) * 2;
+        double *o = Sg + (g * nk * f_total + (col.w - sv) * sk + f * sf) * 2;
         o[0] = AZ + BW;
         o[1] = BZ - AW;
       }
@@ -366,28 +369,28 @@ __device__ __forceinline__ void sf_gemm_body(SfLds &L, const double *__restrict_
   }
 }
 
-// One launch for every tile: grid (frames, tiles, ion groups), so that the
-// dispatch order runs through the frames of the first tiles (the most s
-// blocks, the longest workgroups) first and ends with the tiles of one s
-// block; the s-block count of a tile is set by its first column (the
-// columns are sorted by their largest |n_z|) and selects the body compiled
-// for it.
+// One launch for every tile: grid (frames * ion groups, tiles), so that the
+// dispatch order starts with the first tiles (the most s blocks, the longest
+// workgroups) and ends with the tiles of one s block; the s-block count of a
+// tile is set by its first column (the columns are sorted by their largest
+// |n_z|) and selects the body compiled for it.
 __global__ __launch_bounds__(256, 2) void sf_gemm_kernel(
     const double *__restrict__ ion_pos, const double *__restrict__ ion_q, int64_t m, int64_t ipg,
     const int4 *__restrict__ kcol, double inv_lx, double inv_ly, double inv_lz, int64_t nk,
-    int64_t f_total, double *__restrict__ Sg) {
+    int64_t f_total, int64_t sk, int64_t sf, double *__restrict__ Sg) {
   __shared__ SfLds L;
-  const int64_t f = blockIdx.x, cbase = (int64_t)blockIdx.y * kSfTile, g = blockIdx.z;
+  const int64_t f = blockIdx.x % f_total, g = blockIdx.x / f_total;
+  const int64_t cbase = (int64_t)blockIdx.y * kSfTile;
   const int nsb = (kcol[cbase].z + 16) / 16;
   if (nsb >= 3)
     sf_gemm_body<3>(L, ion_pos, ion_q, m, ipg, kcol, cbase, f, g, inv_lx, inv_ly, inv_lz, nk,
-                    f_total, Sg);
+                    f_total, sk, sf, Sg);
   else if (nsb == 2)
     sf_gemm_body<2>(L, ion_pos, ion_q, m, ipg, kcol, cbase, f, g, inv_lx, inv_ly, inv_lz, nk,
-                    f_total, Sg);
+                    f_total, sk, sf, Sg);
   else
     sf_gemm_body<1>(L, ion_pos, ion_q, m, ipg, kcol, cbase, f, g, inv_lx, inv_ly, inv_lz, nk,
-                    f_total, Sg);
+                    f_total, sk, sf, Sg);
 }
 
 // ---- ion structure factors through a grid (non-uniform FFT of type 1)
@@ -753,14 +756,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3))) voi
     }
 }
 
-// S[e] = sum_g Sg[g][e] over the ion groups (fixed order)
-__global__ void sum_groups_kernel(const double *__restrict__ Sg, int groups, int64_t len,
-                                  double *__restrict__ S) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= len) return;
-  double s = 0.0;
-  for (int g = 0; g < groups; ++g) s += Sg[(int64_t)g * len + e];
-  S[e] = s;
+// S[k][f] = sum_g Sg[g][f][k] over the ion groups (fixed order). The groups
+// are written by frame, where the k-vectors of a column are contiguous, and
+// read by k-vector, where the frames are: 32 vectors by 16 frames per
+// workgroup through LDS. (Written as [k][f], every 16-byte value of a group
+// was a line of its own: 13 frames of 1999 ions with 17 groups, 93 us for the
+// product then, 80 now.)
+constexpr int SGT_K = 32, SGT_F = 16;
+__global__ __launch_bounds__(256) void sum_groups_kernel(const double2 *__restrict__ Sg,
+                                                         int groups, int64_t nk, int64_t f_total,
+                                                         double2 *__restrict__ S) {
+  __shared__ double2 t[SGT_F][SGT_K + 1];
+  const int64_t k0 = (int64_t)blockIdx.x * SGT_K, f0 = (int64_t)blockIdx.y * SGT_F;
+  const int kk = threadIdx.x % SGT_K;
+#pragma unroll
+  for (int h = 0; h < SGT_F * SGT_K / 256; ++h) {
+    const int ff = threadIdx.x / SGT_K + h * (256 / SGT_K);
+    const int64_t k = min(k0 + kk, nk - 1), f = min(f0 + ff, f_total - 1);
+    const double2 *src = Sg + f * nk + k;
+    double re = 0.0, im = 0.0;
+#pragma unroll 4
+    for (int g = 0; g < groups; ++g) {
+      const double2 v = src[(int64_t)g * nk * f_total];
+      re += v.x;
+      im += v.y;
+    }
+    t[ff][kk] = make_double2(re, im);
+  }
+  __syncthreads();
+  const int nf = (int)min((int64_t)SGT_F, f_total - f0);
+  for (int e = threadIdx.x; e < SGT_K * nf; e += 256) {
+    const int k = e / nf, f = e - k * nf;
+    if (k0 + k < nk) S[(k0 + k) * f_total + f0 + f] = t[f][k];
+  }
 }
 
 // Back-projection of the ion structure factors onto the electrode atoms,
@@ -864,119 +892,242 @@ __global__ __launch_bounds__(RB) void backproject_kernel(
   }
 }
 
-// Factored back-projection for electrode atoms on few z-planes. With
+// Factored back-projection for electrode atoms in few thin layers. With
 // exp(i K.r) = P_c(x, y) Z_nz(z), P_c = exp(2 pi i (n_x x / L_x + n_y y / L_y)),
 // Z_nz = exp(2 pi i n_z z / L_z), for the column c = (n_x, n_y):
-//   sum_K w_K Re(exp(-i K.r_i) S_fK) = sum_c Re(conj(P_c(r_i)) T_f(p, c)),
-//   T_f(p, c) = sum_nz w_(c, nz) conj(Z_nz(z_p)) S_f(c, nz),
-// where z_p is the z shared by every atom of plane p: the n_z sums are
-// taken once per (plane, column, frame) instead of once per atom.
+//   sum_K w_K Re(exp(-i K.r_i) S_fK) = sum_c Re(conj(P_c(r_i)) T_f(z_i, c)),
+//   T_f(z, c) = sum_nz w_(c, nz) conj(Z_nz(z)) S_f(c, nz).
+// The n_z sums are taken once per (node, column, frame) instead of once per
+// atom: the node of an exact plane is its z; a layer of finite thickness D
+// has nodes at the Chebyshev points of its z range, and
+//   T_f(z_i, c) = sum_j l_j(z_i) T_f(z_j, c)
+// with the Lagrange polynomials l_j. T is band-limited to k = 2 pi smax / L_z,
+// so n nodes leave an error of at most 2 (k D / 4)^n / n! of the sum, below
+// 1e-17 by the choice of n.
 //
-// plane_table_kernel: T as Re / Im arrays [plane][column][frame] (zero for
-// the padding columns). Grid (columns * frames / PT_THREADS, planes); the
-// plane's Z_s for s = 0..smax sit in LDS (sincospi of the reduced
-// fractional phase), Z_-s = conj(Z_s).
-constexpr int PT_THREADS = 256;
-
-__global__ __launch_bounds__(PT_THREADS) void plane_table_kernel(
-    const double *__restrict__ plane_uz, const int4 *__restrict__ kcol, int64_t ncols_pad,
-    const double *__restrict__ kw, const double *__restrict__ S, int64_t f_total, int smax,
-    double *__restrict__ Tre, double *__restrict__ Tim) {
-  __shared__ double2 zt[kMaxPlaneS + 1];
-  const int p = blockIdx.y;
-  const double u = plane_uz[p];
-  for (int sv = threadIdx.x; sv <= smax; sv += PT_THREADS) {
-    double t = (double)sv * u;
-    t -= rint(t);
-    double sn, cs;
-    sincospi(2.0 * t, &sn, &cs);
-    zt[sv] = make_double2(cs, sn);
+// layer_tables_kernel (system set-up): Z_s of every node, zt[s][node], and
+// l_j of every tile's atoms, lw[tile offset + j][atom] (1 for an exact plane;
+// the barycentric form, whose weights at the Chebyshev points are
+// (-1)^j sin((j + 1/2) pi / n)).
+__global__ void layer_tables_kernel(const double *__restrict__ pos, double inv_lz,
+                                    const int4 *__restrict__ tile,
+                                    const int32_t *__restrict__ tile_atom, int64_t ntiles,
+                                    const double *__restrict__ node_z, int nodes, int nodes_pad,
+                                    int smax, double2 *__restrict__ zt, double *__restrict__ lw) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t nz = (int64_t)(smax + 1) * nodes_pad;
+  if (e < nz) {
+    const int64_t sv = e / nodes_pad;
+    const int node = (int)(e - sv * nodes_pad);
+    double sn = 0.0, cs = 0.0;
+    if (node < nodes) {
+      double t = (double)sv * (node_z[node] * inv_lz);
+      t -= rint(t);
+      sincospi(2.0 * t, &sn, &cs);
+    }
+    zt[e] = make_double2(cs, sn);
   }
-  __syncthreads();
-  const int64_t idx = (int64_t)blockIdx.x * PT_THREADS + threadIdx.x;
-  if (idx >= ncols_pad * f_total) return;
-  const int64_t c = idx / f_total, f = idx - c * f_total;
+  if (e < ntiles * kPlaneTile) {
+    const int4 tl = tile[e / kPlaneTile];
+    const int32_t a = tile_atom[e];
+    const double z = a >= 0 ? pos[3 * (int64_t)a + 2] : node_z[tl.x];
+    double *w = lw + (int64_t)tl.z * kPlaneTile + e % kPlaneTile;
+    int hit = tl.y == 1 ? 0 : -1;
+    double sum = 0.0;
+    for (int j = 0; j < tl.y; ++j) {
+      const double d = z - node_z[tl.x + j];
+      if (d == 0.0) hit = j;
+      const double q = (j & 1 ? -1.0 : 1.0) * sinpi((j + 0.5) / tl.y) / d;
+      w[j * kPlaneTile] = q;
+      sum += q;
+    }
+    for (int j = 0; j < tl.y; ++j)
+      w[j * kPlaneTile] = hit < 0 ? w[j * kPlaneTile] / sum : (j == hit ? 1.0 : 0.0);
+  }
+}
+
+// T as Re / Im arrays [node][column][frame] (zero for the padding columns):
+// per column the product [nodes x n_z] . [n_z x frames] of conj(Z) and w S as
+// four real products on the FP64 matrix cores. One wave per column, 16 nodes
+// and 16 frames; every lane's loads are in bounds and unconditional (n_z
+// beyond the column repeat its last with weight 0), so that they overlap.
+// Bound by latency: a thread per (column, frame) and plane that walked n_z
+// alone took 38 us where this takes 8 (one frame, 6 planes, 448 columns).
+constexpr int PT_WAVES = 4;
+
+__global__ __launch_bounds__(64 * PT_WAVES) void plane_table_kernel(
+    const double2 *__restrict__ zt, int nodes, int nodes_pad, const int4 *__restrict__ kcol,
+    int64_t ncols_pad, const double *__restrict__ kw, const double2 *__restrict__ S,
+    int64_t f_total, double *__restrict__ Tre, double *__restrict__ Tim) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
+  const int64_t c = (int64_t)blockIdx.x * PT_WAVES + wave;   // ncols_pad is a multiple
+  const int node0 = blockIdx.y * 16;
+  const int64_t f = (int64_t)blockIdx.z * 16 + lr, fc = min(f, f_total - 1);
   const int4 col = kcol[c];
-  double re = 0.0, im = 0.0;
+  d4 re = d4{0.0, 0.0, 0.0, 0.0}, im = re;
   if (col.z >= 0) {
     // (0, 0) holds n_z = 1..m only
     const int lo = (col.x == 0 && col.y == 0) ? 1 : -col.z;
-    for (int nz = lo; nz <= col.z; ++nz) {
-      const int64_t k = (int64_t)col.w + nz;
-      const double2 sv = *reinterpret_cast<const double2 *>(S + (k * f_total + f) * 2);
-      const double w = kw[k];
-      const double2 z = zt[nz < 0 ? -nz : nz];
-      const double zi = nz < 0 ? -z.y : z.y;   // Im Z_nz
-      // conj(Z) S = (Re Z Re S + Im Z Im S) + i (Re Z Im S - Im Z Re S)
-      re = fma(w, fma(z.x, sv.x, zi * sv.y), re);
-      im = fma(w, fma(z.x, sv.y, -zi * sv.x), im);
+    const double2 *zn = zt + node0 + lr;
+    for (int n0 = lo; n0 <= col.z; n0 += 16) {
+      d2 sv[4], z[4];
+      double wk[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int nz = min(n0 + 4 * u + lq, col.z);
+        const int64_t k = (int64_t)col.w + nz;
+        sv[u] = *reinterpret_cast<const d2 *>(S + k * f_total + fc);
+        z[u] = *reinterpret_cast<const d2 *>(zn + (int64_t)abs(nz) * nodes_pad);
+        wk[u] = kw[k];
+      }
+      __builtin_amdgcn_sched_barrier(0);   // every load issued before the first wait
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int nz = n0 + 4 * u + lq;
+        const double w = nz > col.z ? 0.0 : wk[u];
+        const double zr = z[u].x, zi = min(nz, col.z) < 0 ? -z[u].y : z[u].y;   // Z_nz
+        const double sr = w * sv[u].x, si = w * sv[u].y;
+        // conj(Z) S = (Re Z Re S + Im Z Im S) + i (Re Z Im S - Im Z Re S)
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(zr, sr, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(zr, si, im, 0, 0, 0);
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(zi, si, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(-zi, sr, im, 0, 0, 0);
+      }
     }
   }
-  const int64_t o = ((int64_t)p * ncols_pad + c) * f_total + f;
-  Tre[o] = re;
-  Tim[o] = im;
+  // D[i][j] (node i, frame j) in lane j + 16 (i % 4), register i / 4
+  if (f >= f_total) return;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int node = node0 + 4 * v + lq;
+    if (node >= nodes) continue;
+    const int64_t o = ((int64_t)node * ncols_pad + c) * f_total + f;
+    Tre[o] = re[v];
+    Tim[o] = im[v];
+  }
 }
 
-// part[f][i] = sum_c cos(theta_ic) Re T_f(p, c) + sin(theta_ic) Im T_f(p, c),
+// part[f][i] = sum_c cos(theta_ic) Re T_f(z_i, c) + sin(theta_ic) Im T_f(z_i, c),
 // theta_ic = 2 pi (n_x x_i / L_x + n_y y_i / L_y): the product
-// [atoms x (cos, sin) of the columns] . [(Re T, Im T) x frames] on the FP64
-// matrix cores. One wave per tile of kPlaneTile atoms of one plane and up to
-// 32 frames: per step of 4 columns, lane (r, q) forms the phase of atom r
-// and column q once (sincospi of the reduced fractional phase) and gives
-// its cosine and sine as the A operand of two v_mfma_f64_16x16x4f64 per 16
-// frames, with Re T and Im T of (column q, frame r) as the B operand.
-// Grid (tiles / PB_WAVES, frames / 32, column splits): split z takes the
+// [frames x (nodes of the columns)] . [l_j (cos, sin) x atoms] on the FP64
+// matrix cores. One wave per tile of kPlaneTile atoms of one layer and up to
+// 16 NF frames: per step of 4 columns, lane (r, q) forms the phase of atom r
+// and column q once; per node its l_j multiples are the B operand and Re T
+// and Im T of (column q, frame r) the A operand of two
+// v_mfma_f64_16x16x4f64 per 16 frames. MULTI: some layer has more than one
+// node; its node count is a multiple of four, whose loads overlap. Measured for 4608
+// atoms: 9 us for one frame, 10 for 16 (sincospi phases, always 32 frames: 16
+// and 18); 4599 atoms in layers of 8 nodes, 13 frames 38 us; 32768 atoms, 64
+// frames 540 us (740).
+// Grid (tiles / PB_WAVES, frames / (16 NF), column splits): split z takes the
 // columns [z cper, (z + 1) cper) and writes part + z f n (summed with the
 // other splits when b is assembled).
 constexpr int PB_WAVES = 4;
 
+template <int NF, bool MULTI>
 __global__ __launch_bounds__(64 * PB_WAVES) void plane_backproject_kernel(
-    const double *__restrict__ pos, int64_t n, const int32_t *__restrict__ tile_plane,
-    const int32_t *__restrict__ tile_atom, int64_t ntiles, const int4 *__restrict__ kcol,
-    int64_t ncols_pad, int64_t cper, double inv_lx, double inv_ly,
+    const double *__restrict__ pos, int64_t n, const int4 *__restrict__ tile,
+    const int32_t *__restrict__ tile_atom, const double *__restrict__ lw, int64_t ntiles,
+    const int4 *__restrict__ kcol, int64_t ncols_pad, int64_t cper, double inv_lx, double inv_ly,
     const double *__restrict__ Tre, const double *__restrict__ Tim, int64_t f_total,
     double *__restrict__ part) {
+  __shared__ double2 tw[kTw];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (threadIdx.x < kTw) {
+    double sj, cj;
+    sincospi(2.0 * (double)threadIdx.x / kTw, &sj, &cj);
+    tw[threadIdx.x] = make_double2(cj, sj);
+  }
+  __syncthreads();
   const int64_t cbeg = (int64_t)blockIdx.z * cper, cend = min(ncols_pad, cbeg + cper);
   part += (int64_t)blockIdx.z * f_total * n;
   const int64_t t = (int64_t)blockIdx.x * PB_WAVES + wave;
   if (t >= ntiles) return;   // no barriers below: a wave may leave alone
   const int lr = lane & 15, lq = lane >> 4;
-  const int p = tile_plane[t];
+  const int4 tl = tile[t];
   const int32_t atom = tile_atom[t * kPlaneTile + lr];
   double ux = 0.0, uy = 0.0;
   if (atom >= 0) {
     ux = pos[3 * (int64_t)atom] * inv_lx;
     uy = pos[3 * (int64_t)atom + 1] * inv_ly;
   }
-  const int64_t fa = (int64_t)blockIdx.y * 32 + lr, fb = fa + 16;
-  const bool va = fa < f_total, vb = fb < f_total;
-  const double *tr = Tre + (int64_t)p * ncols_pad * f_total;
-  const double *ti = Tim + (int64_t)p * ncols_pad * f_total;
-  d4 acc0 = d4{0.0, 0.0, 0.0, 0.0}, acc1 = d4{0.0, 0.0, 0.0, 0.0};
-  for (int64_t c0 = cbeg; c0 < cend; c0 += 4) {
-    const int64_t c = c0 + lq;
+  int64_t fo[NF];
+  d4 acc[NF];
+#pragma unroll
+  for (int h = 0; h < NF; ++h) {
+    // frames beyond the last repeat it (their results are not written)
+    fo[h] = min((int64_t)blockIdx.y * (16 * NF) + 16 * h + lr, f_total - 1);
+    acc[h] = d4{0.0, 0.0, 0.0, 0.0};
+  }
+  const double *tr = Tre + (int64_t)tl.x * ncols_pad * f_total;
+  const double *ti = Tim + (int64_t)tl.x * ncols_pad * f_total;
+  const int64_t nstep = ncols_pad * f_total;
+  const double *wl = lw + (int64_t)tl.z * kPlaneTile + lr;
+  auto phase = [&](int64_t c, double &cs, double &sn) {
     const int4 col = kcol[c];
     double th = (double)col.x * ux + (double)col.y * uy;
     th -= rint(th);
-    double sn, cs;
-    sincospi(2.0 * th, &sn, &cs);
-    const int64_t o = c * f_total;
-    const double ra = va ? tr[o + fa] : 0.0, ia = va ? ti[o + fa] : 0.0;
-    const double rb = vb ? tr[o + fb] : 0.0, ib = vb ? ti[o + fb] : 0.0;
-    acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(cs, ra, acc0, 0, 0, 0);
-    acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(sn, ia, acc0, 0, 0, 0);
-    acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(cs, rb, acc1, 0, 0, 0);
-    acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(sn, ib, acc1, 0, 0, 0);
-  }
-  // D[i][j] (atom i of the tile, frame j) in lane j + 16 (i % 4), register i / 4
+    phase_cs(tw, th, cs, sn);
+  };
+  if (!MULTI || tl.y == 1) {
+    for (int64_t c0 = cbeg; c0 < cend; c0 += 16) {   // splits are multiples of 64
+      double va[4][NF], vb[4][NF], cs[4], sn[4];
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int32_t a = tile_atom[t * kPlaneTile + 4 * v + lq];
-    if (a < 0) continue;
-    if (va) part[fa * n + a] = acc0[v];
-    if (vb) part[fb * n + a] = acc1[v];
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int h = 0; h < NF; ++h) {
+          const int64_t o = (c0 + 4 * u + lq) * f_total + fo[h];
+          va[u][h] = tr[o];
+          vb[u][h] = ti[o];
+        }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) phase(c0 + 4 * u + lq, cs[u], sn[u]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int h = 0; h < NF; ++h) {
+          acc[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(va[u][h], cs[u], acc[h], 0, 0, 0);
+          acc[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(vb[u][h], sn[u], acc[h], 0, 0, 0);
+        }
+    }
+  } else {
+    for (int64_t c0 = cbeg; c0 < cend; c0 += 4) {
+      const int64_t c = c0 + lq, o = c * f_total;
+      double cs, sn;
+      phase(c, cs, sn);
+      for (int j0 = 0; j0 < tl.y; j0 += 4) {
+        double w[4], va[4][NF], vb[4][NF];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          w[j] = wl[(j0 + j) * kPlaneTile];
+#pragma unroll
+          for (int h = 0; h < NF; ++h) {
+            va[j][h] = tr[(j0 + j) * nstep + o + fo[h]];
+            vb[j][h] = ti[(j0 + j) * nstep + o + fo[h]];
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const double wc = w[j] * cs, ws = w[j] * sn;
+#pragma unroll
+          for (int h = 0; h < NF; ++h) {
+            acc[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(va[j][h], wc, acc[h], 0, 0, 0);
+            acc[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(vb[j][h], ws, acc[h], 0, 0, 0);
+          }
+        }
+      }
+    }
   }
+  // D[i][j] (frame i, atom j) in lane j + 16 (i % 4), register i / 4
+  if (atom < 0) return;
+#pragma unroll
+  for (int h = 0; h < NF; ++h)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int64_t f = (int64_t)blockIdx.y * (16 * NF) + 16 * h + 4 * v + lq;
+      if (f < f_total) part[f * n + atom] = acc[h][v];
+    }
 }
 
 // b[f, i] = chi_i / k_e - sum_ks bp[ks][f][i] - sum_g rs[g][f][i] - c0 Q_f
@@ -1345,9 +1496,9 @@ namespace {
 // Work split of one cpm_rhs call over f frames of m ions, and the layout of
 // its scratch buffer:
 //   S   [nk][f][2]             structure factors
-//   Sg  [sf_groups][nk][f][2]  per ion group (only when sf_groups > 1)
+//   Sg  [sf_groups][f][nk][2]  per ion group (only when sf_groups > 1)
 //   bp  [ksplit][f][n]         back-projection partials
-//   T   [2][planes][cols][f]   per-plane n_z sums (factored back-projection)
+//   T   [2][nodes][cols][f]    n_z sums per layer node (factored back-projection)
 //   rs  [rs_groups][f][n]      real-space partials
 //   nu  grid, y and x lines of nu_frames frames (structure factors through a grid)
 struct RhsPlan {
@@ -1458,7 +1609,21 @@ RhsPlan rhs_plan_capped(const cpm_system *s, int64_t m, int64_t f, int64_t cap_s
     const int64_t sf_blocks = p.sf_gemm ? (s->kset.ncols_pad / kSfTile) * f
                                         : std::max<int64_t>(1, rblocks) * f;
     p.nu = grid && m >= kCellMinIons && nu_pays(s, m, f);
-    p.sf_groups = groups_for(sf_blocks, m, std::min(cap_sf, kPartialCap / (2 * nk * f)), p.sf_ipg);
+    const int64_t cap = std::max<int64_t>(1, std::min(cap_sf, kPartialCap / (2 * nk * f)));
+    if (p.sf_gemm) {
+      // whole chunks of ions per group, for about 1024 workgroups (two per CU
+      // are resident): one frame of 2000 ions, 7 tiles: 43 us with 7 groups
+      // of 286 ions, 17 with 32, 16 with 63, whose sum costs 3 us more; 13
+      // frames: 80 us and 8 for the sum with 7 groups, 78 and 10 with 12,
+      // 78 and 13 with 17
+      const int64_t chunks = (m + SG_CH - 1) / SG_CH;
+      const int64_t g = std::max<int64_t>(
+          1, std::min<int64_t>({(1024 + sf_blocks - 1) / sf_blocks, chunks, 32, cap}));
+      p.sf_ipg = (chunks + g - 1) / g * SG_CH;
+      p.sf_groups = (m + p.sf_ipg - 1) / p.sf_ipg;
+    } else {
+      p.sf_groups = groups_for(sf_blocks, m, cap, p.sf_ipg);
+    }
     // k splits of the back-projection: as many as fill every SIMD with three
     // wavefronts (its occupancy) without a fourth on some, at least 32 k each
     const int64_t per = bblocks * fgroups * (RB / 64);
@@ -1467,10 +1632,10 @@ RhsPlan rhs_plan_capped(const cpm_system *s, int64_t m, int64_t f, int64_t cap_s
                             std::max<int64_t>(1, kPartialCap / (f * n)), cap_ks});
     p.kper = (nk + ks - 1) / ks;
     p.ksplit = (nk + p.kper - 1) / p.kper;
-    if (planes && s->nplanes > 0) {
+    if (planes && s->layer.nodes > 0) {
       // column splits (multiples of 64 columns) until about 1024 workgroups
       p.bp_plane = true;
-      const int64_t wgs = (s->plane_ntiles + 3) / 4 * ((f + 31) / 32);
+      const int64_t wgs = (s->layer.ntiles + 3) / 4 * ((f + 31) / 32);
       const int64_t units = s->kset.ncols_pad / 64;
       int64_t cs = std::min<int64_t>({std::max<int64_t>(1, (1024 + wgs - 1) / wgs), units,
                                       std::max<int64_t>(1, kPartialCap / (f * n)), cap_ks});
@@ -1498,7 +1663,7 @@ RhsPlan rhs_plan_capped(const cpm_system *s, int64_t m, int64_t f, int64_t cap_s
   p.off_sg = 2 * nk * f;
   p.off_bp = p.off_sg + (p.sf_groups > 1 ? p.sf_groups * 2 * nk * f : 0);
   p.off_tp = p.off_bp + p.ksplit * f * n;
-  p.off_rs = p.off_tp + (p.bp_plane ? 2 * (int64_t)s->nplanes * s->kset.ncols_pad * f : 0);
+  p.off_rs = p.off_tp + (p.bp_plane ? 2 * (int64_t)s->layer.nodes * s->kset.ncols_pad * f : 0);
   p.off_m1 = p.off_rs + p.rs_groups * f * n;
   p.off_sorted = (p.off_m1 + f + 3) / 4 * 4;   // 32-byte aligned (double4)
   p.off_keys = p.off_sorted + (p.rs_cell ? 4 * f * m : 0);
@@ -1799,6 +1964,7 @@ hipError_t launch_rhs(hipStream_t st, const cpm_system *s, const double *ion_pos
   }
   if (p.ksplit > 0) {
     double *Sg = p.sf_groups > 1 ? buf + p.off_sg : S;
+    const int64_t sk = p.sf_groups > 1 ? 1 : f, sf = p.sf_groups > 1 ? nk : 1;
     const int64_t rblocks = (s->kset.nruns + RB - 1) / RB;
     // live timing (cpm_profile_enable): algorithmic flops 4 n_k m f
     hipEvent_t ea = nullptr, eb = nullptr;
@@ -1811,38 +1977,48 @@ hipError_t launch_rhs(hipStream_t st, const cpm_system *s, const double *ion_pos
     if (p.nu) {
       const hipError_t e = launch_nu(st, s, p, m, f, buf, S, ea, eb);
       if (e != hipSuccess) return e;
-    } else if (p.sf_gemm) {
+    } else if (p.sf_gemm)
       hipExtLaunchKernelGGL(sf_gemm_kernel,
-                            dim3((unsigned)f, (unsigned)(s->kset.ncols_pad / kSfTile),
-                                 (unsigned)p.sf_groups),
+                            dim3((unsigned)(f * p.sf_groups),
+                                 (unsigned)(s->kset.ncols_pad / kSfTile)),
                             dim3(256), 0, st, ea, eb, 0, ion_pos, ion_q, m, p.sf_ipg,
-                            reinterpret_cast<const int4 *>(s->kcol), ilx, ily, ilz, nk, f, Sg);
-    } else
+                            reinterpret_cast<const int4 *>(s->kcol), ilx, ily, ilz, nk, f, sk,
+                            sf, Sg);
+    else
       hipExtLaunchKernelGGL(structure_factor_kernel,
                             dim3((unsigned)rblocks, (unsigned)f, (unsigned)p.sf_groups), dim3(RB),
                             0, st, ea, eb, 0, ion_pos, ion_q, m, p.sf_ipg, s->kinfo, s->krun,
-                            s->kset.nruns, nk, ilx, ily, ilz, f, Sg);
-    if (p.sf_groups > 1) {
-      const int64_t len = 2 * nk * f;
-      hipLaunchKernelGGL(sum_groups_kernel, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, st,
-                         Sg, (int)p.sf_groups, len, S);
-    }
+                            s->kset.nruns, nk, ilx, ily, ilz, f, sk, sf, Sg);
+    if (p.sf_groups > 1)
+      hipLaunchKernelGGL(sum_groups_kernel,
+                         dim3((unsigned)((nk + SGT_K - 1) / SGT_K),
+                              (unsigned)((f + SGT_F - 1) / SGT_F)),
+                         dim3(256), 0, st, reinterpret_cast<const double2 *>(Sg),
+                         (int)p.sf_groups, nk, f, reinterpret_cast<double2 *>(S));
     if (p.bp_plane) {
       const int64_t ncp = s->kset.ncols_pad;
-      double *Tre = buf + p.off_tp, *Tim = Tre + (int64_t)s->nplanes * ncp * f;
+      const Layers &ly = s->layer;
+      double *Tre = buf + p.off_tp, *Tim = Tre + (int64_t)ly.nodes * ncp * f;
+      const int4 *kcol = reinterpret_cast<const int4 *>(s->kcol);
       hipLaunchKernelGGL(plane_table_kernel,
-                         dim3((unsigned)((ncp * f + PT_THREADS - 1) / PT_THREADS),
-                              (unsigned)s->nplanes),
-                         dim3(PT_THREADS), 0, st, (const double *)s->plane_uz,
-                         reinterpret_cast<const int4 *>(s->kcol), ncp, (const double *)s->kw,
-                         (const double *)S, f, s->kset.smax, Tre, Tim);
-      hipLaunchKernelGGL(plane_backproject_kernel,
-                         dim3((unsigned)((s->plane_ntiles + PB_WAVES - 1) / PB_WAVES),
-                              (unsigned)((f + 31) / 32), (unsigned)p.ksplit),
-                         dim3(64 * PB_WAVES), 0, st, (const double *)s->pos, n,
-                         (const int32_t *)s->plane_tile, (const int32_t *)s->plane_atom,
-                         s->plane_ntiles, reinterpret_cast<const int4 *>(s->kcol), ncp, p.kper,
-                         ilx, ily, (const double *)Tre, (const double *)Tim, f, bp);
+                         dim3((unsigned)(ncp / PT_WAVES), (unsigned)(ly.nodes_pad / 16),
+                              (unsigned)((f + 15) / 16)),
+                         dim3(64 * PT_WAVES), 0, st, reinterpret_cast<const double2 *>(ly.zt),
+                         ly.nodes, ly.nodes_pad, kcol, ncp, (const double *)s->kw,
+                         reinterpret_cast<const double2 *>(S), f, Tre, Tim);
+      const int nf = f > 16 ? 2 : 1;
+      const dim3 grid((unsigned)((ly.ntiles + PB_WAVES - 1) / PB_WAVES),
+                      (unsigned)((f + 16 * nf - 1) / (16 * nf)), (unsigned)p.ksplit);
+#define CPM_PLANE_BP(NF, MULTI)                                                                  \
+  hipLaunchKernelGGL((plane_backproject_kernel<NF, MULTI>), grid, dim3(64 * PB_WAVES), 0, st,    \
+                     (const double *)s->pos, n, reinterpret_cast<const int4 *>(ly.tile), ly.atom, \
+                     (const double *)ly.lw, ly.ntiles, kcol, ncp, p.kper, ilx, ily,              \
+                     (const double *)Tre, (const double *)Tim, f, bp)
+      if (nf == 1 && ly.multi) CPM_PLANE_BP(1, true);
+      else if (nf == 1) CPM_PLANE_BP(1, false);
+      else if (ly.multi) CPM_PLANE_BP(2, true);
+      else CPM_PLANE_BP(2, false);
+#undef CPM_PLANE_BP
     } else {
       const int64_t bblocks = (n + RB * BP_AT - 1) / (RB * BP_AT);
       hipLaunchKernelGGL(backproject_kernel<BP_AT>,
@@ -1872,6 +2048,45 @@ hipError_t launch_rhs(hipStream_t st, const cpm_system *s, const double *ion_pos
                      bp, (int)p.ksplit, rs, (int)p.rs_groups, n, f, chi, qsol_out, c0,
                      (const double *)m1, 4.0 * M_PI / s->vol, s->pos, b_out);
   return hipGetLastError();
+}
+
+// One device block for a system's layers: tiles, atoms, node z, tables.
+static int64_t layers_fixed(const LayerPlan &lp) {
+  const int64_t nt = (int64_t)lp.tile.size() / 4, nodes = (int64_t)lp.node_z.size();
+  return (2 * nt + nt * kPlaneTile / 2 + nodes + 1) / 2 * 2;
+}
+int64_t layers_elems(const LayerPlan &lp, int smax) {
+  const int64_t npad = ((int64_t)lp.node_z.size() + 15) / 16 * 16;
+  return layers_fixed(lp) + 2 * (smax + 1) * npad + lp.weights * kPlaneTile;
+}
+hipError_t set_layers(cpm_system *s, hipStream_t st, const LayerPlan &lp, double *d) {
+  const int64_t nt = (int64_t)lp.tile.size() / 4, nodes = (int64_t)lp.node_z.size();
+  const int64_t npad = (nodes + 15) / 16 * 16, smax = s->kset.smax;
+  std::vector<double> h(layers_fixed(lp), 0.0);
+  const int64_t oa = 2 * nt, oz = oa + nt * kPlaneTile / 2;
+  std::memcpy(h.data(), lp.tile.data(), sizeof(int32_t) * 4 * nt);
+  std::memcpy(h.data() + oa, lp.atom.data(), sizeof(int32_t) * kPlaneTile * nt);
+  std::memcpy(h.data() + oz, lp.node_z.data(), sizeof(double) * nodes);
+  Layers &out = s->layer;
+  out.tile = reinterpret_cast<int32_t *>(d);
+  out.atom = reinterpret_cast<int32_t *>(d + oa);
+  out.zt = d + h.size();
+  out.lw = out.zt + 2 * (smax + 1) * npad;
+  out.ntiles = nt;
+  out.nodes = (int)nodes;
+  out.nodes_pad = (int)npad;
+  out.multi = lp.weights > nt;
+  hipError_t e =
+      hipMemcpyAsync(d, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice, st);
+  if (e != hipSuccess) return e;
+  const int64_t work = std::max((smax + 1) * npad, nt * kPlaneTile);
+  hipLaunchKernelGGL(layer_tables_kernel, dim3((unsigned)((work + 255) / 256)), dim3(256), 0, st,
+                     (const double *)s->pos, 1.0 / s->box[2],
+                     reinterpret_cast<const int4 *>(out.tile), (const int32_t *)out.atom, nt,
+                     (const double *)(d + oz), (int)nodes, (int)npad, (int)smax,
+                     reinterpret_cast<double2 *>(out.zt), out.lw);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  return hipStreamSynchronize(st);   // the host copy goes out of scope
 }
 
 // Coefficients of erfc_pw. About x_j = (j + 1/2) / kErfcPer: c_0 = erfc(x_j)
