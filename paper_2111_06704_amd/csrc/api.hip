@@ -549,21 +549,32 @@ cpm_status cpm_build_E(const double *pos_host, int64_t n, const double *box_host
 
   // Reciprocal part A A^T in chunks of k-vectors whose phase matrix stays
   // under 24 GiB (or a third of the free memory): every chunk but the first
-  // adds to the lower tiles of E, so larger chunks re-read E less often.
+  // adds to the lower tiles of E, so larger chunks re-read E less often. It
+  // also stays under four times E (or 256 MiB): a build allocates and
+  // releases it, and the driver clears released memory at about 0.1 TB/s,
+  // so that builds in a row wait for it (4608 atoms with 1.5 GB: 0.4 ms more
+  // in hipFree, and from some hundred builds on stalls of 10 ms and more;
+  // three chunks cost 0.2 ms for E).
   // finalize_kernel writes every entry of E (padding included), so E needs
   // no clearing.
+  double *A = nullptr, *P = nullptr;   // phase matrix, planes of the split k range
+  int32_t *tiles = nullptr;
+  int parts = 1;
+  auto release = [&]() {
+    for (void *q : {(void *)A, (void *)P, (void *)tiles})
+      if (q) (void)hipFree(q);
+  };
   if (nk > 0) {
     size_t free_b = 0, total_b = 0;
     (void)hipMemGetInfo(&free_b, &total_b);
     size_t budget = std::min<size_t>((size_t)24 << 30, free_b / 3);
+    budget = std::min<size_t>(budget, std::max<size_t>((size_t)256 << 20, 4 * sizeof(double) * ld * ld));
     int64_t kc = (int64_t)(budget / (sizeof(double) * 2 * (size_t)ld));
     kc = std::max<int64_t>(8, kc / 8 * 8);
     // equal chunks (the last one is not padded with zero columns)
     const int64_t nchunks = (nk + kc - 1) / kc;
     kc = round_up((nk + nchunks - 1) / nchunks, 8);
     const int64_t lda = 2 * kc;
-    double *A = nullptr;
-    int32_t *tiles = nullptr;
     const std::vector<int32_t> order_t = syrk_tile_order(ld / 128);
     if ((int64_t)order_t.size() != (ld / 128) * (ld / 128 + 1)) {
       set_error("internal: tile list size");
@@ -577,14 +588,17 @@ cpm_status cpm_build_E(const double *pos_host, int64_t n, const double *box_host
     if (hipMalloc((void **)&A, sizeof(double) * (size_t)ld * lda) != hipSuccess ||
         hipMalloc((void **)&tiles, sizeof(int32_t) * order_t.size()) != hipSuccess) {
       (void)hipGetLastError();
-      if (A) (void)hipFree(A);
+      release();
       set_error("phase matrix allocation failed");
       return fail(CPM_ENOMEM);
     }
-    auto release = [&]() {
-      (void)hipFree(A);
-      (void)hipFree(tiles);
-    };
+    parts = syrk_splits(ld, round_up(2 * kc, 16));
+    if (parts > 1 &&
+        hipMalloc((void **)&P, sizeof(double) * (parts - 1) * syrk_plane_elems(ld)) != hipSuccess) {
+      (void)hipGetLastError();
+      P = nullptr;
+      parts = 1;
+    }
     hipError_t e = hipMemcpyAsync(tiles, order_t.data(), sizeof(int32_t) * order_t.size(),
                                   hipMemcpyHostToDevice, st);
     for (int64_t k0 = 0; k0 < nk && e == hipSuccess; k0 += kc) {
@@ -600,8 +614,8 @@ cpm_status cpm_build_E(const double *pos_host, int64_t n, const double *box_host
         eb = r.b;
       }
       if (e == hipSuccess)
-        e = launch_syrk_lower(st, A, round_up(2 * kcur, 16), tiles, ld, s->E64, ld, k0 > 0, ea,
-                              eb);
+        e = launch_syrk_lower(st, A, round_up(2 * kcur, 16), tiles, ld, s->E64, ld, P, parts,
+                              k0 > 0, ea, eb);
       if (progress && e == hipSuccess) {
         e = hipStreamSynchronize(st);
         std::fprintf(stderr, "cpm_build_E: k-vectors %lld of %lld done (%.1f s)\n",
@@ -616,15 +630,16 @@ cpm_status cpm_build_E(const double *pos_host, int64_t n, const double *box_host
       set_error(std::string("E assembly launch failed: ") + hipGetErrorString(e));
       return fail(CPM_EDEVICE);
     }
-    BUILD_CHECK(hipStreamSynchronize(st));
-    release();
   } else {
     BUILD_CHECK(hipMemsetAsync(s->E64, 0, sizeof(double) * ld * ld, st));
   }
-  BUILD_CHECK(launch_finalize(st, s->pos, s->width, s->rs_width, n, ld, s->box, beta, s->rcut,
-                              s->slab, s->E64, s->E32, s->E16));
-  BUILD_CHECK(launch_diag_inverse(st, s->E64, n, ld, s->dinv));
-  BUILD_CHECK(hipStreamSynchronize(st));
+  hipError_t e = launch_finalize(st, s->pos, s->width, s->rs_width, n, ld, s->box, beta, s->rcut,
+                                 s->slab, P, parts - 1, s->E64, s->E32, s->E16);
+  if (e == hipSuccess) e = launch_diag_inverse(st, s->E64, n, ld, s->dinv);
+  const hipError_t done = hipStreamSynchronize(st);
+  release();
+  BUILD_CHECK(e);
+  BUILD_CHECK(done);
 #undef BUILD_CHECK
 
   // d' = E^-1 1 is solved on first use (cpm_solve, cpm_get_dprime, ...):

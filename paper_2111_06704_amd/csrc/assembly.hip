@@ -81,18 +81,26 @@ __device__ inline void tri_index(int64_t t, int64_t &ti, int64_t &tj) {
 // of the list and its concurrent tiles share rows of A in its L2.
 // The whole tile is written (diagonal tiles included); the upper triangle
 // of E is filled from the lower one by finalize_kernel.
+// Grid y splits the stages: part 0 writes E, part q > 0 the packed tile
+// (row-major triangle order) of plane q - 1 of P, which finalize_kernel adds.
+// Few tiles would otherwise leave most of the chip idle in the last round
+// (rule in syrk_splits).
 __global__ __launch_bounds__(256, 2) void syrk_lower_kernel(const double *__restrict__ A, int64_t nrows,
                                                          int64_t kdim,
                                                          const int32_t *__restrict__ tiles,
                                                          int64_t ntiles, int64_t per,
                                                          double *__restrict__ E, int64_t lde,
-                                                         int accumulate) {
+                                                         double *__restrict__ P, int accumulate) {
   __shared__ double sI[2][SY_KB][SY_LDP];
   __shared__ double sJ[2][SY_KB][SY_LDP];
   const int64_t b = blockIdx.x;
   const int64_t L = (b % 8) * per + b / 8;
   if (L >= ntiles) return;
-  const int64_t I0 = (int64_t)tiles[2 * L] * SY_TILE, J0 = (int64_t)tiles[2 * L + 1] * SY_TILE;
+  const int64_t ti = tiles[2 * L], tj = tiles[2 * L + 1];
+  const int64_t I0 = ti * SY_TILE, J0 = tj * SY_TILE;
+  const int64_t stages = kdim / SY_KB;
+  const int64_t kbeg = stages * blockIdx.y / gridDim.y * SY_KB,
+                kend = stages * (blockIdx.y + 1) / gridDim.y * SY_KB;
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
   const int wr = wave >> 1, wc = wave & 1;
@@ -129,12 +137,14 @@ __global__ __launch_bounds__(256, 2) void syrk_lower_kernel(const double *__rest
     sJ[buf][kb + 6][lrow] = vj1.z; sJ[buf][kb + 7][lrow] = vj1.w;
   };
 
-  gload(0);
-  sstore(0);
+  if (kbeg < kend) {
+    gload(kbeg);
+    sstore(0);
+  }
   __syncthreads();
   int buf = 0;
-  for (int64_t k0 = 0; k0 < kdim; k0 += SY_KB) {
-    const bool more = k0 + SY_KB < kdim;
+  for (int64_t k0 = kbeg; k0 < kend; k0 += SY_KB) {
+    const bool more = k0 + SY_KB < kend;
     if (more) gload(k0 + SY_KB);
 #pragma unroll
     for (int ks = 0; ks < SY_KB / 4; ++ks) {
@@ -155,6 +165,12 @@ __global__ __launch_bounds__(256, 2) void syrk_lower_kernel(const double *__rest
     buf ^= 1;
   }
 
+  double *out = E + I0 * lde + J0;
+  int64_t ldo = lde;
+  if (blockIdx.y > 0) {
+    out = P + ((blockIdx.y - 1) * ntiles + ti * (ti + 1) / 2 + tj) * (SY_TILE * SY_TILE);
+    ldo = SY_TILE;
+  }
   // v_mfma_f64_16x16x4f64 output: D[i][j] lives in lane j + 16 * (i % 4),
   // register i / 4 (row i = 4 * register + lane / 16); each register of a
   // block is 4 rows x 128 contiguous bytes.
@@ -164,9 +180,9 @@ __global__ __launch_bounds__(256, 2) void syrk_lower_kernel(const double *__rest
     for (int y = 0; y < 4; ++y)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int64_t row = I0 + wr * 64 + x * 16 + 4 * v + lg;
-        const int64_t col = J0 + wc * 64 + y * 16 + lr;
-        double *p = E + row * lde + col;
+        const int64_t row = wr * 64 + x * 16 + 4 * v + lg;
+        const int64_t col = wc * 64 + y * 16 + lr;
+        double *p = out + row * ldo + col;
         *p = accumulate ? *p + acc[x][y][v] : acc[x][y][v];
       }
 }
@@ -228,7 +244,7 @@ constexpr int FZ_B = 64;   // finalize block edge
 
 // One workgroup per lower 64x64 block (bi >= bj) of the padded ld x ld
 // matrix. Each entry of the block's lower part takes the reciprocal sum the
-// contraction left there and adds the real-space sum, c0, the Eq. 39 term
+// contraction left there and in its planes P, and adds the real-space sum, c0, the Eq. 39 term
 // and the diagonal terms; entries outside [0, n)^2 become 0. The block is
 // written in place and, through an LDS transpose, to its mirror block
 // above the diagonal, so both stores are row-contiguous and E is exactly
@@ -237,10 +253,15 @@ __global__ __launch_bounds__(256) void finalize_kernel(
     const double *__restrict__ pos, const double *__restrict__ width,
     const double *__restrict__ rs_width, int64_t n, int64_t ld,
     double lx, double ly, double lz, double beta, double rcut, double c0, double slab,
-    double *__restrict__ E64, float *__restrict__ E32, uint16_t *__restrict__ E16) {
+    const double *__restrict__ P, int planes, double *__restrict__ E64,
+    float *__restrict__ E32, uint16_t *__restrict__ E16) {
   __shared__ double tile[FZ_B][FZ_B + 1];
   int64_t bi, bj;
   tri_index(blockIdx.x, bi, bj);
+  constexpr int Q = SY_TILE / FZ_B;   // blocks per tile edge
+  const int64_t T = ld / SY_TILE, plane = T * (T + 1) / 2 * (SY_TILE * SY_TILE);
+  const int64_t pt = ((bi / Q) * (bi / Q + 1) / 2 + bj / Q) * (SY_TILE * SY_TILE) +
+                     (bi % Q * FZ_B) * SY_TILE + bj % Q * FZ_B;
   const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
   const int64_t j = bj * FZ_B + c;
   for (int r = r0; r < FZ_B; r += 4) {
@@ -249,7 +270,9 @@ __global__ __launch_bounds__(256) void finalize_kernel(
     double e = 0.0;
     if (i < n && j < n) {
       const int64_t idx = i * ld + j;
-      e = E64[idx] + c0 + real_space_entry(pos, rs_width, j, i, lx, ly, lz, beta, rcut);
+      double rec = E64[idx];
+      for (int q = 0; q < planes; ++q) rec += P[q * plane + pt + r * SY_TILE + c];
+      e = rec + c0 + real_space_entry(pos, rs_width, j, i, lx, ly, lz, beta, rcut);
       // slab geometry (Eq. 39 in its definite form): (4 pi / V) z_i z_j
       if (slab != 0.0) e += slab * (pos[3 * j + 2] * pos[3 * i + 2]);
       if (i == j) {
@@ -310,30 +333,56 @@ std::vector<int32_t> syrk_tile_order(int64_t T) {
   return t;
 }
 
+// Parts of the k range: the chip holds 512 workgroups (two per CU), so
+// `tiles` of them take ceil(tiles parts / 512) / parts rounds; more parts
+// also cost their planes' traffic (about 1 % of a round each at 41 000
+// columns). 4608 atoms, 666 tiles,
+// 41 000 columns: 15.6 ms undivided, 13.7 with 3 parts (the planes cost
+// finalize_kernel 0.04), 14.6 with 5, 13.5 with 8 (0.15).
+int syrk_splits(int64_t ld, int64_t kdim) {
+  const int64_t T = ld / SY_TILE, tiles = T * (T + 1) / 2;
+  int best = 1;
+  double cost = 1e300;
+  for (int q = 1; q <= 16 && q * 8 * SY_KB <= kdim; ++q) {
+    const double c = (double)((tiles * q + 511) / 512) / q + 400.0 * (q - 1) / (double)kdim;
+    if (c < cost) {
+      cost = c;
+      best = q;
+    }
+  }
+  return tiles > 16 * 512 ? 1 : best;
+}
+int64_t syrk_plane_elems(int64_t ld) {
+  const int64_t T = ld / SY_TILE;
+  return T * (T + 1) / 2 * (SY_TILE * SY_TILE);
+}
+
 hipError_t launch_syrk_lower(hipStream_t st, const double *A, int64_t kdim,
-                             const int32_t *tiles, int64_t ld, double *E, int64_t lde,
-                             bool accumulate, hipEvent_t ev_start, hipEvent_t ev_stop) {
+                             const int32_t *tiles, int64_t ld, double *E, int64_t lde, double *P,
+                             int parts, bool accumulate, hipEvent_t ev_start,
+                             hipEvent_t ev_stop) {
   const int64_t T = ld / SY_TILE;
   const int64_t ntiles = T * (T + 1) / 2;
   const int64_t per = (ntiles + 7) / 8;
   if (kdim % SY_KB != 0 || kdim < SY_KB || ld % SY_TILE != 0) return hipErrorInvalidValue;
-  hipExtLaunchKernelGGL(syrk_lower_kernel, dim3((unsigned)(8 * per)), dim3(256), 0, st, ev_start,
-                        ev_stop, 0, A, ld, kdim, tiles, ntiles, per, E, lde, accumulate ? 1 : 0);
+  hipExtLaunchKernelGGL(syrk_lower_kernel, dim3((unsigned)(8 * per), (unsigned)parts), dim3(256), 0,
+                        st, ev_start, ev_stop, 0, A, ld, kdim, tiles, ntiles, per, E, lde, P,
+                        accumulate ? 1 : 0);
   return hipGetLastError();
 }
 
 hipError_t launch_finalize(hipStream_t st, const double *pos, const double *width,
                            const double *rs_width, int64_t n, int64_t ld, const double box[3],
-                           double beta, double rcut, bool slab, double *E64, float *E32,
-                           uint16_t *E16) {
+                           double beta, double rcut, bool slab, const double *P, int planes,
+                           double *E64, float *E32, uint16_t *E16) {
   const double vol = box[0] * box[1] * box[2];
   const double c0 = -M_PI / (vol * beta * beta);
   const double cs = slab ? 4.0 * M_PI / vol : 0.0;
   if (ld % FZ_B != 0) return hipErrorInvalidValue;
   const int64_t B = ld / FZ_B;
   hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)(B * (B + 1) / 2)), dim3(256), 0, st, pos,
-                     width, rs_width, n, ld, box[0], box[1], box[2], beta, rcut, c0, cs, E64,
-                     E32, E16);
+                     width, rs_width, n, ld, box[0], box[1], box[2], beta, rcut, c0, cs, P,
+                     planes, E64, E32, E16);
   return hipGetLastError();
 }
 

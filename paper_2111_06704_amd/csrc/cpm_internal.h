@@ -326,16 +326,19 @@ hipError_t launch_phase_matrix(hipStream_t st, const double *pos, int64_t n, int
 // lower-triangular tile list of the contraction (pairs ti >= tj, in the
 // order the kernel walks them) for T = ld / 128 tile rows
 std::vector<int32_t> syrk_tile_order(int64_t T);
+int syrk_splits(int64_t ld, int64_t kdim);
+int64_t syrk_plane_elems(int64_t ld);
 hipError_t launch_syrk_lower(hipStream_t st, const double *A, int64_t kdim,
-                             const int32_t *tiles, int64_t ld, double *E, int64_t lde,
-                             bool accumulate, hipEvent_t ev_start, hipEvent_t ev_stop);
+                             const int32_t *tiles, int64_t ld, double *E, int64_t lde, double *P,
+                             int parts, bool accumulate, hipEvent_t ev_start,
+                             hipEvent_t ev_stop);
 // width: the Gaussian self-energy of the diagonal; rs_width: the screening
 // of the real-space pair terms (the same array unless the point-charge
 // simplification sets it to +inf)
 hipError_t launch_finalize(hipStream_t st, const double *pos, const double *width,
                            const double *rs_width, int64_t n, int64_t ld, const double box[3],
-                           double beta, double rcut, bool slab, double *E64, float *E32,
-                           uint16_t *E16);
+                           double beta, double rcut, bool slab, const double *P, int planes,
+                           double *E64, float *E32, uint16_t *E16);
 
 // ---- rhs.hip
 // erfc on [0, 6.5): kErfcIntervals intervals of width 1 / kErfcPer, a
