@@ -32,9 +32,8 @@ Kset make_kset(const double box[3], double beta, double kmax) {
                      kz = 2.0 * M_PI * nz / box[2];
         const double k2 = kx * kx + ky * ky + kz * kz;
         if (k2 > k2max) continue;
-        ks.n.push_back(nx);
-        ks.n.push_back(ny);
-        ks.n.push_back(nz);
+        const int32_t nn[3] = {nx, ny, nz};
+        ks.n.insert(ks.n.end(), nn, nn + 3);
         ks.w.push_back(2.0 * (4.0 * M_PI / vol) * std::exp(-k2 / (4.0 * beta * beta)) / k2);
       }
   ks.nk = (int64_t)ks.w.size();
@@ -421,27 +420,39 @@ cpm_status cpm_build_E(const double *pos_host, int64_t n, const double *box_host
     const double tol2 = 1e-12;   // (1e-6 A)^2
     int nc[3];
     for (int d = 0; d < 3; ++d) nc[d] = std::max(1, std::min(256, (int)(box_host[d] / 2.0)));
-    std::vector<std::vector<int64_t>> cells((size_t)nc[0] * nc[1] * nc[2]);
+    // per cell a list of its atoms in ascending order; a pair is in one cell
+    // or within the tolerance of the face between two
+    std::vector<int32_t> head((size_t)nc[0] * nc[1] * nc[2], -1), next(n);
     auto cell_of = [&](int64_t i, int d) {
       int c = (int)(pos[3 * i + d] / box_host[d] * nc[d]);
       return std::min(std::max(c, 0), nc[d] - 1);
     };
-    for (int64_t i = 0; i < n; ++i)
-      cells[((size_t)cell_of(i, 0) * nc[1] + cell_of(i, 1)) * nc[2] + cell_of(i, 2)].push_back(i);
+    for (int64_t i = n - 1; i >= 0; --i) {
+      int32_t &h = head[((size_t)cell_of(i, 0) * nc[1] + cell_of(i, 1)) * nc[2] + cell_of(i, 2)];
+      next[i] = h;
+      h = (int32_t)i;
+    }
     for (int64_t i = 0; i < n; ++i) {
-      const int ci[3] = {cell_of(i, 0), cell_of(i, 1), cell_of(i, 2)};
-      for (int a = -1; a <= 1; ++a)
-        for (int b = -1; b <= 1; ++b)
-          for (int c = -1; c <= 1; ++c) {
+      int ci[3], lo[3], hi[3];
+      for (int d = 0; d < 3; ++d) {
+        ci[d] = cell_of(i, d);
+        const double u = pos[3 * i + d] / box_host[d] * nc[d] - ci[d];
+        const double near = 2e-6 / box_host[d] * nc[d] + 1e-9;
+        lo[d] = u < near ? -1 : 0;
+        hi[d] = u > 1.0 - near ? 1 : 0;
+      }
+      for (int a = lo[0]; a <= hi[0]; ++a)
+        for (int b = lo[1]; b <= hi[1]; ++b)
+          for (int c = lo[2]; c <= hi[2]; ++c) {
             const int cx = (ci[0] + a + nc[0]) % nc[0], cy = (ci[1] + b + nc[1]) % nc[1],
                       cz = (ci[2] + c + nc[2]) % nc[2];
-            for (int64_t j : cells[((size_t)cx * nc[1] + cy) * nc[2] + cz]) {
+            for (int64_t j = head[((size_t)cx * nc[1] + cy) * nc[2] + cz]; j >= 0; j = next[j]) {
               if (j <= i) continue;
-              double d2 = 0;
-              for (int d = 0; d < 3; ++d) {
-                double dx = pos[3 * j + d] - pos[3 * i + d];
-                dx -= box_host[d] * std::nearbyint(dx / box_host[d]);
-                d2 += dx * dx;
+              double d2 = 0;   // wrapped positions: at most one box edge apart
+              for (int d = 0; d < 3 && d2 < tol2; ++d) {
+                const double dx = std::fabs(pos[3 * j + d] - pos[3 * i + d]);
+                const double w = std::min(dx, box_host[d] - dx);
+                d2 += w * w;
               }
               if (d2 < tol2) {
                 set_error("atoms " + std::to_string(i) + " and " + std::to_string(j) +
@@ -512,8 +523,11 @@ cpm_status cpm_build_E(const double *pos_host, int64_t n, const double *box_host
     }                                                                      \
   } while (0)
 
-  std::vector<double> etab(kErfcTab);
-  erfc_table(etab.data());
+  static const std::vector<double> etab = [] {
+    std::vector<double> t(kErfcTab);
+    erfc_table(t.data());
+    return t;
+  }();
   BUILD_CHECK(hipMemcpyAsync(s->erfc_tab, etab.data(), sizeof(double) * kErfcTab,
                              hipMemcpyHostToDevice, st));
   BUILD_CHECK(hipMemcpyAsync(s->pos, pos.data(), sizeof(double) * 3 * n, hipMemcpyHostToDevice, st));
@@ -534,16 +548,6 @@ cpm_status cpm_build_E(const double *pos_host, int64_t n, const double *box_host
                                hipMemcpyHostToDevice, st));
     BUILD_CHECK(hipMemcpyAsync(s->krun, s->kset.runs.data(), sizeof(int32_t) * 2 * s->kset.nruns,
                                hipMemcpyHostToDevice, st));
-  }
-  const std::vector<int32_t> order = spatial_order(pos, n);
-  BUILD_CHECK(hipMemcpyAsync(s->atom_order, order.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice,
-                             st));
-  if (nk > 0 && s->kset.smax <= kMaxPlaneS) {
-    const LayerPlan lp = plan_layers(pos, n, box_host, order, s->kset);
-    if (!lp.tile.empty()) {
-      if ((rc = dev_alloc(s, &s->layer.buf, layers_elems(lp, s->kset.smax)))) return fail(rc);
-      BUILD_CHECK(set_layers(s, st, lp, s->layer.buf));
-    }
   }
   BUILD_CHECK(hipMemsetAsync(s->qchi, 0, sizeof(double) * ld, st));
 
@@ -633,13 +637,24 @@ cpm_status cpm_build_E(const double *pos_host, int64_t n, const double *box_host
   } else {
     BUILD_CHECK(hipMemsetAsync(s->E64, 0, sizeof(double) * ld * ld, st));
   }
+  // the GPU is at work for milliseconds from here on: host planning now, its
+  // copies after the last kernel (pageable memory makes them wait)
+  const std::vector<int32_t> order = spatial_order(pos, n);
+  LayerPlan lp;
+  if (nk > 0 && s->kset.smax <= kMaxPlaneS) lp = plan_layers(pos, n, box_host, order, s->kset);
   hipError_t e = launch_finalize(st, s->pos, s->width, s->rs_width, n, ld, s->box, beta, s->rcut,
                                  s->slab, P, parts - 1, s->E64, s->E32, s->E16);
   if (e == hipSuccess) e = launch_diag_inverse(st, s->E64, n, ld, s->dinv);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(s->atom_order, order.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, st);
   const hipError_t done = hipStreamSynchronize(st);
   release();
   BUILD_CHECK(e);
   BUILD_CHECK(done);
+  if (!lp.tile.empty()) {
+    if ((rc = dev_alloc(s, &s->layer.buf, layers_elems(lp, s->kset.smax)))) return fail(rc);
+    BUILD_CHECK(set_layers(s, st, lp, s->layer.buf));
+  }
 #undef BUILD_CHECK
 
   // d' = E^-1 1 is solved on first use (cpm_solve, cpm_get_dprime, ...):
