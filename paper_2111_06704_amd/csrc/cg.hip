@@ -1164,7 +1164,7 @@ __global__ __launch_bounds__(RED_THREADS) void colsum_kernel(const double *__res
 }
 
 // Preconditioner apply (Sec. III.B.2): z = P r with P in its block-dense
-// form: tile t (one workgroup) holds the kPcTile rows of atoms
+// form: tile t (a workgroup, or one per column group) holds the kPcTile rows of atoms
 // order[kPcTile t ..] over U_t, the union of their columns, so z of the tile
 // is the product [rows x |U_t|] . [|U_t| x cols] on the FP64 matrix cores
 // and every row of r is read once per tile (where a row-by-row sparse
@@ -1186,12 +1186,19 @@ __global__ __launch_bounds__(RED_THREADS) void colsum_kernel(const double *__res
 // tile: 16 read more of r, 64 leave CUs idle at N = 4608 and need too many
 // registers at 64 columns. Measured per apply, N = 4608, r_cut 12 A, 16
 // columns: 10 us (11 with 16-row tiles, 17 with 64; one wave per row of an
-// ELL form took 16); N = 5275, r_cut 10 A, 48 columns: 24 us (ELL 37);
+// ELL form took 16); N = 5275, r_cut 10 A, 48 columns: 17 us (ELL 37);
 // N = 32768, r_cut 14 A, 64 columns: 162 us (535 when every step waited for
 // its three dependent loads and each wave read r for 16 of 64 rows).
-// Waves (small / large systems): 16 / 8 at 16 and 32 columns (10.1 against
-// 10.8 and 81.4 against 83.7 us), 8 / 4 at 48 and 64 (28.4 against 31.0 and
-// 162 against 176 us); small: fewer than two tiles per CU.
+// Small systems (fewer than two tiles per CU): a workgroup per tile and
+// column group, consecutive ones of a tile on one XCD (workgroup b goes to
+// XCD b mod 8) so that its L2 reads the tile once; 16 waves for one group
+// (10.1 against 10.8 us with 8), 8 otherwise. With all groups in a workgroup
+// the CUs without a tile stay idle: N = 5275, r_cut 10 A, 48 columns 24.8 us
+// against 17.1 (19.9 with 16 waves); the whole apply at N = 1536 and 64
+// columns 42 against 28, at N = 16128 and 48 columns 79 against 69 us. Large
+// systems: all groups, 8 waves at 16 and 32 columns (81.4 us against 83.7
+// with 16), 4 at 48 and 64 (N = 32768, 64 columns: 162 us, 176 with 8; a
+// workgroup per group 207).
 //
 // Active columns only (scal == nullptr: all); set_p: p = z; with the Eq. 37
 // fill z += gap (1^T r). bpart (may be null): per tile and column (r.r, r.z),
@@ -1200,7 +1207,6 @@ __global__ __launch_bounds__(RED_THREADS) void colsum_kernel(const double *__res
 // row-interleaved array instead (the coarse correction's inner apply).
 constexpr int PC_RT = kPcTile / 16;
 constexpr int64_t kPcFewTiles = 512;
-template <int NG> constexpr int pc_waves(bool few) { return (NG <= 2 ? 8 : 4) * (few ? 2 : 1); }
 template <int NG> constexpr int pc_batch() { return NG <= 2 ? 2 : NG == 3 ? 6 : 4; }
 template <int NG> constexpr int pc_occ() { return NG <= 2 ? 4 : 2; }   // waves per SIMD
 
@@ -1212,7 +1218,7 @@ precond_block_kernel(
     const double *__restrict__ blk, const int32_t *__restrict__ order, int64_t ld, int64_t n,
     int cols, const double *__restrict__ scal, int slot, double *__restrict__ bpart, int set_p,
     double gap, const double *__restrict__ rsum, const int *__restrict__ gate,
-    double *__restrict__ zt) {
+    double *__restrict__ zt, int ntiles, int parts) {
   constexpr int RT = PC_RT, UB = pc_batch<NG>(), ROWS = kPcTile;
   constexpr int ITEMS = RT * 4;                       // (row block, register) pairs of a group
   constexpr int PER = (ITEMS + W - 1) / W;            // pairs of a wave in the epilogue
@@ -1222,13 +1228,17 @@ precond_block_kernel(
   const int go = gate != nullptr ? *gate : 1;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int lr = lane & 15, lg = lane >> 4;
-  const int64_t tile = blockIdx.x;
+  // 8 consecutive tiles by `parts` runs of NG column groups
+  const int oct = blockIdx.x / (8 * parts), in8 = blockIdx.x - oct * (8 * parts);
+  const int64_t tile = oct * 8 + (in8 & 7);
+  const int g0 = (in8 >> 3) * NG;
+  if (tile >= ntiles) return;
   const int64_t k0 = uoff[tile];
   const int steps = (int)(uoff[tile + 1] - k0) >> 2;   // >= 1
   const int s0 = wave * steps / W, ns = (wave + 1) * steps / W - s0;
   const int32_t *U = uidx + k0 + lg;
   const double *A = blk + (k0 + lg) * ROWS + lr * RT;
-  const double *B = rt + lr;
+  const double *B = rt + (int64_t)g0 * ld * kColGroup + lr;
   // the wave's output rows (atom, -1 past the end)
   int64_t row[PER];
 #pragma unroll
@@ -1251,9 +1261,9 @@ precond_block_kernel(
     double sa[NG], sh[NG], sr[NG];
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
-      sa[g] = scal[S_ACT * cols + g * kColGroup + lr];
-      sh[g] = scal[(S_HOLD0 + slot) * cols + g * kColGroup + lr];
-      sr[g] = scal[S_RST * cols + g * kColGroup + lr];
+      sa[g] = scal[S_ACT * cols + (g0 + g) * kColGroup + lr];
+      sh[g] = scal[(S_HOLD0 + slot) * cols + (g0 + g) * kColGroup + lr];
+      sr[g] = scal[S_RST * cols + (g0 + g) * kColGroup + lr];
     }
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
@@ -1263,7 +1273,7 @@ precond_block_kernel(
   }
   if (rsum != nullptr)
 #pragma unroll
-    for (int g = 0; g < NG; ++g) add[g] = gap * rsum[g * kColGroup + lr];
+    for (int g = 0; g < NG; ++g) add[g] = gap * rsum[(g0 + g) * kColGroup + lr];
   d4 acc[RT][NG];
 #pragma unroll
   for (int q = 0; q < RT; ++q)
@@ -1329,12 +1339,12 @@ precond_block_kernel(
   // register i / 4
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
-    const int c = g * kColGroup + lr;
+    const int c = (g0 + g) * kColGroup + lr;
     double ri[PER];
     if (zt == nullptr)
 #pragma unroll
       for (int q = 0; q < PER; ++q)
-        ri[q] = rt[((int64_t)g * ld + (row[q] < 0 ? 0 : row[q])) * kColGroup + lr];
+        ri[q] = rt[((int64_t)(g0 + g) * ld + (row[q] < 0 ? 0 : row[q])) * kColGroup + lr];
 #pragma unroll
     for (int q = 0; q < RT; ++q)
 #pragma unroll
@@ -1352,7 +1362,7 @@ precond_block_kernel(
     if (zt != nullptr) {
 #pragma unroll
       for (int q = 0; q < PER; ++q)
-        if (row[q] >= 0) zt[((int64_t)g * ld + row[q]) * kColGroup + lr] = zi[q];
+        if (row[q] >= 0) zt[((int64_t)(g0 + g) * ld + row[q]) * kColGroup + lr] = zi[q];
       __syncthreads();
       continue;
     }
@@ -1382,7 +1392,7 @@ precond_block_kernel(
       double t = red[0][cc][s2];
 #pragma unroll
       for (int w = 1; w < W; ++w) t += red[w][cc][s2];
-      bpart[((int64_t)(g * kColGroup + cc) * gridDim.x + tile) * 2 + s2] = t;
+      bpart[((int64_t)((g0 + g) * kColGroup + cc) * ntiles + tile) * 2 + s2] = t;
     }
   }
 }
@@ -2224,18 +2234,24 @@ void launch_local(hipStream_t st, const cpm_system *s, const Precond &pc, const 
                   double *z, VT *p, int64_t cols, const double *scal, int slot, double *bpart,
                   bool set_p, const double *rsum, const int *gate, double *zt) {
   const int64_t ld = s->ld, n = s->n;
-  const dim3 grid((unsigned)pc.ntiles);
-#define CPM_PB(NGV, FEW)                                                                       \
-  hipLaunchKernelGGL((precond_block_kernel<VT, NGV, pc_waves<NGV>(FEW)>), grid,               \
-                     dim3(64 * pc_waves<NGV>(FEW)), 0, st, rt, z, p, (const int64_t *)pc.uoff, \
-                     (const int32_t *)pc.uidx, (const double *)pc.blk, s->atom_order, ld, n,   \
-                     (int)cols, scal, slot, bpart, set_p ? 1 : 0, pc.gap, rsum, gate, zt)
-  const bool few = pc.ntiles < kPcFewTiles;
-  switch (cols / kColGroup) {
-    case 1: if (few) CPM_PB(1, true); else CPM_PB(1, false); break;
-    case 2: if (few) CPM_PB(2, true); else CPM_PB(2, false); break;
-    case 3: if (few) CPM_PB(3, true); else CPM_PB(3, false); break;
-    default: if (few) CPM_PB(4, true); else CPM_PB(4, false); break;
+  const int groups = (int)(cols / kColGroup);
+#define CPM_PB(NGV, W)                                                                         \
+  hipLaunchKernelGGL((precond_block_kernel<VT, NGV, W>),                                       \
+                     dim3((unsigned)((pc.ntiles + 7) / 8 * 8 * (groups / NGV))), dim3(64 * W), \
+                     0, st, rt, z, p, (const int64_t *)pc.uoff, (const int32_t *)pc.uidx,      \
+                     (const double *)pc.blk, s->atom_order, ld, n, (int)cols, scal, slot,      \
+                     bpart, set_p ? 1 : 0, pc.gap, rsum, gate, zt, (int)pc.ntiles,             \
+                     groups / NGV)
+  if (pc.ntiles < kPcFewTiles) {
+    if (groups == 1) CPM_PB(1, 16);
+    else CPM_PB(1, 8);
+  } else {
+    switch (groups) {
+      case 1: CPM_PB(1, 8); break;
+      case 2: CPM_PB(2, 8); break;
+      case 3: CPM_PB(3, 4); break;
+      default: CPM_PB(4, 4); break;
+    }
   }
 #undef CPM_PB
 }
