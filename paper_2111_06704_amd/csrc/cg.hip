@@ -1437,47 +1437,61 @@ __global__ __launch_bounds__(256) void coarse_restrict_kernel(
 
 // out = E_c^-1 in for 16 NG columns on the FP64 matrix cores: out[c * mp + t]
 // = sum_s eci[s * mp + t] in[c * mp + s] (E_c^-1 is symmetric). Workgroup:
-// 16 patches t and every column; its four waves split s in quarters and add
-// their results in LDS in a fixed order. Lane (lr, lg) gives A = eci(s + lg,
-// t0 + lr) and, per group, B = in(column 16 g + lr, s + lg). mode 0: g1 = out
-// and its FP32 copy g1f; mode 1: dg = g1 - out.
+// 16 patches t and every column; its CS_WAVES waves split s and add their
+// results in LDS in a fixed order. Lane (lr, lg) gives A = eci(s + lg,
+// t0 + lr) and, per group, B = in(column 16 g + lr, s + lg); mp is a multiple
+// of 32 CS_WAVES, and the loads of eight steps are under way together (the
+// few workgroups wait for memory: with 512 patches and 64 columns 27 us a step
+// at a time, 21 now). mode 0: g1 = out and its FP32 copy
+// g1f[(t * 16 + lr) * NG + g]; mode 1: dg = g1 - out.
+constexpr int CS_WAVES = 8;
 template <int NG>
-__global__ __launch_bounds__(256) void coarse_solve_kernel(
+__global__ __launch_bounds__(64 * CS_WAVES) void coarse_solve_kernel(
     const double *__restrict__ eci, int64_t mp, const double *__restrict__ in,
     double *__restrict__ g1, float *__restrict__ g1f, double *__restrict__ dg, int mode,
     const int *__restrict__ gate) {
-  __shared__ double red[4][NG][4][64];
-  if (gate != nullptr && *gate == 0) return;
+  __shared__ double red[CS_WAVES][NG][4][64];
+  const int go = gate != nullptr ? *gate : 1;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int lr = lane & 15, lg = lane >> 4;
   const int64_t t0 = (int64_t)blockIdx.x * 16;
-  const int64_t q = mp / 4, s0 = wave * q;
+  const int64_t q = mp / CS_WAVES, s0 = wave * q;
   d4 acc[NG];
 #pragma unroll
   for (int g = 0; g < NG; ++g) acc[g] = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-  for (int64_t s = s0 + lg; s < s0 + q; s += 4) {
-    const double a = eci[s * mp + t0 + lr];
+  const double *A = eci + t0 + lr, *B = in + lr * mp;
+  for (int64_t sb = s0 + lg; sb < s0 + q; sb += 32) {
+    double a[8], b[8][NG];
 #pragma unroll
-    for (int g = 0; g < NG; ++g)
-      acc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, in[(int64_t)(g * 16 + lr) * mp + s], acc[g],
-                                                    0, 0, 0);
+    for (int u = 0; u < 8; ++u) {
+      a[u] = A[(sb + 4 * u) * mp];
+#pragma unroll
+      for (int g = 0; g < NG; ++g) b[u][g] = B[g * 16 * mp + sb + 4 * u];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (go == 0) return;   // tested with the first loads under way
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+        acc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u][g], acc[g], 0, 0, 0);
   }
 #pragma unroll
   for (int g = 0; g < NG; ++g)
 #pragma unroll
     for (int v = 0; v < 4; ++v) red[wave][g][v][lane] = acc[g][v];
   __syncthreads();
-  for (int e = threadIdx.x; e < NG * 256; e += 256) {
+  for (int e = threadIdx.x; e < NG * 256; e += 64 * CS_WAVES) {
     const int g = e >> 8, v = (e >> 6) & 3, l = e & 63;
-    const double val =
-        ((red[0][g][v][l] + red[1][g][v][l]) + red[2][g][v][l]) + red[3][g][v][l];
+    double val = red[0][g][v][l];
+#pragma unroll
+    for (int w = 1; w < CS_WAVES; ++w) val += red[w][g][v][l];
     // D[i][j] in lane j + 16 (i % 4), register i / 4
     const int64_t t = t0 + 4 * v + (l >> 4);
     const int64_t o = (int64_t)(g * 16 + (l & 15)) * mp + t;
     if (mode == 0) {
       g1[o] = val;
-      g1f[o] = (float)val;
+      g1f[(t * 16 + (l & 15)) * NG + g] = (float)val;
     } else {
       dg[o] = g1[o] - val;
     }
@@ -1491,14 +1505,17 @@ __global__ __launch_bounds__(256) void coarse_solve_kernel(
 // .. + 3) as one float4 and gives A = g1f(column 16 g + lr, patch t + lg);
 // product j of a group takes B = the j-th of those atoms, so it holds
 // D[row 4 lg + v][column lr] = column 16 g + 4 lg + v of atom i0 + 4 lr + j
-// in register v. Rows past n stay 0 (az and rt are 0 there).
+// in register v. Rows past n stay 0 (az and rt are 0 there). The loads run
+// one batch of four steps ahead (mp is a multiple of 256): bound by the read
+// of E Z then, 67 MB for 512 patches of 32768 atoms, 37 us (60 when each
+// step waited for its loads and the columns of g1f were 512 floats apart).
 template <int NG>
 __global__ __launch_bounds__(256) void coarse_prolong_kernel(
     const float *__restrict__ az, const float *__restrict__ g1f, int64_t mp,
     const double *__restrict__ rt, int64_t ld, double *__restrict__ ut,
     const int *__restrict__ gate) {
   __shared__ float red[3][NG][4][4][64];
-  if (gate != nullptr && *gate == 0) return;
+  const int go = gate != nullptr ? *gate : 1;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int lr = lane & 15, lg = lane >> 4;
   const int64_t i0 = (int64_t)blockIdx.x * 64;
@@ -1509,16 +1526,38 @@ __global__ __launch_bounds__(256) void coarse_prolong_kernel(
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[g][j] = f4{0.f, 0.f, 0.f, 0.f};
   const float *B = az + i0 + 4 * lr;
-#pragma unroll 2
-  for (int64_t t = t0 + lg; t < t0 + q; t += 4) {
-    const f4 b4 = *reinterpret_cast<const f4 *>(B + t * ld);
+  const float *G = g1f + lr * NG;
+  f4 b[2][4];
+  float a[2][4][NG];
+  auto load = [&](auto buf, int64_t t) {
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      const float a = g1f[(int64_t)(g * 16 + lr) * mp + t];
+    for (int u = 0; u < 4; ++u) {
+      const int64_t tt = min(t + 4 * u, mp - 4) + lg;
+      b[buf.value][u] = *reinterpret_cast<const f4 *>(B + tt * ld);
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b4[j], acc[g][j], 0, 0, 0);
+      for (int g = 0; g < NG; ++g) a[buf.value][u][g] = G[tt * (16 * NG) + g];
     }
+  };
+  auto batch = [&](auto buf, int64_t next) {
+    load(std::integral_constant<int, decltype(buf)::value ^ 1>(), next);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[buf.value][u][g], b[buf.value][u][j],
+                                                           acc[g][j], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const std::integral_constant<int, 0> even;
+  const std::integral_constant<int, 1> odd;
+  load(even, t0);
+  if (go == 0) return;
+  for (int64_t t = t0; t < t0 + q; t += 32) {
+    batch(even, t + 16);
+    batch(odd, t + 32);
   }
   if (wave > 0) {
 #pragma unroll
@@ -1549,12 +1588,14 @@ __global__ __launch_bounds__(256) void coarse_prolong_kernel(
 // four row blocks of 16) and one slice of kslice atoms (a multiple of 16).
 // Per 16 atoms lane (lr, lg) loads az(patch tb + 16 rb + lr, atoms i + 4 lg
 // .. + 3) as one float4; step j (0..3) takes k = lg as the atom i + 4 lg + j,
-// with B = w(i + 4 lg + j, column 16 g + lr).
+// with B = w(i + 4 lg + j, column 16 g + lr). The loads of the next 16 atoms
+// are under way during the products of these: 512 patches, 32768 atoms, 64
+// columns 45 us (56 without; the products alone 14).
 template <int NG>
 __global__ __launch_bounds__(256) void coarse_gather_kernel(
     const float *__restrict__ az, const double *__restrict__ wt, int64_t ld, int64_t mp,
     int64_t kslice, int cols, float *__restrict__ c2p, const int *__restrict__ gate) {
-  if (gate != nullptr && *gate == 0) return;
+  const int go = gate != nullptr ? *gate : 1;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int lr = lane & 15, lg = lane >> 4;
   const int64_t tb = (int64_t)blockIdx.x * kCoarseAlign + wave * 64;
@@ -1565,20 +1606,42 @@ __global__ __launch_bounds__(256) void coarse_gather_kernel(
   for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
     for (int g = 0; g < NG; ++g) acc[rb][g] = f4{0.f, 0.f, 0.f, 0.f};
-  for (int64_t i = i0; i < i1; i += 16) {
-    f4 a[4];
+  f4 a[2][4];
+  double b[2][4][NG];
+  auto load = [&](auto buf, int64_t i) {
+    const int64_t ic = min(i, i1 - 16) + 4 * lg;
 #pragma unroll
     for (int rb = 0; rb < 4; ++rb)
-      a[rb] = *reinterpret_cast<const f4 *>(az + (tb + 16 * rb + lr) * ld + i + 4 * lg);
+      a[buf.value][rb] = *reinterpret_cast<const f4 *>(az + (tb + 16 * rb + lr) * ld + ic);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+        b[buf.value][j][g] = wt[((int64_t)g * ld + ic + j) * kColGroup + lr];
+  };
+  auto step = [&](auto buf, int64_t next) {
+    load(std::integral_constant<int, decltype(buf)::value ^ 1>(), next);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
-        const float b = (float)wt[((int64_t)g * ld + i + 4 * lg + j) * kColGroup + lr];
+        const float bj = (float)b[buf.value][j][g];
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb)
-          acc[rb][g] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[rb][j], b, acc[rb][g], 0, 0, 0);
+          acc[rb][g] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[buf.value][rb][j], bj, acc[rb][g],
+                                                            0, 0, 0);
       }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const std::integral_constant<int, 0> even;
+  const std::integral_constant<int, 1> odd;
+  load(even, i0);
+  if (go == 0) return;
+  for (int64_t i = i0; i < i1; i += 32) {
+    step(even, i + 16);
+    if (i + 16 >= i1) break;
+    step(odd, i + 32);
   }
   float *out = c2p + (int64_t)blockIdx.y * cols * mp;
 #pragma unroll
@@ -1590,16 +1653,30 @@ __global__ __launch_bounds__(256) void coarse_gather_kernel(
         out[(int64_t)(g * 16 + lr) * mp + tb + 16 * rb + 4 * lg + v] = acc[rb][g][v];
 }
 
-// c[e] = sum over the ks slices of c2p (FP64, in slice order), e < count
+// c[e] = sum over the ks slices of c2p (FP64), e < count, a multiple of 64:
+// lane = e, the four waves take a quarter of the slices each, eight loads at
+// a time, and their sums are added in wave order. 512 patches, 64 columns:
+// 14 us for 512 slices, 5 for 128 (a thread per e and a load at a time, 512
+// slices: 127).
 __global__ __launch_bounds__(256) void coarse_sum_kernel(const float *__restrict__ c2p, int ks,
                                                          int64_t count, double *__restrict__ c,
                                                          const int *__restrict__ gate) {
+  __shared__ double red[4][64];
   if (gate != nullptr && *gate == 0) return;
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= count) return;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t e = (int64_t)blockIdx.x * 64 + lane;
+  const int k0 = wave * ks / 4, k1 = (wave + 1) * ks / 4;
   double v = 0.0;
-  for (int k = 0; k < ks; ++k) v += (double)c2p[(int64_t)k * count + e];
-  c[e] = v;
+  for (int k = k0; k < k1; k += 8) {
+    float x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = c2p[(int64_t)min(k + u, ks - 1) * count + e];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v += k + u < k1 ? (double)x[u] : 0.0;
+  }
+  red[wave][lane] = v;
+  __syncthreads();
+  if (wave == 0) c[e] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
 }
 
 // 1^T u per column of the row-interleaved ut (fixed order): the Eq. 37 term
@@ -2265,7 +2342,8 @@ void launch_coarse_ng(hipStream_t st, const cpm_system *s, const double *rt, con
   if (stage == 0) {
     hipLaunchKernelGGL(coarse_restrict_kernel<NG>, dim3((unsigned)(mp / 4)), dim3(256), 0, st, rt,
                        ld, (const int32_t *)cz.perm, (const int32_t *)cz.off, mp, cz.c1, gate);
-    hipLaunchKernelGGL(coarse_solve_kernel<NG>, dim3((unsigned)(mp / 16)), dim3(256), 0, st,
+    hipLaunchKernelGGL(coarse_solve_kernel<NG>, dim3((unsigned)(mp / 16)),
+                       dim3(64 * CS_WAVES), 0, st,
                        (const double *)cz.eci, mp, (const double *)cz.c1, cz.g1, cz.g1f,
                        (double *)nullptr, 0, gate);
     hipLaunchKernelGGL(coarse_prolong_kernel<NG>, dim3((unsigned)(ld / 64)), dim3(256), 0, st,
@@ -2275,9 +2353,10 @@ void launch_coarse_ng(hipStream_t st, const cpm_system *s, const double *rt, con
                        dim3(256), 0, st, (const float *)cz.az, (const double *)cz.wt, ld, mp,
                        cz.kslice, NG * 16, cz.c2p, gate);
     const int64_t count = (int64_t)NG * 16 * mp;
-    hipLaunchKernelGGL(coarse_sum_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st,
+    hipLaunchKernelGGL(coarse_sum_kernel, dim3((unsigned)(count / 64)), dim3(256), 0, st,
                        (const float *)cz.c2p, cz.ks, count, cz.c1, gate);
-    hipLaunchKernelGGL(coarse_solve_kernel<NG>, dim3((unsigned)(mp / 16)), dim3(256), 0, st,
+    hipLaunchKernelGGL(coarse_solve_kernel<NG>, dim3((unsigned)(mp / 16)),
+                       dim3(64 * CS_WAVES), 0, st,
                        (const double *)cz.eci, mp, (const double *)cz.c1, cz.g1, (float *)nullptr,
                        cz.dg, 1, gate);
   }
@@ -2660,11 +2739,13 @@ cpm_status solve_columns(cpm_system *s, int fc, const cpm_solve_opts &o, cpm_sol
 
 }  // namespace
 
-// slices of the Z^T-side coarse product: about 1024 workgroups of
+// slices of the Z^T-side coarse product: about 256 workgroups of
 // kCoarseAlign patches, at least 64 atoms and a multiple of 16 per slice
+// (512 patches, 64 columns: 50 us with the sum of the slices, 57 with 512
+// workgroups, 73 with 1024)
 void coarse_slices(int64_t ld, int64_t mp, int &ks, int64_t &kslice) {
   const int64_t pw = std::max<int64_t>(1, mp / kCoarseAlign);
-  int64_t want = std::max<int64_t>(1, (1024 + pw - 1) / pw);
+  int64_t want = std::max<int64_t>(1, (256 + pw - 1) / pw);
   want = std::min<int64_t>(want, std::max<int64_t>(1, ld / 64));
   kslice = round_up((ld + want - 1) / want, 16);
   ks = (int)((ld + kslice - 1) / kslice);
