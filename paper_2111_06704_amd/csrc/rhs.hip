@@ -415,6 +415,9 @@ __global__ __launch_bounds__(256, 2) void sf_gemm_kernel(
 //   blocks (one y each, rows x) of v_mfma_f64_16x16x4f64. An ion reaches 8
 //   tiles, so 7/8 of the products are with zeros; that is still 65.5 kflop
 //   per ion against 4 n_k (482 kflop for 120 000 vectors).
+//   A step of 4 ions multiplies only the y that one of them reaches (the
+//   cell list keeps ions of about one y together: 11 of 16 on average) and
+//   positions are scaled by reciprocals: 50000 ions, 8 frames 750 -> 658 us.
 // nu_dftz_kernel, nu_dfty_kernel, nu_dftx_kernel: the three transforms, each
 //   a product with a dense (cos, sin) matrix on the FP64 matrix cores that
 //   computes only the wanted n (z: n >= 0; y and x: both signs from the same
@@ -443,6 +446,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     const double *__restrict__ coef, double *__restrict__ grid) {
   __shared__ double lst[4][NU_CH + 64];   // (x, y, z) in grid points from the tile's origin, q
   __shared__ double tab[3][NU_CH][NU_T + 2];
+  __shared__ unsigned rows[NU_CH / 4];   // the y of the tile that a step's ions reach
   const int lane = threadIdx.x, lr = lane & 15, lg = lane >> 4;
   int t = blockIdx.x;
   const int oz = t % (gz / NU_T) * NU_T;
@@ -467,17 +471,20 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   const double4 *sf = sorted + f * m;
   const int xlen = xb - xa + 1, xw0 = wrap_cell(xa, ncx);
   // the ion's coordinate from the tile's origin, nearest image to its centre
-  auto local = [&](double x, double l, int g, int o) {
-    double w = x / l;
+  const double ilx = 1.0 / lx, ily = 1.0 / ly, ilz = 1.0 / lz;
+  const double igx = 1.0 / gx, igy = 1.0 / gy, igz = 1.0 / gz;
+  auto local = [&](double x, double il, double g, double ig, int o) {
+    double w = x * il;
     w -= floor(w);
     const double u = w * g - o;
-    return u - g * rint((u - 7.5) / g);
+    return u - g * rint((u - 7.5) * ig);
   };
   // the product of the first `cnt` listed ions, cnt <= NU_CH (padded with q = 0)
   auto flush = [&](int cnt) {
     const int steps = (cnt + 3) >> 2;
     if (lane < 4 * steps && lane >= cnt) {
-      lst[0][lane] = lst[1][lane] = lst[2][lane] = 7.5;
+      lst[0][lane] = lst[2][lane] = 7.5;
+      lst[1][lane] = 1000.0;   // reaches no y
       lst[3][lane] = 0.0;
     }
     __syncthreads();
@@ -493,8 +500,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         double v = cf[NU_DEG];
 #pragma unroll
         for (int e = NU_DEG - 1; e >= 0; --e) v = fma(v, x, cf[e]);
-        if (d == 1) v *= lst[3][ion];
         const int j = (int)i0 + lr;
+        if (d == 1) {
+          v *= lst[3][ion];
+          const int i = (int)fmin(fmax(i0, -16.0), 16.0);
+          unsigned m = u != u ? 0xffffu : (i < 0 ? 0xffffu >> -i : (0xffffu << i) & 0xffffu);
+          m |= __shfl_xor(m, 16, 64);
+          m |= __shfl_xor(m, 32, 64);
+          if (lane == 0) rows[s] = m;
+        }
         tab[d][ion][j & (NU_T - 1)] = ((unsigned)j < (unsigned)NU_T) | (u != u) ? v : 0.0;
       }
     }
@@ -505,9 +519,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
       d2 fy[NU_T / 2];
 #pragma unroll
       for (int r = 0; r < NU_T / 2; ++r) fy[r] = *reinterpret_cast<const d2 *>(&tab[1][ion][2 * r]);
+      const unsigned m = __builtin_amdgcn_readfirstlane(rows[s]);
 #pragma unroll
       for (int r = 0; r < NU_T; ++r)
-        acc[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(fx * fy[r / 2][r & 1], fz, acc[r], 0, 0, 0);
+        if (m >> r & 1)
+          acc[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(fx * fy[r / 2][r & 1], fz, acc[r], 0, 0, 0);
     }
     __syncthreads();
   };
@@ -522,8 +538,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         const int64_t s0 = cs[row + c0], s1 = cs[row + c1];
         for (int64_t base = s0; base < s1; base += 64) {
           const double4 ion = sf[min(base + lane, s1 - 1)];
-          const double ux = local(ion.x, lx, gx, ox), uy = local(ion.y, ly, gy, oy),
-                       uz = local(ion.z, lz, gz, oz);
+          const double ux = local(ion.x, ilx, gx, igx, ox), uy = local(ion.y, ily, gy, igy, oy),
+                       uz = local(ion.z, ilz, gz, igz, oz);
           constexpr double kReach = 0.5 * (NU_T - 1 + NU_W);   // |u - 7.5| below this
           const bool in = base + lane < s1 && !(fabs(ux - 7.5) >= kReach) &&
                           !(fabs(uy - 7.5) >= kReach) && !(fabs(uz - 7.5) >= kReach);
@@ -1611,8 +1627,8 @@ RhsPlan rhs_plan_capped(const cpm_system *s, int64_t m, int64_t f, int64_t cap_s
     p.nu = grid && m >= kCellMinIons && nu_pays(s, m, f);
     const int64_t cap = std::max<int64_t>(1, std::min(cap_sf, kPartialCap / (2 * nk * f)));
     if (p.sf_gemm) {
-      // whole chunks of ions per group, for about 1024 workgroups (two per CU
-      // are resident): one frame of 2000 ions, 7 tiles: 43 us with 7 groups
+      // whole chunks of ions per group, for about 1024 workgroups (three per
+      // CU are resident): one frame of 2000 ions, 7 tiles: 43 us with 7 groups
       // of 286 ions, 17 with 32, 16 with 63, whose sum costs 3 us more; 13
       // frames: 80 us and 8 for the sum with 7 groups, 78 and 10 with 12,
       // 78 and 13 with 17
