@@ -13,7 +13,7 @@
 //     of an FP64 E: the streamed-P FP64 kernel; 32..64 columns of an FP32 /
 //     BF16 E: the split-bf16 kernel). MFMA blocks of 16x16
 //     (v_mfma_f64_16x16x4f64 for FP64 E, v_mfma_f32_16x16x4f32 for FP32 and
-//     BF16 E, products accumulated in FP32). Lane l supplies A[l % 16][l / 16]
+//     BF16 E, FP32 sums that move to FP64 every 128 entries). Lane l supplies A[l % 16][l / 16]
 //     and B[l / 16][l % 16]; the k slots of the MFMA are mapped to 32
 //     contiguous bytes of an E row per lane, so E and P are read with wide,
 //     coalesced loads. Each workgroup also reduces its share of p.v.
@@ -22,7 +22,7 @@
 //                        z = M^-1 r (Jacobi, M = diag E); partial r.r, r.z.
 //   cg_direction_kernel  beta = r'.z' / r.z; p = z + beta p.
 // With PCG-DC (Sec. III.B.2) the update is cg_update_pc_kernel (it also
-// writes the row-interleaved copy of r) and precond_kernel computes z = P r
+// writes the row-interleaved copy of r) and precond_block_kernel computes z = P r
 // and the partial r.r, r.z before the direction kernel.
 // All dots are FP64 and reduced in a fixed order (bitwise reproducible).
 //

@@ -1531,7 +1531,7 @@ namespace {
 struct RhsPlan {
   int64_t sf_groups = 1, sf_ipg = 0, ksplit = 0, kper = 0, rs_groups = 0, rs_ipg = 0;
   bool sf_gemm = false;         // structure factors on the matrix cores (|n_z| <= 47)
-  bool bp_plane = false;        // factored back-projection over the atoms' z-planes
+  bool bp_plane = false;        // factored back-projection over the atoms' layers
   bool rs_cell = false;         // real space over the cell list of the ions
   bool nu = false;              // structure factors through a grid, nu_frames frames at a time
   int64_t nu_frames = 0, off_nu = 0;
@@ -1629,7 +1629,7 @@ RhsPlan rhs_plan_capped(const cpm_system *s, int64_t m, int64_t f, int64_t cap_s
   RhsPlan p;
   const int64_t n = s->n, nk = std::max<int64_t>(s->kset.nk, 1);
   const int64_t rblocks = (s->kset.nruns + RB - 1) / RB;
-  const int64_t iblocks = (n + RB - 1) / RB, fgroups = (f + FG - 1) / FG;
+  const int64_t fgroups = (f + FG - 1) / FG;
   const int64_t bblocks = (n + RB * BP_AT - 1) / (RB * BP_AT);
   if (m > 0 && s->kset.nk > 0) {
     p.sf_gemm = s->kset.smax < SG_SB * 16;
@@ -1706,7 +1706,7 @@ constexpr int64_t kNoCap = (int64_t)1 << 40;
 // the default plan, or with limit > 0 the most parallel plan whose scratch
 // holds at most limit doubles (halving the largest partial count first)
 RhsPlan rhs_plan(const cpm_system *s, int64_t m, int64_t f, int64_t limit = 0) {
-  // the factored back-projection first; without it when its per-plane sums
+  // the factored back-projection first; without it when its per-node sums
   // do not fit the limit
   for (int planes = 1;; planes = 0) {
     RhsPlan p = rhs_plan_capped(s, m, f, kNoCap, kNoCap, kNoCap, planes != 0, limit <= 0 && !s->nu.off);
@@ -1958,7 +1958,7 @@ hipError_t launch_rhs(hipStream_t st, const cpm_system *s, const double *ion_pos
   const double c0 = -M_PI / (s->vol * s->beta * s->beta);
   const RhsPlan p = rhs_plan(s, m, f, limit);
   double *S = buf, *bp = buf + p.off_bp, *rs = buf + p.off_rs;
-  const int64_t iblocks = (n + RB - 1) / RB, fgroups = (f + FG - 1) / FG;
+  const int64_t fgroups = (f + FG - 1) / FG;
   double *m1 = s->slab ? buf + p.off_m1 : nullptr;
   if (m > 0) {
     hipLaunchKernelGGL(qsum_kernel, dim3((unsigned)f), dim3(RB), 0, st, ion_q, m, qsol_out, ion_pos,
