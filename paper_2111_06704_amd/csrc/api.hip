@@ -724,8 +724,14 @@ cpm_status cpm_rhs(cpm_system *s, const double *ion_pos_dev, const double *ion_q
       s->rhs_S_elems = 0;
     }
     cpm_status rc = dev_alloc(s, &s->rhs_S, need);
+    if (rc == CPM_ENOMEM && !s->nu.off && s->nu.elems > kNuFew) {
+      // the grid path's scratch is the larger one: try fewer grids at a time
+      s->nu.elems = kNuFew;
+      need = scratch();
+      rc = dev_alloc(s, &s->rhs_S, need);
+    }
     if (rc == CPM_ENOMEM && !s->nu.off) {
-      // the grid path's scratch is the larger one: try without it
+      // and without it
       s->nu.off = true;
       need = scratch();
       rc = dev_alloc(s, &s->rhs_S, need);

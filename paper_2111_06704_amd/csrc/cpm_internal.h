@@ -187,8 +187,13 @@ struct NuGrid {
   double *coef = nullptr;       // window polynomials
   const double *inv = nullptr;  // 1 / Phi per axis
   int2 *col = nullptr;          // (k index of n_z = 0, largest |n_z|) by (n_x, n_y)
+  // doubles of grids at a time, then kNuFew when they do not fit: every launch
+  // ends with a nearly empty chip (32 frames of 7.9 M doubles: 4.6 ms for the
+  // right-hand side with 2^26, 8 frames a launch, 4.1 with all of them)
+  int64_t elems = (int64_t)1 << 28;
   bool off = false;             // no room for the scratch: the direct product
 };
+constexpr int64_t kNuFew = (int64_t)1 << 26;
 
 struct Gcd {                 // capacitance coefficients (Supplementary Eq. S22-S24)
   bool ready = false;

@@ -1597,7 +1597,6 @@ int64_t nu_frame_elems(const cpm_system *s) {
   return (int64_t)g.g[0] * g.g[1] * g.g[2] + 2 * nz * g.g[0] * g.g[1] +
          2 * nz * (2 * g.m[1] + 1) * g.g[0];
 }
-constexpr int64_t kNuGridElems = (int64_t)1 << 26;   // 512 MB of them at a time
 
 // Whether the grid path beats the direct product, from the time of both at
 // the rates each was measured at. With few frames the densest tile's wave
@@ -1674,7 +1673,7 @@ RhsPlan rhs_plan_capped(const cpm_system *s, int64_t m, int64_t f, int64_t cap_s
   if (p.nu) {
     p.sf_gemm = false;
     p.sf_groups = 1;
-    p.nu_frames = std::max<int64_t>(1, std::min<int64_t>(f, kNuGridElems / nu_frame_elems(s)));
+    p.nu_frames = std::max<int64_t>(1, std::min<int64_t>(f, s->nu.elems / nu_frame_elems(s)));
   }
   if (m >= kCellMinIons) {
     p.rs_cell = true;
