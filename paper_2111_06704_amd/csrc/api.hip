@@ -116,7 +116,12 @@ std::vector<int32_t> spatial_order(const std::vector<double> &pos, int64_t n) {
 // runs of atoms without a gap of about 1 / k in z (found by bins of
 // 1 / (4 k)), cut into slices of at most 2 / k, each with the least multiple
 // of four Chebyshev nodes that interpolates to 1e-17, 2 (k D / 4)^n / n! for
-// thickness D (at most 16). The direct sum costs n_k products per atom and
+// thickness D (at most 16). Atoms that differ in the last bits of z only
+// (one plane computed in two ways) would put all nodes on the same few
+// doubles, and the sum of the barycentric weights would cancel (weights up
+// to 1e16 at 1 to 3 last bits): the nodes of a layer span at least 1e-4 / k,
+// 10^9 last bits of z in a box of 100 A, which still takes four nodes. The
+// direct sum costs n_k products per atom and
 // frame, the layers n n_cols per atom plus n_k per node: taken when that is
 // at most half in each part and the node sums need at most four times the
 // memory of the structure factors (4599 atoms in 6 layers 0.1 A thick have 8
@@ -200,6 +205,11 @@ LayerPlan plan_layers(const std::vector<double> &pos, int64_t n, const double bo
   for (int32_t l = 0; l < ns; ++l) {
     if (members[l].empty()) continue;
     if (z1[l] > z0[l]) {
+      if (z1[l] - z0[l] < 1e-4 / k) {
+        const double mid = z0[l] + 0.5 * (z1[l] - z0[l]);
+        z0[l] = mid - 0.5e-4 / k;
+        z1[l] = mid + 0.5e-4 / k;
+      }
       const double x = 0.25 * k * (z1[l] - z0[l]);
       double e = 2.0;
       int c = 0;
