@@ -314,7 +314,6 @@ void free_system(cpm_system *s) {
     if (p) (void)hipFree(p);
   if (s->mlp.hloss) (void)hipHostFree(s->mlp.hloss);
   if (s->nu.tab) (void)hipFree(s->nu.tab);
-  if (s->nu.col) (void)hipFree(s->nu.col);
   if (s->rs_width && s->rs_width != s->width) (void)hipFree(s->rs_width);
   for (DevBuf *b : {&s->buf_warm, &s->buf_eq, &s->buf_mean, &s->buf_aux})
     if (b->p) (void)hipFree(b->p);

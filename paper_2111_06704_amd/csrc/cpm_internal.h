@@ -182,11 +182,11 @@ void free_coarse(Coarse &c);
 struct NuGrid {
   int g[3] = {0, 0, 0}, m[3] = {0, 0, 0};
   int zrows = 0, zpasses = 1, passes[2] = {1, 1};   // padded rows and passes of the transforms
-  double *tab = nullptr;        // the allocation behind mat, coef and inv
+  double *tab = nullptr;        // the allocation behind mat, coef, inv and col
   const double *mat[3] = {nullptr, nullptr, nullptr};
   double *coef = nullptr;       // window polynomials
   const double *inv = nullptr;  // 1 / Phi per axis
-  int2 *col = nullptr;          // (k index of n_z = 0, largest |n_z|) by (n_x, n_y)
+  const int2 *col = nullptr;    // (k index of n_z = 0, largest |n_z|) by (n_x, n_y)
   // doubles of grids at a time, then kNuFew when they do not fit: every launch
   // ends with a nearly empty chip (32 frames of 7.9 M doubles: 4.6 ms for the
   // right-hand side with 2^26, 8 frames a launch, 4.1 with all of them)

@@ -1562,7 +1562,12 @@ void cell_grid(const double box[3], double rcut, int nc[3]) {
 constexpr int64_t kTargetBlocks = 2048;          // workgroups that fill the chip several times
 constexpr int64_t kPartialCap = (int64_t)1 << 27;  // doubles per partial buffer
 
-// cost model of nu_pays in seconds per flop (per grid point; fixed per call)
+// cost model of nu_pays in seconds per flop (per grid point; fixed per call).
+// A system's first such call also makes its tables, 0.15 ms, which the model
+// leaves out: with 130 us fixed, a system that serves one call saves 0.1 ms
+// (9000 ions x 8 frames, 38 000 vectors: 0.63 against 0.72 ms, after 5 ms of
+// assembly) and one that serves many loses up to 0.18 ms on each (12 000 x 8 in
+// a box of 60 x 60 x 120 A: 0.85 against 0.67 ms).
 constexpr double kNuDirect = 1.0 / 38e12, kNuSpread = 1.0 / 33e12, kNuPoint = 2.5e-12,
                  kNuDft = 1.0 / 38e12, kNuFixed = 30e-6, kNuWave = 0.4e-6;
 
@@ -1829,123 +1834,198 @@ void nu_sizes(cpm_system *s) {
 
 bool rhs_uses_grid(const cpm_system *s, int64_t m, int64_t f) { return rhs_plan(s, m, f).nu; }
 
-// Window polynomials and transforms, transform matrices and the column table
-// on the device (once per system, on the first call that takes the grid).
+// ---- tables of the grid path
+
+namespace {
+
+// The window phi of the spreading, its polynomials (coef[s][d]: phi on
+// [-w/2 + s, -w/2 + s + 1] as monomials of x = 2 delta - 1, through the
+// Chebyshev points) and Gauss-Legendre nodes on (0, w/2) with weights 2 phi
+// for its transform Phi (phi falls to exp(-beta) = 1e-16 at the ends).
+// Constants of the program: made once per process, 0.15 ms of long double
+// (2.3 ms when every system made them, with a cosine per term and 128 nodes;
+// 40 give Phi to 5e-19, 32 to 3e-18).
+struct NuWindow {
+  static constexpr int N = NU_DEG + 1, Q = 40;
+  double coef[NU_W * N];
+  long double node[Q], weight[Q];
+  NuWindow() {
+    typedef long double ld;
+    const ld pi = 3.14159265358979323846264338327950288L, beta = (ld)NU_BETA, half = 0.5L * NU_W;
+    auto phi = [&](ld t) {
+      const ld z = 1.0L - (t / half) * (t / half);
+      return z > 0.0L ? std::exp(beta * (std::sqrt(z) - 1.0L)) : 0.0L;
+    };
+    ld cosine[N][N];   // T_j at the Chebyshev points
+    for (int j = 0; j < N; ++j)
+      for (int k = 0; k < N; ++k) cosine[j][k] = std::cos(pi * j * (k + 0.5L) / N);
+    for (int si = 0; si < NU_W; ++si) {
+      ld mono[N] = {}, t0[N] = {}, t1[N] = {}, fx[N];
+      for (int k = 0; k < N; ++k) fx[k] = phi(-half + si + 0.5L * (cosine[1][k] + 1.0L));
+      t0[0] = 1.0L;
+      t1[1] = 1.0L;
+      for (int j = 0; j < N; ++j) {   // t0 = T_j
+        ld c = 0.0L;
+        for (int k = 0; k < N; ++k) c += fx[k] * cosine[j][k];
+        c *= (j == 0 ? 1.0L : 2.0L) / N;
+        for (int k = 0; k < N; ++k) mono[k] += c * t0[k];
+        ld t2[N] = {};
+        for (int k = 0; k + 1 < N; ++k) t2[k + 1] = 2.0L * t1[k];
+        for (int k = 0; k < N; ++k) {
+          t2[k] -= t0[k];
+          t0[k] = t1[k];
+          t1[k] = t2[k];
+        }
+      }
+      for (int k = 0; k < N; ++k) coef[si * N + k] = (double)mono[k];
+    }
+    for (int i = 0; i < Q / 2; ++i) {   // the nodes come in pairs +-x
+      ld x = std::cos(pi * (i + 0.75L) / (Q + 0.5L)), dp = 0.0L;
+      for (int it = 0; it < 6; ++it) {
+        ld p0 = 1.0L, p1 = x;
+        for (int j = 2; j <= Q; ++j) {
+          const ld p2 = ((2 * j - 1) * x * p1 - (j - 1) * p0) / j;
+          p0 = p1;
+          p1 = p2;
+        }
+        dp = Q * (x * p1 - p0) / (x * x - 1.0L);
+        x -= p1 / dp;
+      }
+      const ld w = 2.0L / ((1.0L - x * x) * dp * dp);
+      for (int k : {i, Q - 1 - i}) {
+        node[k] = 0.5L * half * ((k == i ? x : -x) + 1.0L);
+        weight[k] = half * phi(node[k]) * w;
+      }
+    }
+  }
+};
+
+// mat (rows of one axis by g): row n of the cosines at n * cos_step, of the
+// sines at n * cos_step + sin_off, zero for n > m; cs: (cos, sin)(2 pi j / g).
+// Grid (rows, axes).
+struct NuAxis {
+  double *mat;
+  const double2 *cs;
+  int g, m, rows, step, sin_off;
+};
+struct NuAxes {
+  NuAxis a[3];
+};
+__global__ __launch_bounds__(128) void nu_matrix_kernel(NuAxes axes) {
+  const NuAxis &a = axes.a[blockIdx.y];
+  const int row = blockIdx.x;
+  if (row >= a.rows) return;
+  const bool sine = a.step == 2 ? row & 1 : row >= a.sin_off;
+  const int n = a.step == 2 ? row >> 1 : row - (sine ? a.sin_off : 0);
+  for (int j = threadIdx.x; j < a.g; j += 128) {
+    const double2 v = a.cs[(int64_t)n * j % a.g];
+    a.mat[(int64_t)row * a.g + j] = n > a.m ? 0.0 : sine ? v.y : v.x;
+  }
+}
+
+}  // namespace
+
+// The tables of one system on the device (on its first call that takes the
+// grid): the transform matrices, expanded there from (cos, sin)(2 pi j / G),
+// the window's polynomials, 1 / Phi and the column table. Of the host's work
+// 1 / Phi is the largest part: exp(2 pi i n t / G) at the quadrature nodes by
+// repeated rotation (2e-18).
 cpm_status ensure_nu(cpm_system *s) {
   NuGrid &g = s->nu;
   if (g.coef) return CPM_OK;
+  static const NuWindow win;
   typedef long double ld;
-  const ld pi = 3.14159265358979323846264338327950288L, beta = (ld)NU_BETA, half = 0.5L * NU_W;
-  auto phi = [&](ld t) {
-    const ld z = 1.0L - (t / half) * (t / half);
-    return z > 0.0L ? std::exp(beta * (std::sqrt(z) - 1.0L)) : 0.0L;
-  };
-  // phi on [-w/2 + s, -w/2 + s + 1] as a polynomial in x = 2 delta - 1 through
-  // the Chebyshev points, as monomials
-  constexpr int N = NU_DEG + 1;
-  std::vector<double> coef(NU_W * N);
-  for (int si = 0; si < NU_W; ++si) {
-    ld c[N], mono[N] = {}, t0[N] = {}, t1[N] = {}, fx[N];
-    for (int k = 0; k < N; ++k)
-      fx[k] = phi(-half + si + 0.5L * (std::cos(pi * (k + 0.5L) / N) + 1.0L));
-    for (int j = 0; j < N; ++j) {
-      c[j] = 0.0L;
-      for (int k = 0; k < N; ++k) c[j] += fx[k] * std::cos(pi * j * (k + 0.5L) / N);
-      c[j] *= (j == 0 ? 1.0L : 2.0L) / N;
-    }
-    t0[0] = 1.0L;
-    t1[1] = 1.0L;
-    for (int j = 0; j < N; ++j) {   // t0 = T_j
-      for (int k = 0; k < N; ++k) mono[k] += c[j] * t0[k];
-      ld t2[N] = {};
-      for (int k = 0; k + 1 < N; ++k) t2[k + 1] = 2.0L * t1[k];
-      for (int k = 0; k < N; ++k) {
-        t2[k] -= t0[k];
-        t0[k] = t1[k];
-        t1[k] = t2[k];
-      }
-    }
-    for (int k = 0; k < N; ++k) coef[si * N + k] = (double)mono[k];
-  }
-  // Gauss-Legendre nodes for Phi (the integrand is smooth: phi falls to
-  // exp(-beta) = 1e-16 at the ends)
-  constexpr int Q = 128;
-  std::vector<ld> node(Q), weight(Q);
-  for (int i = 0; i < Q; ++i) {
-    ld x = std::cos(pi * (i + 0.75L) / (Q + 0.5L)), dp = 0.0L;
-    for (int it = 0; it < 8; ++it) {
-      ld p0 = 1.0L, p1 = x;
-      for (int j = 2; j <= Q; ++j) {
-        const ld p2 = ((2 * j - 1) * x * p1 - (j - 1) * p0) / j;
-        p0 = p1;
-        p1 = p2;
-      }
-      dp = Q * (x * p1 - p0) / (x * x - 1.0L);
-      x -= p1 / dp;
-    }
-    node[i] = 0.5L * half * (x + 1.0L);
-    weight[i] = half * phi(node[i]) / ((1.0L - x * x) * dp * dp) * 2.0L;
-  }
-  std::vector<double> inv, mats;
-  size_t moff[3];
+  const ld two_pi = 6.28318530717958647692528676655900577L;
+  std::vector<double> h(win.coef, win.coef + NU_W * NuWindow::N);
   for (int d = 0; d < 3; ++d) {
-    const int G = g.g[d];
+    ld c[NuWindow::Q], sn[NuWindow::Q], rc[NuWindow::Q], rs[NuWindow::Q];
+    for (int i = 0; i < NuWindow::Q; ++i) {
+      c[i] = win.weight[i];
+      sn[i] = 0.0L;
+      rc[i] = std::cos(two_pi * win.node[i] / g.g[d]);
+      rs[i] = std::sin(two_pi * win.node[i] / g.g[d]);
+    }
     for (int n = 0; n <= g.m[d]; ++n) {
       ld v = 0.0L;
-      for (int i = 0; i < Q; ++i) v += weight[i] * std::cos(2.0L * pi * n * node[i] / G);
-      inv.push_back((double)(1.0L / v));
-    }
-    std::vector<double> cs(G), sn(G);
-    for (int j = 0; j < G; ++j) {
-      cs[j] = (double)std::cos(2.0L * pi * j / G);
-      sn[j] = (double)std::sin(2.0L * pi * j / G);
-    }
-    moff[d] = mats.size();
-    const int rows = d == 2 ? g.zrows : 2 * g.passes[d] * NU_K2 * 16, off = rows / 2;
-    mats.resize(moff[d] + (size_t)rows * G, 0.0);
-    double *M = mats.data() + moff[d];
-    for (int n = 0; n <= g.m[d]; ++n)
-      for (int j = 0; j < G; ++j) {
-        const int q = (int)((int64_t)n * j % G);
-        M[(size_t)(d == 2 ? 2 * n : n) * G + j] = cs[q];
-        M[(size_t)(d == 2 ? 2 * n + 1 : off + n) * G + j] = sn[q];
+      for (int i = 0; i < NuWindow::Q; ++i) {
+        v += c[i];
+        const ld t = c[i] * rc[i] - sn[i] * rs[i];
+        sn[i] = sn[i] * rc[i] + c[i] * rs[i];
+        c[i] = t;
       }
+      h.push_back((double)(1.0L / v));
+    }
   }
+  if (h.size() & 1) h.push_back(0.0);   // pairs from here on
+  const size_t cs_off = h.size();
+  for (int d = 0; d < 3; ++d) {
+    const int G = g.g[d], q = G / 4;   // G is a multiple of 16
+    std::vector<double> cq(q + 1);
+    for (int j = 0; j < q; ++j) cq[j] = (double)std::cos(two_pi * j / G);
+    cq[q] = 0.0;
+    for (int j = 0; j < G; ++j) {
+      const int k = j % q;
+      const double c = cq[k], sv = cq[q - k];
+      const double cs[4][2] = {{c, sv}, {-sv, c}, {-c, -sv}, {sv, -c}};
+      h.insert(h.end(), cs[j / q], cs[j / q] + 2);
+    }
+  }
+  const size_t col_off = h.size();
   const int ny = 2 * g.m[1] + 1;
   std::vector<int2> col((size_t)(g.m[0] + 1) * ny, make_int2(0, -1));
   for (int64_t c = 0; c < s->kset.ncols; ++c) {
     const int32_t *k = s->kset.cols.data() + 4 * c;
     col[(size_t)k[0] * ny + g.m[1] + k[1]] = make_int2(k[3], k[2]);
   }
-  const size_t nd = coef.size() + mats.size() + inv.size();
+  static_assert(sizeof(int2) == sizeof(double), "the column table in the block of doubles");
+  h.resize(col_off + col.size());
+  std::memcpy(h.data() + col_off, col.data(), sizeof(int2) * col.size());
+  NuAxes axes;
+  size_t moff[3], mats = 0;   // the matrices first: rows of 16 k are 128-byte aligned
+  int rows = 0;
+  for (int d = 0; d < 3; ++d) {
+    NuAxis &a = axes.a[d];
+    a.g = g.g[d];
+    a.m = g.m[d];
+    a.rows = d == 2 ? g.zrows : 2 * g.passes[d] * NU_K2 * 16;
+    a.step = d == 2 ? 2 : 1;
+    a.sin_off = d == 2 ? 1 : a.rows / 2;
+    moff[d] = mats;
+    mats += (size_t)a.rows * a.g;
+    rows = std::max(rows, a.rows);
+  }
+  const size_t nd = mats + h.size();
   double *dev = nullptr;
-  int2 *dcol = nullptr;
-  if (hipMalloc((void **)&dev, sizeof(double) * nd) != hipSuccess ||
-      hipMalloc((void **)&dcol, sizeof(int2) * col.size()) != hipSuccess) {
+  if (hipMalloc((void **)&dev, sizeof(double) * nd) != hipSuccess) {
     (void)hipGetLastError();
-    if (dev) (void)hipFree(dev);
     set_error("structure-factor table allocation failed");
     return CPM_ENOMEM;
   }
-  std::vector<double> all(mats);   // the matrices first: rows of 16 k are 128-byte aligned
-  all.insert(all.end(), coef.begin(), coef.end());
-  all.insert(all.end(), inv.begin(), inv.end());
-  if (hipMemcpyAsync(dev, all.data(), sizeof(double) * nd, hipMemcpyHostToDevice, s->stream) !=
-          hipSuccess ||
-      hipMemcpyAsync(dcol, col.data(), sizeof(int2) * col.size(), hipMemcpyHostToDevice,
-                     s->stream) != hipSuccess ||
-      hipStreamSynchronize(s->stream) != hipSuccess) {
+  double *small = dev + mats;
+  size_t cs_at = cs_off;
+  for (int d = 0; d < 3; ++d) {
+    axes.a[d].mat = dev + moff[d];
+    axes.a[d].cs = reinterpret_cast<const double2 *>(small + cs_at);
+    cs_at += 2 * (size_t)g.g[d];
+  }
+  hipError_t e = hipMemcpyAsync(small, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice,
+                                s->stream);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(nu_matrix_kernel, dim3((unsigned)rows, 3), dim3(128), 0, s->stream, axes);
+    e = hipGetLastError();
+  }
+  const hipError_t done = hipStreamSynchronize(s->stream);   // the host copy goes out of scope
+  if (e != hipSuccess || done != hipSuccess) {
     (void)hipFree(dev);
-    (void)hipFree(dcol);
     set_error("structure-factor table copy failed");
     return CPM_EDEVICE;
   }
   for (int d = 0; d < 3; ++d) g.mat[d] = dev + moff[d];
   g.tab = dev;
-  g.coef = dev + mats.size();
-  g.inv = g.coef + coef.size();
-  g.col = dcol;
-  s->device_bytes += (int64_t)(sizeof(double) * nd + sizeof(int2) * col.size());
+  g.coef = small;
+  g.inv = small + NU_W * NuWindow::N;
+  g.col = reinterpret_cast<const int2 *>(small + col_off);
+  s->device_bytes += (int64_t)(sizeof(double) * nd);
   return CPM_OK;
 }
 
