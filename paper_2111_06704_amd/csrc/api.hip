@@ -713,17 +713,28 @@ cpm_status cpm_rhs(cpm_system *s, const double *ion_pos_dev, const double *ion_q
   }
   const int64_t fchunk = 1024;
   // scratch for the largest of the chunk sizes used (full chunks and the tail)
-  const int64_t tail = f > fchunk ? f % fchunk : 0;
-  if (rhs_uses_grid(s, m, std::min(f, fchunk)) || (tail && rhs_uses_grid(s, m, tail))) {
-    // no room for the tables: the direct product, as for the scratch below
-    cpm_status rc = ensure_nu(s);
-    if (rc == CPM_ENOMEM) s->nu.off = true;
-    else if (rc != CPM_OK) return rc;
-  }
+  const int64_t head = std::min(f, fchunk), tail = f > fchunk ? f % fchunk : 0;
   auto scratch = [&]() {
-    const int64_t e = rhs_scratch_elems(s, m, std::min(f, fchunk));
+    const int64_t e = rhs_scratch_elems(s, m, head);
     return tail ? std::max(e, rhs_scratch_elems(s, m, tail)) : e;
   };
+  NuGrid &nu = s->nu;
+  const bool pays = rhs_grid_pays(s, m, head) || (tail && rhs_grid_pays(s, m, tail));
+  if (pays && (!nu.sized || s->rhs_S_elems < scratch())) {
+    // the grids take at most a sixteenth of what is free (with the scratch
+    // that they replace), so that what the system allocates later fits as
+    // well; asked again only when the scratch grows anyway, so that a call of
+    // no larger size never moves it (a captured graph may hold its address)
+    size_t free_b = 0, total_b = 0;
+    (void)hipMemGetInfo(&free_b, &total_b);
+    nu.elems = std::min(nu.full, ((int64_t)(free_b / sizeof(double)) + s->rhs_S_elems) / 16);
+    nu.sized = true;
+  }
+  if (rhs_uses_grid(s, m, head) || (tail && rhs_uses_grid(s, m, tail))) {
+    const cpm_status rc = ensure_nu(s);
+    if (rc == CPM_ENOMEM) nu.elems = 0;   // no room for the tables: the direct product
+    else if (rc != CPM_OK) return rc;
+  }
   int64_t need = scratch();
   if (s->rhs_S_elems < need) {
     if (s->rhs_S) {
@@ -733,15 +744,8 @@ cpm_status cpm_rhs(cpm_system *s, const double *ion_pos_dev, const double *ion_q
       s->rhs_S_elems = 0;
     }
     cpm_status rc = dev_alloc(s, &s->rhs_S, need);
-    if (rc == CPM_ENOMEM && !s->nu.off && s->nu.elems > kNuFew) {
-      // the grid path's scratch is the larger one: try fewer grids at a time
-      s->nu.elems = kNuFew;
-      need = scratch();
-      rc = dev_alloc(s, &s->rhs_S, need);
-    }
-    if (rc == CPM_ENOMEM && !s->nu.off) {
-      // and without it
-      s->nu.off = true;
+    if (rc == CPM_ENOMEM && pays && nu.elems > 0) {
+      nu.elems = 0;   // without the grids
       need = scratch();
       rc = dev_alloc(s, &s->rhs_S, need);
     }

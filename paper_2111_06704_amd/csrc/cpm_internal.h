@@ -187,13 +187,11 @@ struct NuGrid {
   double *coef = nullptr;       // window polynomials
   const double *inv = nullptr;  // 1 / Phi per axis
   const int2 *col = nullptr;    // (k index of n_z = 0, largest |n_z|) by (n_x, n_y)
-  // doubles of grids at a time, then kNuFew when they do not fit: every launch
-  // ends with a nearly empty chip (32 frames of 7.9 M doubles: 4.6 ms for the
-  // right-hand side with 2^26, 8 frames a launch, 4.1 with all of them)
-  int64_t elems = (int64_t)1 << 28;
-  bool off = false;             // no room for the scratch: the direct product
+  // doubles of grids at a time (0: none, the direct product): at most `full`,
+  // set from the free memory when cpm_rhs sizes its scratch
+  int64_t full = 0, elems = 0;
+  bool sized = false;
 };
-constexpr int64_t kNuFew = (int64_t)1 << 26;
 
 struct Gcd {                 // capacitance coefficients (Supplementary Eq. S22-S24)
   bool ready = false;
@@ -360,6 +358,8 @@ int64_t rhs_scratch_elems(const cpm_system *s, int64_t m, int64_t f);
 // sizes of the grid path (system set-up), whether this call takes it, its tables
 void nu_sizes(cpm_system *s);
 bool rhs_uses_grid(const cpm_system *s, int64_t m, int64_t f);
+bool rhs_grid_pays(const cpm_system *s, int64_t m, int64_t f);
+int64_t nu_frame_elems(const cpm_system *s);
 cpm_status ensure_nu(cpm_system *s);
 // scratch of the plan limited to limit doubles (fewer partial buffers), and
 // the static scratch of cpm_rhs_noalloc: its size and this device's address

@@ -1518,6 +1518,15 @@ __global__ __launch_bounds__(64 * RS_W) void real_space_kernel(
 
 }  // namespace
 
+// doubles of one frame in the grid path's scratch: the grid, (n_z, part, x,
+// y) and (n_z, n_y, part, x)
+int64_t nu_frame_elems(const cpm_system *s) {
+  const NuGrid &g = s->nu;
+  const int64_t nz = g.m[2] + 1;
+  return (int64_t)g.g[0] * g.g[1] * g.g[2] + 2 * nz * g.g[0] * g.g[1] +
+         2 * nz * (2 * g.m[1] + 1) * g.g[0];
+}
+
 namespace {
 
 // Work split of one cpm_rhs call over f frames of m ions, and the layout of
@@ -1594,15 +1603,6 @@ int64_t wave_groups(int64_t waves, int64_t items, int64_t least, int64_t cap, in
   return per > 0 ? (items + per - 1) / per : 1;
 }
 
-// doubles of one frame in the grid path's scratch: the grid, (n_z, part, x,
-// y) and (n_z, n_y, part, x)
-int64_t nu_frame_elems(const cpm_system *s) {
-  const NuGrid &g = s->nu;
-  const int64_t nz = g.m[2] + 1;
-  return (int64_t)g.g[0] * g.g[1] * g.g[2] + 2 * nz * g.g[0] * g.g[1] +
-         2 * nz * (2 * g.m[1] + 1) * g.g[0];
-}
-
 // Whether the grid path beats the direct product, from the time of both at
 // the rates each was measured at. With few frames the densest tile's wave
 // sets the spreading time (an ion reaches 8 tiles; a slit's electrolyte is
@@ -1625,6 +1625,14 @@ bool nu_pays(const cpm_system *s, int64_t m, int64_t f) {
   return direct * (double)f > std::max(spread * (double)f, tile_wave) + dft * kNuDft * (double)f + kNuFixed;
 }
 
+}  // namespace
+
+bool rhs_grid_pays(const cpm_system *s, int64_t m, int64_t f) {
+  return s->kset.nk > 0 && m >= kCellMinIons && nu_pays(s, m, f);
+}
+
+namespace {
+
 // cap_* > 0 bound the ion groups of the structure factor, the k splits of
 // the back-projection and the ion groups of the real-space sum (fewer
 // partial buffers, less parallelism)
@@ -1639,7 +1647,7 @@ RhsPlan rhs_plan_capped(const cpm_system *s, int64_t m, int64_t f, int64_t cap_s
     p.sf_gemm = s->kset.smax < SG_SB * 16;
     const int64_t sf_blocks = p.sf_gemm ? (s->kset.ncols_pad / kSfTile) * f
                                         : std::max<int64_t>(1, rblocks) * f;
-    p.nu = grid && m >= kCellMinIons && nu_pays(s, m, f);
+    p.nu = grid && s->nu.elems >= nu_frame_elems(s) && rhs_grid_pays(s, m, f);
     const int64_t cap = std::max<int64_t>(1, std::min(cap_sf, kPartialCap / (2 * nk * f)));
     if (p.sf_gemm) {
       // whole chunks of ions per group, for about 1024 workgroups (three per
@@ -1678,7 +1686,7 @@ RhsPlan rhs_plan_capped(const cpm_system *s, int64_t m, int64_t f, int64_t cap_s
   if (p.nu) {
     p.sf_gemm = false;
     p.sf_groups = 1;
-    p.nu_frames = std::max<int64_t>(1, std::min<int64_t>(f, s->nu.elems / nu_frame_elems(s)));
+    p.nu_frames = std::min<int64_t>(f, s->nu.elems / nu_frame_elems(s));
   }
   if (m >= kCellMinIons) {
     p.rs_cell = true;
@@ -1713,7 +1721,7 @@ RhsPlan rhs_plan(const cpm_system *s, int64_t m, int64_t f, int64_t limit = 0) {
   // the factored back-projection first; without it when its per-node sums
   // do not fit the limit
   for (int planes = 1;; planes = 0) {
-    RhsPlan p = rhs_plan_capped(s, m, f, kNoCap, kNoCap, kNoCap, planes != 0, limit <= 0 && !s->nu.off);
+    RhsPlan p = rhs_plan_capped(s, m, f, kNoCap, kNoCap, kNoCap, planes != 0, limit <= 0);
     int64_t csf = p.sf_groups, cks = std::max<int64_t>(1, p.ksplit), crs = p.rs_groups;
     while (limit > 0 && p.total > limit && (csf > 1 || cks > 1 || crs > 1)) {
       const int64_t nk = std::max<int64_t>(s->kset.nk, 1);
@@ -1830,6 +1838,17 @@ void nu_sizes(cpm_system *s) {
   g.zpasses = (zt + NU_RZ - 1) / NU_RZ;
   g.zrows = (zt + g.zpasses - 1) / g.zpasses * g.zpasses * 16;
   for (int d = 0; d < 2; ++d) g.passes[d] = (g.m[d] + 1 + 16 * NU_K2 - 1) / (16 * NU_K2);
+  // Grids at a time: the more frames a launch has, the less its last waves
+  // count (8192 atoms, 32 frames of 7.0 M doubles: 5.0 ms with 256 MB, 4.6 with
+  // 512, 4.2 with 1 GB, 4.0 with 2 GB). But the scratch stays with the system,
+  // and once a process has been through the device's memory the driver clears
+  // what is released at some 0.03 TB/s: 300 systems of 1024 atoms in a row that
+  // each take 32 frames need 15 ms a system with 512 MB and 59 with 2 GB
+  // (single waits of 2 s). So, as for the phase matrix of the assembly, at most
+  // four times E, at least 512 MB and at most 2 GB; or one grid.
+  const int64_t frame = nu_frame_elems(s);
+  g.full = std::min<int64_t>((int64_t)1 << 28, std::max<int64_t>((int64_t)1 << 26, 4 * s->ld * s->ld));
+  g.full = std::max(g.full, frame);
 }
 
 bool rhs_uses_grid(const cpm_system *s, int64_t m, int64_t f) { return rhs_plan(s, m, f).nu; }
