@@ -1590,9 +1590,12 @@ __global__ __launch_bounds__(256) void coarse_prolong_kernel(
 // .. + 3) as one float4; step j (0..3) takes k = lg as the atom i + 4 lg + j,
 // with B = w(i + 4 lg + j, column 16 g + lr). The loads of the next 16 atoms
 // are under way during the products of these: 512 patches, 32768 atoms, 64
-// columns 45 us (56 without; the products alone 14).
+// columns 45 us (56 without; the products alone 14). The FP32 sums move to
+// FP64 registers every 64 atoms, whatever the slice length (one FP32 sum over
+// a slice of 256 to 8192 atoms would lose what a workgroup per 64 atoms
+// keeps); the few workgroups leave a wave per SIMD, whose registers they fit.
 template <int NG>
-__global__ __launch_bounds__(256) void coarse_gather_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void coarse_gather_kernel(
     const float *__restrict__ az, const double *__restrict__ wt, int64_t ld, int64_t mp,
     int64_t kslice, int cols, float *__restrict__ c2p, const int *__restrict__ gate) {
   const int go = gate != nullptr ? *gate : 1;
@@ -1602,10 +1605,24 @@ __global__ __launch_bounds__(256) void coarse_gather_kernel(
   const int64_t i0 = (int64_t)blockIdx.y * kslice;
   const int64_t i1 = min(ld, i0 + kslice);
   f4 acc[4][NG];
+  d4 accd[4][NG];
 #pragma unroll
   for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
-    for (int g = 0; g < NG; ++g) acc[rb][g] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int g = 0; g < NG; ++g) {
+      acc[rb][g] = f4{0.f, 0.f, 0.f, 0.f};
+      accd[rb][g] = d4{0.0, 0.0, 0.0, 0.0};
+    }
+  auto flush = [&]() {
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) accd[rb][g][v] += (double)acc[rb][g][v];
+        acc[rb][g] = f4{0.f, 0.f, 0.f, 0.f};
+      }
+  };
   f4 a[2][4];
   double b[2][4][NG];
   auto load = [&](auto buf, int64_t i) {
@@ -1642,7 +1659,9 @@ __global__ __launch_bounds__(256) void coarse_gather_kernel(
     step(even, i + 16);
     if (i + 16 >= i1) break;
     step(odd, i + 32);
+    if ((i - i0) & 32) flush();
   }
+  flush();
   float *out = c2p + (int64_t)blockIdx.y * cols * mp;
 #pragma unroll
   for (int rb = 0; rb < 4; ++rb)
@@ -1650,7 +1669,7 @@ __global__ __launch_bounds__(256) void coarse_gather_kernel(
     for (int g = 0; g < NG; ++g)
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        out[(int64_t)(g * 16 + lr) * mp + tb + 16 * rb + 4 * lg + v] = acc[rb][g][v];
+        out[(int64_t)(g * 16 + lr) * mp + tb + 16 * rb + 4 * lg + v] = (float)accd[rb][g][v];
 }
 
 // c[e] = sum over the ks slices of c2p (FP64), e < count, a multiple of 64:

@@ -1,0 +1,58 @@
+"""The sums (E Z)^T w of the coarse correction over long slices of atoms: many
+workgroups share a slice's patches, so a slice is 464 or 832 of 8192 atoms.
+
+With r of sum zero on every patch (small whole numbers, so exactly) the
+correction is z = w - Z E_c^-1 (E Z)^T w, w = P r, and the sums follow from
+z - w. They are compared with FP64 sums of the FP64 E in units of 2^-24 times
+the root of the sum of squares of their terms. E Z and w are rounded to FP32
+(2^-24 each at most, about one unit together), and an FP32 accumulator over L
+terms of either sign adds sqrt(L / 6) units (its rounding errors are uniform
+in 2^-24 of a partial sum that grows as a random walk): 3.3 for 64 terms, 9
+and 12 for whole slices. The largest of 64 columns x 3738 or 6600 patches is
+about 4.8 times that, 16 units; the limit is 24.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from oracle import precond as pc  # noqa: E402
+from paper_2111_06704_amd import workloads as wl  # noqa: E402
+
+
+@pytest.mark.parametrize("edge", [2.4, 1.62])
+def test_sums_over_long_slices(edge):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2111_06704_amd import cpm
+    geo = wl.electrode_geometry("sums", 32, 32, False, [10.0], [50.0], 60.0)
+    pos = geo.pos + np.array([0.3, 0.2, 0.0])
+    pid = pc.coarse_patches(pos, geo.box, edge)
+    m = int(pid.max()) + 1
+    print(f"[case] N={geo.n} patches {m}", flush=True)
+    S = cpm.System(pos, geo.box)
+    S.precond_dc(0.083, 8.0)
+    rng = np.random.default_rng(m)
+    cols = 64
+    r = rng.integers(-3, 4, size=(cols, geo.n)).astype(np.float64)
+    last = np.zeros(m, dtype=np.int64)
+    last[pid] = np.arange(geo.n)   # one atom per patch takes what is left
+    sums = np.zeros((cols, m))
+    np.add.at(sums, (slice(None), pid), r)
+    r[:, last] -= sums
+    dev = "cuda"
+    rt, pt = torch.tensor(r, device=dev), torch.tensor(pid, device=dev)
+    w = S.precond_apply(rt)
+    S.precond_coarse(edge)
+    z = S.precond_apply(rt)
+    E = S.get_E(cpm.PREC_F64)
+    EZ = torch.zeros((geo.n, m), device=dev, dtype=torch.float64).index_add_(1, pt, E)
+    Ec = torch.zeros((m, m), device=dev, dtype=torch.float64).index_add_(0, pt, EZ)
+    g2 = (w - z)[:, torch.tensor(last, device=dev)]
+    c2 = g2 @ Ec
+    exact = w @ EZ
+    unit = torch.sqrt((w * w) @ (EZ * EZ)) * 2.0 ** -24
+    err = float(((c2 - exact).abs() / unit).max())
+    print(f"[case] error {err:.1f} units", flush=True)
+    assert err <= 24.0, err
