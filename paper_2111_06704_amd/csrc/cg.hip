@@ -1397,6 +1397,32 @@ precond_block_kernel(
   }
 }
 
+// z = P r again for the rows that the tiles' product leaves not finite: over
+// the entries of P alone, so that a NaN or an infinity of r reaches the rows
+// whose pattern holds its atom and no others (0 * NaN is NaN). For vectors of
+// the caller; inside a solve such a column is lost either way. Workgroup = 8
+// rows of a tile by 32 columns; r from the row-interleaved rt.
+__global__ __launch_bounds__(256) void precond_rows_kernel(
+    const double *__restrict__ rt, double *__restrict__ z, const int64_t *__restrict__ uoff,
+    const int32_t *__restrict__ uidx, const double *__restrict__ blk,
+    const int32_t *__restrict__ order, int64_t ld, int64_t n, int fc) {
+  constexpr int PER = kPcTile / 8;
+  const int64_t tile = blockIdx.x / PER;
+  const int row = (int)(blockIdx.x % PER) * 8 + (threadIdx.x & 7);
+  const int c = (int)blockIdx.y * 32 + (threadIdx.x >> 3);
+  const int64_t t = tile * kPcTile + row;
+  if (t >= n || c >= fc) return;
+  double *zi = z + (int64_t)c * ld + order[t];
+  if (isfinite(*zi)) return;
+  const double *r = rt + (int64_t)(c / kColGroup) * ld * kColGroup + c % kColGroup;
+  double s = 0.0;
+  for (int64_t k = uoff[tile]; k < uoff[tile + 1]; ++k) {
+    const double a = blk[k * kPcTile + row];
+    if (a != 0.0) s = fma(a, r[(int64_t)uidx[k] * kColGroup], s);
+  }
+  *zi = s;
+}
+
 // ---- coarse-space correction (two-level, balancing Neumann-Neumann form)
 // z = P_D^T P P_D r + Q r with Q = Z E_c^-1 Z^T, P_D = I - E Q, Z the
 // indicator columns of the patches, applied as
@@ -2966,6 +2992,12 @@ cpm_status precond_cols(cpm_system *s, const double *r_dev, int64_t f, double *z
                        (const int *)nullptr);
     launch_precond<double>(st, s, s->pc, in, r_dev + f0 * n, n, fc, out, (double *)nullptr, cols,
                            nullptr, 0, nullptr, false, nullptr);
+    if (!s->cz.ready && s->pc.gap == 0.0)   // (these reach every row)
+      hipLaunchKernelGGL(precond_rows_kernel,
+                         dim3((unsigned)(s->pc.ntiles * (kPcTile / 8)), (unsigned)((fc + 31) / 32)),
+                         dim3(256), 0, st, (const double *)in, out, (const int64_t *)s->pc.uoff,
+                         (const int32_t *)s->pc.uidx, (const double *)s->pc.blk, s->atom_order, ld,
+                         n, fc);
     CPM_HIP_CHECK(hipMemcpy2DAsync(z_dev + f0 * n, sizeof(double) * n, out, sizeof(double) * ld,
                                    sizeof(double) * n, fc, hipMemcpyDeviceToDevice, st));
   }
