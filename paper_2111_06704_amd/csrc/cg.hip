@@ -980,14 +980,13 @@ __device__ inline double add_slices(const VT *__restrict__ part, int slices, int
   for (int m = SM; m < slices; ++m) v += (double)part[m * stride + idx];
   return v;
 }
-// the smallest of 1, 2, 4, 7, 9, 12, 16 that is at least the slice count (16 above)
+// the smallest power of two that is at least the slice count (16 above): at
+// most half of the loads repeat the last slice
 template <typename F> void with_slices(int slices, F &&f) {
   if (slices <= 1) f(std::integral_constant<int, 1>());
   else if (slices <= 2) f(std::integral_constant<int, 2>());
   else if (slices <= 4) f(std::integral_constant<int, 4>());
-  else if (slices <= 7) f(std::integral_constant<int, 7>());
-  else if (slices <= 9) f(std::integral_constant<int, 9>());
-  else if (slices <= 12) f(std::integral_constant<int, 12>());
+  else if (slices <= 8) f(std::integral_constant<int, 8>());
   else f(std::integral_constant<int, 16>());
 }
 
