@@ -336,14 +336,15 @@ std::vector<int32_t> syrk_tile_order(int64_t T) {
 // Parts of the k range: the chip holds 512 workgroups (two per CU), so
 // `tiles` of them take ceil(tiles parts / 512) / parts rounds; more parts
 // also cost their planes' traffic (about 1 % of a round each at 41 000
-// columns). 4608 atoms, 666 tiles,
+// columns) and memory, which the caller limits. 4608 atoms, 666 tiles,
 // 41 000 columns: 15.6 ms undivided, 13.7 with 3 parts (the planes cost
 // finalize_kernel 0.04), 14.6 with 5, 13.5 with 8 (0.15).
-int syrk_splits(int64_t ld, int64_t kdim) {
+int syrk_splits(int64_t ld, int64_t kdim, int64_t plane_elems) {
   const int64_t T = ld / SY_TILE, tiles = T * (T + 1) / 2;
+  const int64_t most = 1 + plane_elems / syrk_plane_elems(ld);
   int best = 1;
   double cost = 1e300;
-  for (int q = 1; q <= 16 && q * 8 * SY_KB <= kdim; ++q) {
+  for (int q = 1; q <= std::min<int64_t>(16, most) && q * 8 * SY_KB <= kdim; ++q) {
     const double c = (double)((tiles * q + 511) / 512) / q + 400.0 * (q - 1) / (double)kdim;
     if (c < cost) {
       cost = c;

@@ -329,7 +329,8 @@ hipError_t launch_phase_matrix(hipStream_t st, const double *pos, int64_t n, int
 // lower-triangular tile list of the contraction (pairs ti >= tj, in the
 // order the kernel walks them) for T = ld / 128 tile rows
 std::vector<int32_t> syrk_tile_order(int64_t T);
-int syrk_splits(int64_t ld, int64_t kdim);
+// parts of the k range whose planes (all but one) hold at most plane_elems doubles
+int syrk_splits(int64_t ld, int64_t kdim, int64_t plane_elems);
 int64_t syrk_plane_elems(int64_t ld);
 hipError_t launch_syrk_lower(hipStream_t st, const double *A, int64_t kdim,
                              const int32_t *tiles, int64_t ld, double *E, int64_t lde, double *P,
