@@ -2140,11 +2140,15 @@ int64_t f64s_slices(int64_t ld, int64_t cols) {
   return wide_slices(ld, cols, sizeof(double), sizeof(double), 256);
 }
 
-// k slices of the row-split kernel (16 columns): about 216 workgroups (N =
-// 4608, FP32: 17.6 us with 216, 18.3 with 432, and fewer partial sums for
-// the update to read; FP64, whose reads need more in flight: 36 us with 360,
-// 31.3 with 432, 30.1 with 504), each slice a multiple of the k step, at least four steps,
-// and short enough for its P copy in LDS
+// k slices of the row-split kernel (16 columns): as many as give 216
+// workgroups, so that a slice more than asked for still leaves one to a CU
+// (product with its pack and sum, FP32, 216 and 256 workgroups asked for: N =
+// 2304 25.8 and 27.2 us, 3456 29.3 and 34.6, 4608 36.5 and 41.6, 5280 39.7 and
+// 48.3, no difference at 1152 and from 6144 on; 432 is ahead at 6144 only, 46.8
+// against 52.1). FP64 above ld = 2048: its reads need more in flight, two to a
+// CU (504 against 216: 48.6 and 54.5 us at 4608, 57.9 and 60.8 at 5280; but 32.6
+// and 29.0 at 2304, 41.0 and 36.6 at 3456). Each slice is a multiple of the k
+// step, at least four steps, and short enough for its P copy in LDS.
 template <typename T> int64_t rows_slices(int64_t ld, int64_t &kslice) {
   constexpr int64_t kb = 4 * Mv<T>::VEC;
   const int64_t blocks = ld / (16 * mr_waves(ld));

@@ -430,8 +430,8 @@ __global__ __launch_bounds__(256, 2) void sf_gemm_kernel(
 //   space; S(-K) = conj(S(K))).
 // 50 000 ions x 32 frames, 120 500 vectors (box 79 x 136 x 120 A): structure
 // factors 19.0 -> 4.3 ms; 20 000 ions x 64 frames: 15.6 -> 5.6 ms. Error of b
-// against the same sums in long double: 1.7e-15 and 2.2e-15 of |b| (the
-// direct product 1.4e-13 and 2.1e-14).
+// against the same sums in long double at 2592 atoms, 12 000 ions and 38 000
+// vectors: 6.7e-16 of max|b|, with the direct product 1.0e-15.
 constexpr int NU_W = 16;              // support of the window (grid points)
 constexpr int NU_DEG = 13;            // degree of its polynomials per interval
 constexpr double NU_BETA = 2.3 * NU_W;
@@ -1550,8 +1550,12 @@ struct RhsPlan {
           off_hist = 0, off_cstart = 0, total = 0;
 };
 
-// below this many ions per frame the cell list costs more than it saves
-// (measured: 2000 ions, 4608 atoms: the all-pairs kernel takes 126 us)
+// From this many ions per frame they are sorted into cells: the spreading of
+// the grid path needs the list, so this is also where grids begin. For the
+// real-space sums alone the line lies too low: the whole call without k-vectors,
+// list and all pairs, takes 168 and 58 us at 2304 atoms and 8192 ions of one
+// frame, 228 and 152 at 8192 atoms and 16 frames, and all pairs are ahead up to
+// 20 000 ions at every size measured (8192 atoms, 16 frames: 351 and 317 us).
 constexpr int64_t kCellMinIons = 8192;
 
 // Cells of edge >= rcut / 2 (widened until there are at most kMaxCells).
@@ -1844,8 +1848,8 @@ void nu_sizes(cpm_system *s) {
   // and once a process has been through the device's memory the driver clears
   // what is released at some 0.03 TB/s: 300 systems of 1024 atoms in a row that
   // each take 32 frames need 15 ms a system with 512 MB and 59 with 2 GB
-  // (single waits of 2 s). So, as for the phase matrix of the assembly, at most
-  // four times E, at least 512 MB and at most 2 GB; or one grid.
+  // (single waits of 2 s). So at most four times E (whose assembly takes the
+  // longer the larger it is), at least 512 MB and at most 2 GB; or one grid.
   const int64_t frame = nu_frame_elems(s);
   g.full = std::min<int64_t>((int64_t)1 << 28, std::max<int64_t>((int64_t)1 << 26, 4 * s->ld * s->ld));
   g.full = std::max(g.full, frame);
