@@ -735,7 +735,11 @@ cpm_status cpm_rhs(cpm_system *s, const double *ion_pos_dev, const double *ion_q
     nu.sized = true;
   }
   if (rhs_uses_grid(s, m, head) || (tail && rhs_uses_grid(s, m, tail))) {
-    const cpm_status rc = ensure_nu(s);
+    cpm_status rc = CPM_ENOMEM;
+    try {
+      rc = ensure_nu(s);
+    } catch (const std::bad_alloc &) {   // its host tables
+    }
     if (rc == CPM_ENOMEM) nu.elems = 0;   // no room for the tables: the direct product
     else if (rc != CPM_OK) return rc;
   }
