@@ -1610,15 +1610,17 @@ __global__ __launch_bounds__(256) void coarse_prolong_kernel(
 // Slice partials of (E Z)^T w on the FP32 matrix cores: c2p[(k * cols + c) *
 // mp + t] = sum over the atoms i of slice k of az(t, i) w(i, c), w from the
 // row-interleaved wt. Workgroup: kCoarseAlign patches (wave w: 64 of them,
-// four row blocks of 16) and one slice of kslice atoms (a multiple of 16).
+// four row blocks of 16) and one slice of kslice atoms (a multiple of 64).
 // Per 16 atoms lane (lr, lg) loads az(patch tb + 16 rb + lr, atoms i + 4 lg
 // .. + 3) as one float4; step j (0..3) takes k = lg as the atom i + 4 lg + j,
 // with B = w(i + 4 lg + j, column 16 g + lr). The loads of the next 16 atoms
-// are under way during the products of these: 512 patches, 32768 atoms, 64
-// columns 45 us (56 without; the products alone 14). The FP32 sums move to
-// FP64 registers every 64 atoms, whatever the slice length (one FP32 sum over
-// a slice of 256 to 8192 atoms would lose what a workgroup per 64 atoms
-// keeps); the few workgroups leave a wave per SIMD, whose registers they fit.
+// are under way during the products of these, and the loop body is one
+// straight path of 64 atoms (a slice is a multiple), at whose end the FP32 sums
+// move to FP64 registers: one FP32 sum over a slice of 256 to 8192 atoms would
+// lose what a slice of 64 keeps. 512 patches, 32768 atoms, 64 columns 30 us (37
+// with steps of 16 and no move; the products alone 14), 4096 patches, 131072
+// atoms, 32 columns 459 us (503). The 256 workgroups leave a wave per SIMD, whose
+// registers hold both sums.
 template <int NG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void coarse_gather_kernel(
     const float *__restrict__ az, const double *__restrict__ wt, int64_t ld, int64_t mp,
@@ -1680,13 +1682,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const std::integral_constant<int, 1> odd;
   load(even, i0);
   if (go == 0) return;
-  for (int64_t i = i0; i < i1; i += 32) {
+  for (int64_t i = i0; i < i1; i += 64) {
     step(even, i + 16);
-    if (i + 16 >= i1) break;
     step(odd, i + 32);
-    if ((i - i0) & 32) flush();
+    step(even, i + 48);
+    step(odd, i + 64);
+    flush();
   }
-  flush();
   float *out = c2p + (int64_t)blockIdx.y * cols * mp;
 #pragma unroll
   for (int rb = 0; rb < 4; ++rb)
@@ -2788,14 +2790,14 @@ cpm_status solve_columns(cpm_system *s, int fc, const cpm_solve_opts &o, cpm_sol
 }  // namespace
 
 // slices of the Z^T-side coarse product: about 256 workgroups of
-// kCoarseAlign patches, at least 64 atoms and a multiple of 16 per slice
+// kCoarseAlign patches, a multiple of 64 atoms per slice
 // (512 patches, 64 columns: 50 us with the sum of the slices, 57 with 512
 // workgroups, 73 with 1024)
 void coarse_slices(int64_t ld, int64_t mp, int &ks, int64_t &kslice) {
   const int64_t pw = std::max<int64_t>(1, mp / kCoarseAlign);
   int64_t want = std::max<int64_t>(1, (256 + pw - 1) / pw);
   want = std::min<int64_t>(want, std::max<int64_t>(1, ld / 64));
-  kslice = round_up((ld + want - 1) / want, 16);
+  kslice = round_up((ld + want - 1) / want, 64);
   ks = (int)((ld + kslice - 1) / kslice);
 }
 

@@ -1,5 +1,5 @@
 """The sums (E Z)^T w of the coarse correction over long slices of atoms: many
-workgroups share a slice's patches, so a slice is 464 or 832 of 8192 atoms.
+workgroups share a slice's patches, so a slice is 512 or 832 of 8192 atoms.
 
 With r of sum zero on every patch (small whole numbers, so exactly) the
 correction is z = w - Z E_c^-1 (E Z)^T w, w = P r, and the sums follow from
