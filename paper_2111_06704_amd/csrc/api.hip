@@ -563,14 +563,13 @@ cpm_status cpm_build_E(const double *pos_host, int64_t n, const double *box_host
   // Reciprocal part A A^T in chunks of k-vectors whose phase matrix stays
   // under 24 GiB (or a third of the free memory): every chunk but the first
   // adds to the lower tiles of E, so larger chunks re-read E less often. It
-  // also stays under 1.5 E64 (or 64 MiB) and the planes of the split k range
-  // under 9/8 E64, which is two (or 64 MiB): a build allocates and releases
-  // both, and once a process has been through the device's memory the driver
-  // clears what is released at some 0.04 TB/s. Builds in a row, as of electrodes
-  // that move, wait when they release more in their time. With 4 E64 and up to
-  // 15 planes, 900 builds in a row took 15.1 ms at first and then 18 to 44 each
-  // (single waits of 3 s) at 4608 atoms, 12.6 and 20 to 39 at 4096; now 15.3 and
-  // 13.6 throughout.
+  // also stays, with the planes of the split k range, under 2.5 E64 (or 128
+  // MiB): a build allocates and releases both, and once a process has been
+  // through the device's memory the driver clears what is released at some
+  // 0.04 TB/s. Builds in a row, as of electrodes that move, wait when they
+  // release more in their time. With 4 E64 and up to 15 planes, 900 builds in a
+  // row took 15.1 ms at first and then 18 to 44 each (single waits of 3 s) at
+  // 4608 atoms, 12.6 and 20 to 39 at 4096; now 15.2 and 13.5 throughout.
   // finalize_kernel writes every entry of E (padding included), so E needs
   // no clearing.
   double *A = nullptr, *P = nullptr;   // phase matrix, planes of the split k range
@@ -584,13 +583,9 @@ cpm_status cpm_build_E(const double *pos_host, int64_t n, const double *box_host
     size_t free_b = 0, total_b = 0;
     (void)hipMemGetInfo(&free_b, &total_b);
     size_t budget = std::min<size_t>((size_t)24 << 30, free_b / 3);
-    const size_t e64 = sizeof(double) * ld * ld, least = (size_t)64 << 20;
-    budget = std::min<size_t>(budget, std::max<size_t>(least, e64 + e64 / 2));
-    int64_t kc = (int64_t)(budget / (sizeof(double) * 2 * (size_t)ld));
-    kc = std::max<int64_t>(8, kc / 8 * 8);
-    // equal chunks (the last one is not padded with zero columns)
-    const int64_t nchunks = (nk + kc - 1) / kc;
-    kc = round_up((nk + nchunks - 1) / nchunks, 8);
+    budget = std::min<size_t>(budget, std::max<size_t>((size_t)128 << 20, 5 * sizeof(double) * ld * ld / 2));
+    const SyrkPlan plan = syrk_plan(ld, nk, (int64_t)budget);
+    const int64_t kc = plan.kc;
     const int64_t lda = 2 * kc;
     const std::vector<int32_t> order_t = syrk_tile_order(ld / 128);
     if ((int64_t)order_t.size() != (ld / 128) * (ld / 128 + 1)) {
@@ -609,7 +604,7 @@ cpm_status cpm_build_E(const double *pos_host, int64_t n, const double *box_host
       set_error("phase matrix allocation failed");
       return fail(CPM_ENOMEM);
     }
-    parts = syrk_splits(ld, round_up(2 * kc, 16), (int64_t)(std::max(least, e64 + e64 / 8) / sizeof(double)));
+    parts = plan.parts;
     if (parts > 1 &&
         hipMalloc((void **)&P, sizeof(double) * (parts - 1) * syrk_plane_elems(ld)) != hipSuccess) {
       (void)hipGetLastError();

@@ -84,7 +84,7 @@ __device__ inline void tri_index(int64_t t, int64_t &ti, int64_t &tj) {
 // Grid y splits the stages: part 0 writes E, part q > 0 the packed tile
 // (row-major triangle order) of plane q - 1 of P, which finalize_kernel adds.
 // Few tiles would otherwise leave most of the chip idle in the last round
-// (rule in syrk_splits).
+// (rule in syrk_plan).
 __global__ __launch_bounds__(256, 2) void syrk_lower_kernel(const double *__restrict__ A, int64_t nrows,
                                                          int64_t kdim,
                                                          const int32_t *__restrict__ tiles,
@@ -333,29 +333,40 @@ std::vector<int32_t> syrk_tile_order(int64_t T) {
   return t;
 }
 
-// Parts of the k range: the chip holds 512 workgroups (two per CU), so
-// `tiles` of them take ceil(tiles parts / 512) / parts rounds; more parts
-// also cost their planes' traffic (about 1 % of a round each at 41 000
-// columns) and memory, which the caller limits. 4608 atoms, 666 tiles,
-// 41 000 columns: 15.6 ms undivided, 13.7 with 3 parts (the planes cost
-// finalize_kernel 0.04), 14.6 with 5, 13.5 with 8 (0.15).
-int syrk_splits(int64_t ld, int64_t kdim, int64_t plane_elems) {
-  const int64_t T = ld / SY_TILE, tiles = T * (T + 1) / 2;
-  const int64_t most = 1 + plane_elems / syrk_plane_elems(ld);
-  int best = 1;
-  double cost = 1e300;
-  for (int q = 1; q <= std::min<int64_t>(16, most) && q * 8 * SY_KB <= kdim; ++q) {
-    const double c = (double)((tiles * q + 511) / 512) / q + 400.0 * (q - 1) / (double)kdim;
-    if (c < cost) {
-      cost = c;
-      best = q;
-    }
-  }
-  return tiles > 16 * 512 ? 1 : best;
-}
 int64_t syrk_plane_elems(int64_t ld) {
   const int64_t T = ld / SY_TILE;
   return T * (T + 1) / 2 * (SY_TILE * SY_TILE);
+}
+
+// Chunks and parts of the k range. The chip holds 512 workgroups (two per CU),
+// so `tiles` of them take ceil(tiles parts / 512) / parts rounds; but the parts'
+// planes and the phase matrix of a chunk share `budget` bytes, and every chunk
+// reads and writes the lower tiles and the planes once more. 4608 atoms, 666
+// tiles, 41 000 columns: 15.6 ms undivided, 13.7 with 3 parts (the planes cost
+// finalize_kernel 0.04), 14.6 with 5, 13.5 with 8 (0.15).
+SyrkPlan syrk_plan(int64_t ld, int64_t nk, int64_t budget) {
+  const int64_t T = ld / SY_TILE, tiles = T * (T + 1) / 2;
+  const double plane = (double)(sizeof(double) * syrk_plane_elems(ld));
+  const double round = 512.0 * 2.0 * SY_TILE * SY_TILE * 2.0 * (double)nk / 66e12;   // s, undivided
+  SyrkPlan best;
+  double cost = 1e300;
+  for (int q = 1; q <= (tiles > 16 * 512 ? 1 : 16); ++q) {
+    const int64_t left = budget - (int64_t)((q - 1) * plane);
+    int64_t kc = std::max<int64_t>(8, left / (int64_t)(sizeof(double) * 2 * ld) / 8 * 8);
+    const int64_t chunks = (nk + kc - 1) / kc;
+    // equal chunks (the last one is not padded with zero columns)
+    kc = (nk + chunks - 1) / chunks;
+    kc = (kc + 7) / 8 * 8;
+    if (q > 1 && (left < budget / 4 || q * 4 * SY_KB > kc)) break;
+    const double c = (double)((tiles * q + 511) / 512) / q * round +
+                     (double)chunks * (2.0 * q * plane / 5e12 + 20e-6);
+    if (c < cost) {
+      cost = c;
+      best.parts = q;
+      best.kc = kc;
+    }
+  }
+  return best;
 }
 
 hipError_t launch_syrk_lower(hipStream_t st, const double *A, int64_t kdim,

@@ -329,8 +329,13 @@ hipError_t launch_phase_matrix(hipStream_t st, const double *pos, int64_t n, int
 // lower-triangular tile list of the contraction (pairs ti >= tj, in the
 // order the kernel walks them) for T = ld / 128 tile rows
 std::vector<int32_t> syrk_tile_order(int64_t T);
-// parts of the k range whose planes (all but one) hold at most plane_elems doubles
-int syrk_splits(int64_t ld, int64_t kdim, int64_t plane_elems);
+// k-vectors per chunk (a multiple of 8) and parts of the k range, whose phase
+// matrix and planes (all parts but one) stay within budget bytes
+struct SyrkPlan {
+  int parts = 1;
+  int64_t kc = 8;
+};
+SyrkPlan syrk_plan(int64_t ld, int64_t nk, int64_t budget);
 int64_t syrk_plane_elems(int64_t ld);
 hipError_t launch_syrk_lower(hipStream_t st, const double *A, int64_t kdim,
                              const int32_t *tiles, int64_t ld, double *E, int64_t lde, double *P,
