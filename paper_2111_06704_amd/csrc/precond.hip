@@ -21,6 +21,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstdlib>
+#include <memory>
 #include <string>
 #include <thread>
 
@@ -166,9 +167,11 @@ void block_pattern(Precond &p, int64_t n) {
     std::copy(u[t].begin(), u[t].end(), p.h_uidx.begin() + p.h_uoff[t]);
 }
 
-// the dense tile entries (host): P minus gap on its pattern
-std::vector<double> block_values(const Precond &p, int64_t n, double gap) {
-  std::vector<double> b((size_t)p.h_uoff[p.ntiles] * kPcTile, 0.0);
+// the dense tile entries (host): P minus gap on its pattern. Every thread
+// clears its own tiles: cleared by one thread first, the array's new pages
+// took half of the time (51 MB at 4608 atoms, r_cut 12 A).
+std::unique_ptr<double[]> block_values(const Precond &p, int64_t n, double gap) {
+  std::unique_ptr<double[]> b(new double[(size_t)p.h_uoff[p.ntiles] * kPcTile]);
   parallel_for(p.ntiles, [&](int64_t t, int) {
     const int32_t *u0 = p.h_uidx.data() + p.h_uoff[t];
     int64_t K = p.h_uoff[t + 1] - p.h_uoff[t];
@@ -178,7 +181,8 @@ std::vector<double> block_values(const Precond &p, int64_t n, double gap) {
         K = i;
         break;
       }
-    double *bt = b.data() + (size_t)p.h_uoff[t] * kPcTile;
+    double *bt = b.get() + (size_t)p.h_uoff[t] * kPcTile;
+    std::fill(bt, b.get() + (size_t)p.h_uoff[t + 1] * kPcTile, 0.0);
     for (int64_t r = t * kPcTile; r < std::min<int64_t>(n, (t + 1) * kPcTile); ++r)
       for (int k = 0; k < p.h_len[r]; ++k) {
         const int32_t j = p.h_idx[(size_t)r * p.width + k];
@@ -193,10 +197,11 @@ std::vector<double> block_values(const Precond &p, int64_t n, double gap) {
 // the system's preconditioner (the previous one is freed)
 cpm_status install_precond(cpm_system *s, Precond &p) {
   block_pattern(p, s->n);
-  const std::vector<double> b = block_values(p, s->n, 0.0);
+  const std::unique_ptr<double[]> b = block_values(p, s->n, 0.0);
+  const size_t b_bytes = sizeof(double) * (size_t)p.h_uoff[p.ntiles] * kPcTile;
   if (hipMalloc((void **)&p.uoff, sizeof(int64_t) * p.h_uoff.size()) != hipSuccess ||
       hipMalloc((void **)&p.uidx, sizeof(int32_t) * p.h_uidx.size()) != hipSuccess ||
-      hipMalloc((void **)&p.blk, sizeof(double) * b.size()) != hipSuccess) {
+      hipMalloc((void **)&p.blk, b_bytes) != hipSuccess) {
     (void)hipGetLastError();
     free_precond(p);
     set_error("preconditioner allocation failed");
@@ -206,10 +211,9 @@ cpm_status install_precond(cpm_system *s, Precond &p) {
                                hipMemcpyHostToDevice, s->stream));
   CPM_HIP_CHECK(hipMemcpyAsync(p.uidx, p.h_uidx.data(), sizeof(int32_t) * p.h_uidx.size(),
                                hipMemcpyHostToDevice, s->stream));
-  CPM_HIP_CHECK(hipMemcpyAsync(p.blk, b.data(), sizeof(double) * b.size(),
-                               hipMemcpyHostToDevice, s->stream));
+  CPM_HIP_CHECK(hipMemcpyAsync(p.blk, b.get(), b_bytes, hipMemcpyHostToDevice, s->stream));
   p.bytes = (int64_t)(sizeof(int64_t) * p.h_uoff.size() + sizeof(int32_t) * p.h_uidx.size() +
-                      sizeof(double) * b.size());
+                      b_bytes);
   CPM_HIP_CHECK(hipStreamSynchronize(s->stream));
   p.sum_p = 0.0;
   for (size_t e = 0; e < p.h_val.size(); ++e) p.sum_p += p.h_val[e];   // padding entries are 0
@@ -817,9 +821,9 @@ cpm_status cpm_precond_gap(cpm_system *s, int enable, double *gap_out) {
     // 1^T E^-1 1 = 1^T d' = C_ele
     gap = n_zero > 0.0 ? (s->c_ele - p.sum_p) / n_zero : 0.0;
   }
-  const std::vector<double> b = block_values(p, s->n, gap);
-  CPM_HIP_CHECK(hipMemcpyAsync(p.blk, b.data(), sizeof(double) * b.size(), hipMemcpyHostToDevice,
-                               s->stream));
+  const std::unique_ptr<double[]> b = block_values(p, s->n, gap);
+  CPM_HIP_CHECK(hipMemcpyAsync(p.blk, b.get(), sizeof(double) * (size_t)p.h_uoff[p.ntiles] * kPcTile,
+                               hipMemcpyHostToDevice, s->stream));
   CPM_HIP_CHECK(hipStreamSynchronize(s->stream));
   p.gap = gap;
   if (gap_out) *gap_out = gap;
