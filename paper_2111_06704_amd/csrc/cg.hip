@@ -980,13 +980,18 @@ __device__ inline double add_slices(const VT *__restrict__ part, int slices, int
   for (int m = SM; m < slices; ++m) v += (double)part[m * stride + idx];
   return v;
 }
-// the smallest power of two that is at least the slice count (16 above): at
-// most half of the loads repeat the last slice
+// the smallest of 1, 2, 3, 4, 6, 8, 12, 16 that is at least the slice count (16
+// above): at most half more loads than slices. With powers of two alone the
+// iteration of 2304 atoms (12 slices of an FP32 E) took 23.6 us against 21.7, of
+// 3520 (9) 27.0 against 25.8.
 template <typename F> void with_slices(int slices, F &&f) {
   if (slices <= 1) f(std::integral_constant<int, 1>());
   else if (slices <= 2) f(std::integral_constant<int, 2>());
+  else if (slices <= 3) f(std::integral_constant<int, 3>());
   else if (slices <= 4) f(std::integral_constant<int, 4>());
+  else if (slices <= 6) f(std::integral_constant<int, 6>());
   else if (slices <= 8) f(std::integral_constant<int, 8>());
+  else if (slices <= 12) f(std::integral_constant<int, 12>());
   else f(std::integral_constant<int, 16>());
 }
 
